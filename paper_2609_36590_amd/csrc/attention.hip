@@ -359,8 +359,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     if (n_groups == 1) {
       // the only group: the merge of groups reduces to o / l for it (weight 1), so finish here
       const int rl = qv / a.G, gq = qv - rl * a.G;
-      *reinterpret_cast<float4*>(a.out + (size_t)(mrow0 + rl) * qstride + (h * a.G + gq) * HD + d) =
-          make_float4(o_r[0] / l_r, o_r[1] / l_r, o_r[2] / l_r, o_r[3] / l_r);
+      act_put4<T>(a.out, qstride >> 5, mrow0 + rl, (h * a.G + gq) * HD + d,
+                  make_float4(o_r[0] / l_r, o_r[1] / l_r, o_r[2] / l_r, o_r[3] / l_r));
     } else {
       float* pp = part + (size_t)qv * PS;
       *reinterpret_cast<float4*>(pp + d) = make_float4(o_r[0], o_r[1], o_r[2], o_r[3]);
@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // Merge of the group partials: an 8-lane team per (query vector, 4 columns). Lane j merges groups
 // j, j+8, .. left to right from the identity (4 groups' loads in flight at a time), then the team
 // merges pairwise with a fixed butterfly; both lanes of a pair compute merge(lower, upper).
-template <int HD>
+template <typename T, int HD>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
   constexpr int PS = HD + 4, HD4 = HD / 4;
   const int h = blockIdx.y % a.n_kv, rb = blockIdx.y / a.n_kv;
@@ -432,8 +432,8 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
   }
   if (j == 0) {
     const int rl = qv / a.G, gq = qv - rl * a.G;
-    *reinterpret_cast<float4*>(a.out + (size_t)(mrow0 + rl) * a.n_heads * HD + (h * a.G + gq) * HD + d) =
-        make_float4(o_r[0] / l_r, o_r[1] / l_r, o_r[2] / l_r, o_r[3] / l_r);
+    act_put4<T>(a.out, a.n_heads * HD >> 5, mrow0 + rl, (h * a.G + gq) * HD + d,
+                make_float4(o_r[0] / l_r, o_r[1] / l_r, o_r[2] / l_r, o_r[3] / l_r));
   }
 }
 
@@ -692,12 +692,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 
   // lane (qv, kg) holds dims dt*16 + 4kg .. +3 of query vector qv
   if (qok && n_split == 1) {
-    float* op = a.out + (size_t)(r0 + rl) * qstride + (h * a.G + gq) * HD;
     const float inv = 1.f / l_c;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      *reinterpret_cast<float4*>(op + dt * 16 + 4 * kg) =
-          make_float4(o_c[dt][0] * inv, o_c[dt][1] * inv, o_c[dt][2] * inv, o_c[dt][3] * inv);
+      act_put4<T>(a.out, qstride >> 5, r0 + rl, (h * a.G + gq) * HD + dt * 16 + 4 * kg,
+                  make_float4(o_c[dt][0] * inv, o_c[dt][1] * inv, o_c[dt][2] * inv, o_c[dt][3] * inv));
   } else if (qok) {
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -709,6 +708,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 
 // The partials of a split one-launch pass merged in split order (the online-softmax merge),
 // normalised and written: one thread per (row, head, 4 dims).
+template <typename T>
 __global__ void __launch_bounds__(256) k_prefill_merge(AttnArgs a) {
   const int hd4 = a.head_dim / 4;
   const long long rh_n = (long long)a.R * a.n_heads;
@@ -725,7 +725,9 @@ __global__ void __launch_bounds__(256) k_prefill_merge(AttnArgs a) {
     softmax_merge(m, l, o, ml.x, ml.y, ov, 4);
   }
   const float inv = 1.f / l;
-  *reinterpret_cast<float4*>(a.out + rh * a.head_dim + d) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+  const int row = (int)(rh / a.n_heads), head = (int)(rh - (long long)row * a.n_heads);
+  act_put4<T>(a.out, a.n_heads * a.head_dim >> 5, row, head * a.head_dim + d,
+              make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv));
 }
 
 template <typename Kern>
@@ -817,21 +819,24 @@ void launch_attention_prefill(const AttnArgs& a, hipStream_t s, const LaunchEven
   }
   if (a.pf_split > 1) {
     const long long items = (long long)a.R * a.n_heads * (a.head_dim / 4);
-    launch_kernel(k_prefill_merge, dim3((unsigned)((items + 255) / 256)), s, ev ? &e1 : nullptr, a);
+    launch_kernel(k_prefill_merge<T>, dim3((unsigned)((items + 255) / 256)), s, ev ? &e1 : nullptr, a);
   }
 }
 
 bool attention_needs_combine(const AttnArgs& a) { return a.n_groups_max > 1; }
 
+template <typename T>
 void launch_attn_combine(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev) {
   const int items = 32 * (a.head_dim / 4) * CMB_LANES;
   const dim3 grid((items + 255) / 256, a.n_kv * a.n_rb, a.B);
-  if (a.head_dim == 128) launch_kernel(k_attn_combine<128>, grid, s, ev, a);
-  else launch_kernel(k_attn_combine<64>, grid, s, ev, a);
+  if (a.head_dim == 128) launch_kernel(k_attn_combine<T, 128>, grid, s, ev, a);
+  else launch_kernel(k_attn_combine<T, 64>, grid, s, ev, a);
 }
 
 template void launch_attention<uint16_t>(const AttnArgs&, hipStream_t, const LaunchEvents*);
 template void launch_attention<float>(const AttnArgs&, hipStream_t, const LaunchEvents*);
+template void launch_attn_combine<uint16_t>(const AttnArgs&, hipStream_t, const LaunchEvents*);
+template void launch_attn_combine<float>(const AttnArgs&, hipStream_t, const LaunchEvents*);
 template void launch_attention_prefill<uint16_t>(const AttnArgs&, hipStream_t, const LaunchEvents*);
 template void launch_attention_prefill<float>(const AttnArgs&, hipStream_t, const LaunchEvents*);
 

@@ -4,7 +4,9 @@
 // residual stream, softmax and logits are fp32. MFMA consumes the stored operand (weights or
 // K/V) exactly and the fp32 activation as a bf16 hi/lo pair (x = hi + lo), which keeps products
 // within ~2^-16 of fp32 at the cost of a second MFMA (the path is HBM-bound, so MFMA time is
-// not on the critical path).
+// not on the critical path). The kernel that produces an activation splits it, once, and stores
+// the pair in the MFMA operand layout (packed activations, kernels.h): 32 bits per value, as the
+// fp32 value itself would take, and its consumers load operands with no conversion.
 //
 // Determinism: the reduction order of every output depends only on the weight shape (N, K) and
 // on absolute positions, never on how many rows share a pass. A row therefore gets bit-identical
@@ -63,6 +65,11 @@ struct ET<uint16_t> {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b.hi, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b.lo, acc, 0, 0, 0);
   }
+  // the products of one plane of the B operand
+  __device__ static void mma_plane(f32x4& acc, const A& a, const u32x4 b, int) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.v), __builtin_bit_cast(bf16x8, b), acc,
+                                                  0, 0, 0);
+  }
   __device__ static void to_f32(const A& a, float out[8]) {
     const uint32_t w[4] = {a.v.x, a.v.y, a.v.z, a.v.w};
 #pragma unroll
@@ -72,27 +79,40 @@ struct ET<uint16_t> {
     }
   }
   __device__ static uint16_t from_f32(float f) { return f2bf(f); }
-  // B operand kept in LDS as 32 bytes per lane slot: 8 bf16 hi, then 8 bf16 lo
-  __device__ static void to_lds(char* p, const float x[8]) {
-    const B b = split(x);
-    *reinterpret_cast<bf16x8*>(p) = b.hi;
-    *reinterpret_cast<bf16x8*>(p + 16) = b.lo;
+  // the B operand's two 16-byte halves: 8 bf16 hi, 8 bf16 lo
+  __device__ static B join(const uint4 p0, const uint4 p1) {
+    return B{__builtin_bit_cast(bf16x8, p0), __builtin_bit_cast(bf16x8, p1)};
   }
-  __device__ static B from_lds(const char* p) {
-    return B{*reinterpret_cast<const bf16x8*>(p), *reinterpret_cast<const bf16x8*>(p + 16)};
-  }
-  // half `hf` (values 4hf..4hf+3) of a slot: the same bytes to_lds writes for them
-  __device__ static void to_lds_half(char* p, int hf, const float4 x) {
+  // 4 consecutive values (k a multiple of 4) of a packed activation row
+  __device__ static void put4(char* row, int k, const float4 x) {
     const float v[4] = {x.x, x.y, x.z, x.w};
     bf16x4 h, l;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      __bf16 t = (__bf16)v[j];
+      const __bf16 t = (__bf16)v[j];
       h[j] = t;
       l[j] = (__bf16)(v[j] - (float)t);
     }
-    *reinterpret_cast<bf16x4*>(p + hf * 8) = h;
-    *reinterpret_cast<bf16x4*>(p + 16 + hf * 8) = l;
+    char* p = row + (k & 31) * 2;
+    *reinterpret_cast<bf16x4*>(p) = h;
+    *reinterpret_cast<bf16x4*>(p + ACT_PLANE) = l;
+  }
+  // one plane's share of put4
+  __device__ static void put4_plane(char* row, int k, const float4 x, int plane) {
+    const float v[4] = {x.x, x.y, x.z, x.w};
+    bf16x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const __bf16 t = (__bf16)v[j];
+      o[j] = plane ? (__bf16)(v[j] - (float)t) : t;
+    }
+    *reinterpret_cast<bf16x4*>(row + plane * ACT_PLANE + (k & 31) * 2) = o;
+  }
+  __device__ static void put1(char* row, int k, float x) {
+    const __bf16 h = (__bf16)x;
+    char* p = row + (k & 31) * 2;
+    *reinterpret_cast<__bf16*>(p) = h;
+    *reinterpret_cast<__bf16*>(p + ACT_PLANE) = (__bf16)(x - (float)h);
   }
 };
 
@@ -119,27 +139,63 @@ struct ET<float> {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], b.x[j], acc, 0, 0, 0);
   }
+  __device__ static void mma_plane(f32x4& acc, const A& a, const u32x4 b, int plane) {
+    const float4 av = plane ? a.b : a.a, bv = __builtin_bit_cast(float4, b);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, bv.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, bv.w, acc, 0, 0, 0);
+  }
   __device__ static void to_f32(const A& a, float out[8]) {
     out[0] = a.a.x; out[1] = a.a.y; out[2] = a.a.z; out[3] = a.a.w;
     out[4] = a.b.x; out[5] = a.b.y; out[6] = a.b.z; out[7] = a.b.w;
   }
   __device__ static float from_f32(float f) { return f; }
-  // B operand kept in LDS as 32 bytes per lane slot: 8 fp32
-  __device__ static void to_lds(char* p, const float x[8]) {
-    reinterpret_cast<float4*>(p)[0] = make_float4(x[0], x[1], x[2], x[3]);
-    reinterpret_cast<float4*>(p)[1] = make_float4(x[4], x[5], x[6], x[7]);
-  }
-  __device__ static B from_lds(const char* p) {
-    const float4 u = reinterpret_cast<const float4*>(p)[0], v = reinterpret_cast<const float4*>(p)[1];
+  // the B operand's two 16-byte halves: values 0..3 and 4..7
+  __device__ static B join(const uint4 p0, const uint4 p1) {
+    const float4 u = __builtin_bit_cast(float4, p0), v = __builtin_bit_cast(float4, p1);
     return B{{u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w}};
   }
-  __device__ static void to_lds_half(char* p, int hf, const float4 x) { reinterpret_cast<float4*>(p)[hf] = x; }
+  __device__ static void put4(char* row, int k, const float4 x) {
+    *reinterpret_cast<float4*>(row + ((k >> 2) & 1) * ACT_PLANE + ((k >> 3) & 3) * 16) = x;
+  }
+  __device__ static void put4_plane(char* row, int k, const float4 x, int plane) {
+    if (plane == ((k >> 2) & 1)) put4(row, k, x);
+  }
+  __device__ static void put1(char* row, int k, float x) {
+    *reinterpret_cast<float*>(row + ((k >> 2) & 1) * ACT_PLANE + ((k >> 3) & 3) * 16 + (k & 3) * 4) = x;
+  }
 };
+
+// Packed activations (layout in kernels.h): the line holding x[row][k] of a matrix of KT k-tiles.
+__device__ __forceinline__ char* act_row(void* base, int KT, int row, int k) {
+  return reinterpret_cast<char*>(base) + ((size_t)(row >> 4) * KT + (k >> 5)) * ACT_TILE + (row & 15) * ACT_ROW;
+}
+template <typename T>
+__device__ __forceinline__ void act_put4(void* base, int KT, int row, int k, const float4 x) {
+  ET<T>::put4(act_row(base, KT, row, k), k, x);
+}
+template <typename T>
+__device__ __forceinline__ void act_put1(void* base, int KT, int row, int k, float x) {
+  ET<T>::put1(act_row(base, KT, row, k), k, x);
+}
 
 __device__ __forceinline__ void load8(const float* p, float x[8]) {
   const float4 a = reinterpret_cast<const float4*>(p)[0];
   const float4 b = reinterpret_cast<const float4*>(p)[1];
   x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+}
+
+// QKV section of n-tile nt: 0 = q, 1 = k, 2 = v; (head, j) = tile j of that head (dims 8j..8j+7
+// and head_dim/2+8j..+7, so rotary partners share the tile).
+__device__ __forceinline__ void qkv_tile(const LinArgs& a, int nt, int& sec, int& head, int& j) {
+  const int tpd = a.head_dim >> 4, q_tiles = a.n_heads * tpd, k_tiles = a.n_kv * tpd;
+  int lt;
+  if (nt < q_tiles) { sec = 0; lt = nt; }
+  else if (nt < q_tiles + k_tiles) { sec = 1; lt = nt - q_tiles; }
+  else { sec = 2; lt = nt - q_tiles - k_tiles; }
+  head = lt / tpd;
+  j = lt - head * tpd;
 }
 
 // Online-softmax merge (base 2) of a partial (m_c, l_c, o_c) into a running (m_r, l_r, o_r).
@@ -152,6 +208,13 @@ __device__ __forceinline__ void softmax_merge(float& m_r, float& l_r, float* o_r
   l_r = l_r * ar + l_c * ac;
   for (int i = 0; i < n; ++i) o_r[i] = o_r[i] * ar + o_c[i] * ac;
   m_r = m_n;
+}
+
+// a launch, optionally stamping timing events at the kernel's start and end
+template <typename K, typename... Args>
+static void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, const LaunchEvents* ev, Args... args) {
+  if (ev) hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, s, ev->start, ev->stop, 0, args...);
+  else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
 }
 
 }  // namespace seedk

@@ -21,6 +21,15 @@ namespace seedk {
 //  * gate/up: tile t holds gate rows 8t..8t+7 followed by up rows 8t..8t+7.
 // ---------------------------------------------------------------------------------------------
 
+// Packed activations. The inputs of the linear kernels (x * gain, attention output, SwiGLU output;
+// M rows x K features) are stored by their producers as MFMA B operands: tiles of 16 rows x 32
+// features, tile (mt, kt) at byte offset (mt * (K/32) + kt) * ACT_TILE. A row of a tile is one 128-byte
+// line: two planes of four 16-byte slots, slot kg of plane p for features 8kg .. 8kg+7: bf16 models
+// keep the 8 values' bf16 hi halves in plane 0 and their lo halves in plane 1, fp32 models values
+// 0..3 and 4..7. Either way the slot pair (row, kg) is one lane's operand of a 16x16x32 contraction; a
+// pass of one row reads whole lines, and a full tile is 2 KB without gaps.
+constexpr int ACT_TILE = 2048, ACT_ROW = 128, ACT_PLANE = 64;
+
 enum Prologue { PRO_NORM = 0, PRO_PLAIN = 1 };
 enum Epilogue { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
 
@@ -34,19 +43,20 @@ struct LinArgs {
                           // by group in order (k_linear_lds: S == 1)
   int NJ;                 // LDS kernel: passes per workgroup (n-group blockIdx.x + j*gridDim.x)
   // input
-  const float* X;         // [M][ldx] fp32 activations; PRO_NORM: x*g formed by the producer
-  int ldx;
+  const void* X;          // packed activations [M][K]; PRO_NORM: x*g formed by the producer
+  const float* rs;        // LIN_WIDE with PRO_NORM: RMSNorm row scales [M]
   const float* ssq;       // PRO_NORM: [M][nssq] partial sums of squares of x (per 16 features)
   int nssq;
   float eps;
   // EPI_RESID: h[m][n] += y, xg[m][n] = h[m][n] * gain_next[n] (input of the next RMSNorm
   // consumer), ssq_out[m][n/16] = sum of squares of the 16 updated values
   float* h;
-  float* xg;
+  void* xg;               // packed
   const float* gain_next;
   float* ssq_out;
+  float* rs_out;          // LIN_WIDE: the updated rows' RMSNorm scales [M] (in place of ssq_out)
   // EPI_SWIGLU: act[m][f] = silu(gate) * up, f = nt*8 + c
-  float* act;
+  void* act;              // packed
   // EPI_QKV
   float* q;               // [M][n_heads*head_dim] rotated queries (fp32)
   void* kv;               // KV pool
@@ -95,7 +105,7 @@ struct AttnArgs {
   int n_groups_max;       // grid extent over groups; n_groups_max * span == bt_stride * 16
   float scale_log2;       // log2(e) / sqrt(head_dim)
   float* part;            // group partials [B][n_kv][n_rb][n_groups_max][32][head_dim + 4]
-  float* out;             // [M][n_heads*head_dim]
+  void* out;              // packed activations [M][n_heads*head_dim]
 };
 
 // bytes of a prefill attention workgroup's staged block table (16-byte aligned)
@@ -133,9 +143,11 @@ struct SetupArgs {
   int* row_blk;           // [M]
   float* row_rope;        // [M][head_dim]
   float* h;               // [M][H]
-  float* xg;              // [M][H] h * gain (input of the pass's first RMSNorm consumer)
+  void* xg;               // packed [M][H]: h * gain (input of the pass's first RMSNorm consumer)
   const float* gain;      // [H]
   float* ssq;             // [M][H/16]
+  float* rs;              // nullable [M]: RMSNorm row scales (passes of more than 64 rows)
+  float eps;
   // phase clock (nullable): block 0 writes the constant-rate clock to stamp[round * 3 + stamp_col]
   // when the kernel starts (round = *rounds, only while round < stamp_cap)
   long long* stamp;
@@ -183,6 +195,9 @@ struct LaunchEvents {
 template <typename T>
 void launch_linear(const LinArgs& a, int prologue, int epilogue, int kind, hipStream_t s,
                    const LaunchEvents* ev = nullptr);
+// LIN_WIDE: passes of more than 64 rows (wide.hip).
+template <typename T>
+void launch_linear_wide(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev);
 // Attention partials per group of span positions (the final output when the rows see one group).
 template <typename T>
 void launch_attention(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
@@ -196,6 +211,7 @@ bool attention_needs_combine(const AttnArgs& a);
 // Positions per attention group for a context capacity and batch capacity (fixed per decoder, so
 // that a query's merge tree depends only on absolute positions).
 int attention_span(int max_ctx, int max_batch);
+template <typename T>
 void launch_attn_combine(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
 template <typename T>
 void launch_setup(const SetupArgs& a, hipStream_t s);

@@ -45,18 +45,6 @@ __device__ __forceinline__ void epi_coords(const LinArgs& a, Grp gr, int e, int&
   nt = (gr.g0 + j * gr.gs) * a.NT + nl;
 }
 
-// QKV section of n-tile nt: 0 = q, 1 = k, 2 = v; (head, j) = tile j of that head (dims 8j..8j+7
-// and head_dim/2+8j..+7, so rotary partners share the tile).
-__device__ __forceinline__ void qkv_tile(const LinArgs& a, int nt, int& sec, int& head, int& j) {
-  const int tpd = a.head_dim >> 4, q_tiles = a.n_heads * tpd, k_tiles = a.n_kv * tpd;
-  int lt;
-  if (nt < q_tiles) { sec = 0; lt = nt; }
-  else if (nt < q_tiles + k_tiles) { sec = 1; lt = nt - q_tiles; }
-  else { sec = 2; lt = nt - q_tiles - k_tiles; }
-  head = lt / tpd;
-  j = lt - head * tpd;
-}
-
 template <int EPI>
 __device__ __forceinline__ void epi_load(const LinArgs& a, Grp gr, int e, EpiPre& p) {
   int lt, m, c, nt;
@@ -96,7 +84,7 @@ __device__ void linear_epilogue(const LinArgs& a, Grp gr, const float* Y, int y_
         const float v = p.h + YV(lt, m, c);
         const size_t off = (size_t)m * a.N + nt * 16 + c;
         a.h[off] = v;
-        a.xg[off] = v * p.g;
+        act_put1<T>(a.xg, a.N >> 5, m, nt * 16 + c, v * p.g);
         float s = v * v;
         s += __shfl_xor(s, 8);
         s += __shfl_xor(s, 4);
@@ -130,7 +118,7 @@ __device__ void linear_epilogue(const LinArgs& a, Grp gr, const float* Y, int y_
       const int j = lt / a.NT, nt = (gr.g0 + j * gr.gs) * a.NT + (lt - j * a.NT);
       if (nt >= n_tiles) continue;
       const float g = YV(lt, m, c), u = YV(lt, m, c + 8);
-      a.act[(size_t)m * F + nt * 8 + c] = g / (1.f + __expf(-g)) * u;
+      act_put1<T>(a.act, F >> 5, m, nt * 8 + c, g / (1.f + __expf(-g)) * u);
     }
   } else {  // EPI_HEAD
     if (a.logits) {
@@ -207,6 +195,25 @@ __device__ __forceinline__ float sum_partials(const float* p, int n, int per) {
   return t;
 }
 
+// A staged B-operand slot: 32 bytes of LDS holding one row's 8 values of k-group kg of k-tile kt
+// (rest = kt * 4 + kg), the two 16-byte halves of the packed activation slot side by side.
+struct Slot {
+  uint4 p0, p1;
+};
+__device__ __forceinline__ Slot load_slot(const void* X, int KT, int row, int rest) {
+  const char* p = reinterpret_cast<const char*>(X) + ((size_t)(row >> 4) * KT + (rest >> 2)) * ACT_TILE +
+                  (row & 15) * ACT_ROW + (rest & 3) * 16;
+  return Slot{*reinterpret_cast<const uint4*>(p), *reinterpret_cast<const uint4*>(p + ACT_PLANE)};
+}
+__device__ __forceinline__ void store_slot(char* p, const Slot& v) {
+  reinterpret_cast<uint4*>(p)[0] = v.p0;
+  reinterpret_cast<uint4*>(p)[1] = v.p1;
+}
+template <typename T>
+__device__ __forceinline__ typename ET<T>::B lds_slot(const char* p) {
+  return ET<T>::join(reinterpret_cast<const uint4*>(p)[0], reinterpret_cast<const uint4*>(p)[1]);
+}
+
 __host__ __device__ inline size_t lds_x_bytes(int M, int nkt) { return (size_t)nkt * 4 * M * 32 + 32; }
 
 // ---------------------------------------------------------------------------------------------
@@ -264,30 +271,26 @@ __global__ void __launch_bounds__(1024) k_linear_lds(LinArgs a) {
   float* part = reinterpret_cast<float*>(alias ? lds : lds + lds_x_bytes(M, KT));
   float* s_rs = part + (size_t)a.NJ * NW * M * 16;
   {
-    // two batches of 2 items per thread per round trip: both batches' loads are issued before
+    // two batches of 2 slots per thread per round trip: both batches' loads are issued before
     // either is written, so a workgroup whose rows take several batches (O at 5 rows, the LM head
-    // at more than 3) pays half the round trips. Loads are branch-free (items past the end reload
+    // at more than 3) pays half the round trips. Loads are branch-free (slots past the end reload
     // the last one and are not written) and none is issued after a wait: a load under a branch
     // makes the compiler wait for every load in flight before each write, and a surplus load
     // issued after the first wait would add a round trip to the one-batch case.
-    const int row_items = KT * 4, items = M * row_items, bs = 2 * (int)blockDim.x;
-    float xa[2][8], xb[2][8];
-    auto ld = [&](float (&xv)[2][8], int q0) {
+    const int items = KT * 4 * M, bs = 2 * (int)blockDim.x;
+    Slot xa[2], xb[2];
+    auto ld = [&](Slot (&xv)[2], int q0) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int q = min(q0 + u * (int)blockDim.x + tid, items - 1);
-        const int r = q / row_items, rem = q - r * row_items;
-        load8(a.X + (size_t)r * a.ldx + (size_t)rem * 8, xv[u]);
+        xv[u] = load_slot(a.X, KT, q % M, q / M);
       }
     };
-    auto st = [&](const float (&xv)[2][8], int q0) {
+    auto st = [&](const Slot (&xv)[2], int q0) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int q = q0 + u * (int)blockDim.x + tid;
-        if (q < items) {
-          const int r = q / row_items, rem = q - r * row_items;
-          ET<T>::to_lds(lds + ((size_t)rem * M + r) * 32, xv[u]);
-        }
+        if (q < items) store_slot(lds + (size_t)q * 32, xv[u]);
       }
     };
     if constexpr (!ALIAS) {
@@ -309,10 +312,7 @@ __global__ void __launch_bounds__(1024) k_linear_lds(LinArgs a) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int q = q0 + u * (int)blockDim.x + tid;
-          if (q < items) {
-            const int r = q / row_items, rem = q - r * row_items;
-            load8(a.X + (size_t)r * a.ldx + (size_t)rem * 8, xa[u]);
-          }
+          if (q < items) xa[u] = load_slot(a.X, KT, q % M, q / M);
         }
         st(xa, q0);
       }
@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(1024) k_linear_lds(LinArgs a) {
   f32x4 done[ALIAS ? LDS_MAX_PASSES : 1];   // finished passes, kept until the staged rows are no longer read
   int jC = 0, iC = 0;  // pass / k-tile of the next tile to consume
   auto consume = [&](int slot) {
-    ET<T>::mma(acc, wb[slot], ET<T>::from_lds(xa + iC * xs));
+    ET<T>::mma(acc, wb[slot], lds_slot<T>(xa + iC * xs));
     if (++iC == nk) {
       if constexpr (!ALIAS) {
         if (live_col) {
@@ -435,29 +435,31 @@ __global__ void __launch_bounds__(1024) k_linear_mfma(LinArgs a) {
     const int kt0 = (ks * KT) / a.KS, kt1 = ((ks + 1) * KT) / a.KS;
     const int nk = kt1 - kt0;
     const T* wp = reinterpret_cast<const T*>(a.W) + ((size_t)nt * KT + kt0) * 512 + lane * 8;
-    const float* xp[TT];
+    const char* xp[TT];
     bool ok[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       const int tok = tt * 16 + tl;
       ok[tt] = tok < M;
-      xp[tt] = a.X + (size_t)(ok[tt] ? tok : 0) * a.ldx + kg * 8 + kt0 * 32;
+      xp[tt] = reinterpret_cast<const char*>(a.X) + ((size_t)(ok[tt] ? tt : 0) * KT + kt0) * ACT_TILE +
+               (ok[tt] ? tl : 0) * ACT_ROW + kg * 16;
     }
     constexpr int P = (TT <= 1) ? 4 : (TT == 2 ? 3 : 2);
     typename ET<T>::A wb[P];
-    float xb[P][TT][8];
+    Slot xb[P][TT];
     auto issue = [&](int slot, int j) {
       wb[slot] = ET<T>::load_nt(wp + (size_t)j * 512);
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) load8(xp[tt] + j * 32, xb[slot][tt]);
+      for (int tt = 0; tt < TT; ++tt) {
+        const char* p = xp[tt] + (size_t)j * ACT_TILE;
+        xb[slot][tt] = Slot{*reinterpret_cast<const uint4*>(p), *reinterpret_cast<const uint4*>(p + ACT_PLANE)};
+      }
     };
     auto consume = [&](int slot) {
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt) {
-        float x[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = ok[tt] ? xb[slot][tt][q] : 0.f;
-        ET<T>::mma(acc[tt], wb[slot], ET<T>::split(x));
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        ET<T>::mma(acc[tt], wb[slot], ET<T>::join(ok[tt] ? xb[slot][tt].p0 : z, ok[tt] ? xb[slot][tt].p1 : z));
       }
     };
 #pragma unroll
@@ -538,12 +540,11 @@ __global__ void __launch_bounds__(512) k_linear_splitk(LinArgs a, float* part) {
   // q = (i*4 + kg)*M + r is slot q = x[r][32(kt0+i) + 8kg .. +7]; items past the end load item 0
   // and go to a dummy slot ----
   const int items = nk * 4 * M;
-  float xv[XI][8];
+  Slot xv[XI];
 #pragma unroll
   for (int u = 0; u < XI; ++u) {
     const int q = u * (int)blockDim.x + tid, qc = q < items ? q : 0;
-    const int r = qc % M, rest = qc / M;
-    load8(a.X + (size_t)r * a.ldx + (size_t)kt0 * 32 + rest * 8, xv[u]);
+    xv[u] = load_slot(a.X, KT, qc % M, kt0 * 4 + qc / M);
   }
 
   // ---- weight prefetch (slots past the range re-read its last tile, never consumed) ----
@@ -555,14 +556,11 @@ __global__ void __launch_bounds__(512) k_linear_splitk(LinArgs a, float* part) {
 #pragma unroll
   for (int u = 0; u < XI; ++u) {
     const int q = u * (int)blockDim.x + tid;
-    ET<T>::to_lds(lds + (q < items ? (size_t)q * 32 : zero_off + 32), xv[u]);
+    store_slot(lds + (q < items ? (size_t)q * 32 : zero_off + 32), xv[u]);
   }
   // items beyond XI per thread (shapes the launcher could not cover up front)
   for (int q = XI * (int)blockDim.x + tid; q < items; q += blockDim.x) {
-    const int r = q % M, rest = q / M;
-    float x[8];
-    load8(a.X + (size_t)r * a.ldx + (size_t)kt0 * 32 + rest * 8, x);
-    ET<T>::to_lds(lds + (size_t)q * 32, x);
+    store_slot(lds + (size_t)q * 32, load_slot(a.X, KT, q % M, kt0 * 4 + q / M));
   }
   if (tid < 2) *reinterpret_cast<float4*>(lds + zero_off + tid * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
@@ -582,7 +580,7 @@ __global__ void __launch_bounds__(512) k_linear_splitk(LinArgs a, float* part) {
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       const int m = tt * 16 + tl;
-      ET<T>::mma(acc[tt], wb[slot], ET<T>::from_lds(xa[tt] + (m < M ? i * xs : 0)));
+      ET<T>::mma(acc[tt], wb[slot], lds_slot<T>(xa[tt] + (m < M ? i * xs : 0)));
     }
   };
   int s0 = 0;
@@ -661,312 +659,6 @@ __global__ void __launch_bounds__(1024) k_splitk_reduce(LinArgs a, const float* 
   linear_epilogue<T, EPI>(a, gr, Y, per, epre);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Wide passes (more than 64 rows: the prompt's prefill and the drafting objective's decoder
-// pass): a compute-bound MFMA GEMM, Y[M, N] = X[M, K] W^T. A workgroup owns WIDE_WN n-tiles
-// (16 output features each) x WIDE_WM token tiles (16 rows each); its 8 waves form a 4 x 2 grid,
-// wave (wn, wm) accumulating WN/4 n-tiles for token tiles 4wm..4wm+3, so each weight fragment
-// feeds 4 token tiles and each activation fragment WN/4 n-tiles. WN (8, 12, 16 or 20) is chosen
-// per projection so that the grid fills whole rounds of one workgroup per CU: the cost is rounds x
-// WN (gate/up's 1216 n-tiles: 20 gives 2 rounds of 488 workgroups where 16 gives 3 of 608; QKV's
-// 384: 12 gives one round of 256; the 2560-wide O and down stay at 8, 160 workgroups). K runs in
-// chunks of WIDE_CK k-tiles: a chunk's activation rows are staged in LDS as bf16 hi/lo B-operand
-// slots, double-buffered (chunk c+1's global loads are issued before chunk c is consumed and
-// written to the other buffer after it), and the weight fragments of chunk c+1 are loaded into
-// registers while chunk c is consumed. Every output is one MFMA chain over all of K in k order
-// (these passes write the prompt's cache and the drafting objective's logits, which no decode
-// pass has to reproduce bit for bit).
-// Workgroup order: the token tiles of one n-group are consecutive workgroups of one XCD (workgroup
-// w runs on XCD w mod 8), so that n-group's weights come from HBM once and from that XCD's L2 for
-// its other token tiles. The finished tile goes through the same epilogues as the narrow kernels,
-// 8 (or 4) n-tiles at a time.
-// ---------------------------------------------------------------------------------------------
-constexpr int WIDE_WM = 8;    // token tiles per workgroup (128 rows)
-constexpr int WIDE_CK = 2;    // k-tiles per staged chunk
-// n-tiles per epilogue group: 8 (the head's argmax partials are per 8 n-tiles), or 4 for workgroup
-// widths that are not a multiple of 8 (their epilogues are all tile-local)
-constexpr int wide_epi_nt(int wn) { return wn % 8 == 0 ? 8 : 4; }
-constexpr int WIDE_ROWS_TILE = WIDE_WM * 16;
-constexpr size_t WIDE_CHUNK_BYTES = (size_t)WIDE_CK * 4 * WIDE_ROWS_TILE * 32;   // one staging buffer
-constexpr size_t WIDE_LDS = 2 * WIDE_CHUNK_BYTES;   // = 8 n-tiles x 128 rows x 16 fp32 outputs (the epilogue)
-
-// A staging buffer's B-operand slots. bf16: two planes, the 16-byte hi halves of all slots, then
-// the lo halves, so that the 16 lanes of a fragment read (consecutive slots) cover 256 contiguous
-// bytes (interleaved 32-byte slots would put lanes tl and tl + 8 on the same banks); fp32: 32-byte
-// slots of 8 values.
-template <typename T>
-__device__ __forceinline__ void wide_store_half(char* buf, int q, int hf, const float4 x) {
-  if constexpr (sizeof(T) == 2) {
-    const float v[4] = {x.x, x.y, x.z, x.w};
-    bf16x4 h, l;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      __bf16 t = (__bf16)v[j];
-      h[j] = t;
-      l[j] = (__bf16)(v[j] - (float)t);
-    }
-    *reinterpret_cast<bf16x4*>(buf + (size_t)q * 16 + hf * 8) = h;
-    *reinterpret_cast<bf16x4*>(buf + WIDE_CHUNK_BYTES / 2 + (size_t)q * 16 + hf * 8) = l;
-  } else {
-    ET<T>::to_lds_half(buf + (size_t)q * 32, hf, x);
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ typename ET<T>::B wide_load_slot(const char* buf, int q) {
-  if constexpr (sizeof(T) == 2) {
-    return typename ET<T>::B{*reinterpret_cast<const bf16x8*>(buf + (size_t)q * 16),
-                             *reinterpret_cast<const bf16x8*>(buf + WIDE_CHUNK_BYTES / 2 + (size_t)q * 16)};
-  } else {
-    return ET<T>::from_lds(buf + (size_t)q * 32);
-  }
-}
-
-// row-indexed arguments of rows m0.. of a pass
-__device__ __forceinline__ LinArgs wide_rows(const LinArgs& a0, int m0, int Mt, int epi_nt) {
-  LinArgs a = a0;
-  const int n_tiles = a0.N >> 4;
-  a.M = Mt;
-  a.X = a0.X + (size_t)m0 * a0.ldx;
-  if (a0.ssq) a.ssq = a0.ssq + (size_t)m0 * a0.nssq;
-  if (a0.h) a.h = a0.h + (size_t)m0 * a0.N;
-  if (a0.xg) a.xg = a0.xg + (size_t)m0 * a0.N;
-  if (a0.ssq_out) a.ssq_out = a0.ssq_out + (size_t)m0 * n_tiles;
-  if (a0.act) a.act = a0.act + (size_t)m0 * (a0.N >> 1);
-  if (a0.q) a.q = a0.q + (size_t)m0 * a0.n_heads * a0.head_dim;
-  if (a0.row_pos) a.row_pos = a0.row_pos + m0;
-  if (a0.row_slot) a.row_slot = a0.row_slot + m0;
-  if (a0.row_blk) a.row_blk = a0.row_blk + m0;
-  if (a0.row_rope) a.row_rope = a0.row_rope + (size_t)m0 * a0.head_dim;
-  if (a0.logits) a.logits = a0.logits + (long long)m0 * a0.ld_logits;
-  if (a0.amax_val) a.amax_val = a0.amax_val + (size_t)m0 * a0.amax_stride;
-  if (a0.amax_idx) a.amax_idx = a0.amax_idx + (size_t)m0 * a0.amax_stride;
-  a.NT = epi_nt;
-  a.KS = 1;
-  a.S = 1;
-  a.NJ = 1;
-  return a;
-}
-
-template <typename T, int PRO, int EPI, int WIDE_WN, bool SPLIT>
-__global__ void __launch_bounds__(512) k_linear_wide(LinArgs a0) {
-  constexpr int NI = WIDE_WN / 4;   // n-tiles per wave
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  __shared__ float s_rs[WIDE_ROWS_TILE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int tl = lane & 15, kg = lane >> 4;
-  const int KTF = a0.K >> 5, n_tiles = a0.N >> 4;
-  const int NG = (n_tiles + WIDE_WN - 1) / WIDE_WN;
-  const int MT = (a0.M + WIDE_ROWS_TILE - 1) / WIDE_ROWS_TILE;
-  // SPLIT: K in a0.KS k-ranges, each (n-group, k-range) pair a virtual n-group of its own
-  const int S = SPLIT ? a0.KS : 1;
-  // workgroup -> (virtual n-group, token tile): the MT token tiles of virtual n-group gv share the
-  // XCD gv mod 8
-  const int b = blockIdx.x, xcd = b & 7, r = b >> 3;
-  const int mt = r % MT, gv = (r / MT) * 8 + xcd;
-  if (gv >= NG * S) return;   // padding of the grid to whole XCD rounds; the workgroup leaves together
-  const int g = gv / S, ks = gv - g * S;
-  const int kt0 = (ks * KTF) / S, KT = ((ks + 1) * KTF) / S - kt0;   // this workgroup's k-tiles
-  const int m0 = mt * WIDE_ROWS_TILE;
-  const int Mt = min(WIDE_ROWS_TILE, a0.M - m0);
-  constexpr int EPI_NT = wide_epi_nt(WIDE_WN);
-  const LinArgs a = wide_rows(a0, m0, Mt, EPI_NT);
-  const int wn = wave & 3, wm = wave >> 2;
-
-  // weight fragments of n-tiles g*WN + NI*wn + i (past the last n-tile: the last one, never stored)
-  const T* wp[NI];
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int nt = min(g * WIDE_WN + NI * wn + i, n_tiles - 1);
-    wp[i] = reinterpret_cast<const T*>(a.W) + ((size_t)nt * KTF + kt0) * 512 + lane * 8;
-  }
-  const float* X = a.X + (size_t)kt0 * 32;
-  // staged slot q = (ktl*4 + kg') * 128 + row holds x[row][32 (c*CK + ktl) + 8 kg' .. +7]; rows past
-  // the tile's last row read its last row (their outputs are never stored). A chunk is read as
-  // (8 rows x one k-tile) blocks, one per wave and load: lane (r, e) takes floats 4e..4e+3 of the
-  // k-tile in row r, so a load touches 8 cache lines (not 64 rows' pieces), and its LDS stores
-  // (half e&1 of slot kg' = e/2) fall on 16 distinct 8-byte bank positions.
-  const int NC = (KT + WIDE_CK - 1) / WIDE_CK;
-  constexpr int XP = 2 * WIDE_CK;   // 16-byte pieces per thread and chunk (16 x CK blocks / 8 waves)
-  static_assert(XP * 512 * 16 == WIDE_ROWS_TILE * WIDE_CK * 32 * 4, "chunk pieces");
-  float4 xv[XP];
-  auto stage_load = [&](int c) {
-#pragma unroll
-    for (int u = 0; u < XP; ++u) {
-      const int blk = u * 8 + wave, ktl = blk % WIDE_CK;
-      const int rr = min((blk / WIDE_CK) * 8 + (lane >> 3), Mt - 1);
-      const int kt = min(c * WIDE_CK + ktl, KT - 1);
-      xv[u] = *reinterpret_cast<const float4*>(X + (size_t)rr * a.ldx + kt * 32 + (lane & 7) * 4);
-    }
-  };
-  auto stage_store = [&](int c) {
-    char* buf = lds + (size_t)(c & 1) * WIDE_CHUNK_BYTES;
-#pragma unroll
-    for (int u = 0; u < XP; ++u) {
-      const int blk = u * 8 + wave, ktl = blk % WIDE_CK, row = (blk / WIDE_CK) * 8 + (lane >> 3);
-      const int q = (ktl * 4 + ((lane & 7) >> 1)) * WIDE_ROWS_TILE + row;
-      wide_store_half<T>(buf, q, lane & 1, xv[u]);
-    }
-  };
-  typename ET<T>::A wa[NI][WIDE_CK], wb[NI][WIDE_CK];
-  auto wload = [&](typename ET<T>::A (&w)[NI][WIDE_CK], int c) {
-#pragma unroll
-    for (int kk = 0; kk < WIDE_CK; ++kk) {
-      const int kt = min(c * WIDE_CK + kk, KT - 1);
-#pragma unroll
-      for (int i = 0; i < NI; ++i) w[i][kk] = ET<T>::load(wp[i] + (size_t)kt * 512);
-    }
-  };
-  f32x4 acc[NI][4];
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto consume = [&](const typename ET<T>::A (&w)[NI][WIDE_CK], int c) {
-    const char* buf = lds + (size_t)(c & 1) * WIDE_CHUNK_BYTES;
-    const int nk = min(WIDE_CK, KT - c * WIDE_CK);
-#pragma unroll
-    for (int kk = 0; kk < WIDE_CK; ++kk) {
-      if (kk < nk) {
-        typename ET<T>::B xb[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          xb[j] = wide_load_slot<T>(buf, (kk * 4 + kg) * WIDE_ROWS_TILE + (wm * 4 + j) * 16 + tl);
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) ET<T>::mma(acc[i][j], w[i][kk], xb[j]);
-      }
-    }
-  };
-
-  stage_load(0);
-  wload(wa, 0);
-  stage_store(0);
-  __syncthreads();
-  // chunk c (weights in wa, activations in buffer 0), then chunk c+1 (wb, buffer 1). The next
-  // chunk's loads are issued unconditionally (indices clamped to the last k-tile; a chunk past the
-  // end is staged but never consumed): under a data-dependent branch the compiler's wait counts
-  // merge the path without the loads, and every chunk then waits for all loads in flight,
-  // including the prefetch just issued.
-  for (int c = 0; c < NC; c += 2) {
-    stage_load(c + 1);
-    wload(wb, c + 1);
-    consume(wa, c);
-    stage_store(c + 1);
-    __syncthreads();
-    stage_load(c + 2);
-    wload(wa, c + 2);
-    consume(wb, c + 1);
-    stage_store(c + 2);
-    __syncthreads();
-  }
-
-  if constexpr (SPLIT) {
-    // the k-range's partial tile: part[ks][row][feature] over the pass's rows, added in k-range
-    // order by k_wide_splitk_reduce, which runs the epilogue
-    float* pp = a0.part + ((size_t)ks * a0.M + m0) * a0.N;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int nt = g * WIDE_WN + NI * wn + i;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = (wm * 4 + j) * 16 + tl;
-        if (nt < n_tiles && row < Mt)
-          *reinterpret_cast<float4*>(pp + (size_t)row * a0.N + nt * 16 + 4 * kg) =
-              make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      }
-    }
-    return;
-  }
-
-  // RMSNorm row scales, then the tile in groups of EPI_NT n-tiles through the staging buffers:
-  // Y[lt][row][16], lane (tl, kg) holding features 4kg..4kg+3 of its n-tile for row (4wm+j)*16 + tl
-  if constexpr (PRO == PRO_NORM) {
-    const float ssv[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int m = wave; m < Mt; m += 8) {
-      const float rs = wave_row_scale(a, m, ssv, false);
-      if (lane == 0) s_rs[m] = rs;
-    }
-  }
-  float* Y = reinterpret_cast<float*>(lds);
-  constexpr int YS = WIDE_ROWS_TILE * 16;   // floats per local n-tile
-  constexpr int HALVES = WIDE_WN / EPI_NT;
-#pragma unroll
-  for (int half = 0; half < HALVES; ++half) {
-    const Grp gr{HALVES * g + half, HALVES * NG};   // n-tiles (HALVES g + half) * EPI_NT + local tile
-    EpiPre epre{};
-    epi_load<EPI>(a, gr, tid, epre);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int lt = NI * wn + i;   // a wave's n-tiles may straddle two groups
-      if (lt / EPI_NT == half) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *reinterpret_cast<float4*>(Y + (size_t)(lt % EPI_NT) * YS + ((wm * 4 + j) * 16 + tl) * 16 + 4 * kg) =
-              make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      }
-    }
-    __syncthreads();
-    if constexpr (PRO == PRO_NORM) {
-      for (int e = tid; e < EPI_NT * Mt * 16; e += 512) {
-        const int lt = e / (Mt * 16), rem = e - lt * Mt * 16;
-        Y[(size_t)lt * YS + rem] *= s_rs[rem >> 4];
-      }
-      __syncthreads();
-    }
-    linear_epilogue<T, EPI>(a, gr, Y, YS, epre);
-    __syncthreads();   // the epilogue is done with Y before the next group overwrites it
-  }
-}
-
-// k-range partials of a split wide pass (the residual projections) added in k-range order from 0,
-// then the residual epilogue of linear_epilogue (h += y, xg = h * gain of the next norm, and the
-// per-16-feature sums of squares in the same xor order): a workgroup per 128 features x
-// WIDE_RED_ROWS rows, 4 rows per thread with all their loads issued before the first store, each
-// row's 128 features read and written as one contiguous 512-byte run.
-constexpr int WIDE_RED_ROWS = 16;
-__global__ void __launch_bounds__(512) k_wide_splitk_resid(LinArgs a, const float* part) {
-  constexpr int RPT = WIDE_RED_ROWS / 4;   // rows per thread
-  const int tid = threadIdx.x, f = tid & 127, rsub = tid >> 7;
-  const int n_tiles = a.N >> 4, nt = blockIdx.x * 8 + (f >> 4);
-  const int m0 = blockIdx.y * WIDE_RED_ROWS;
-  const size_t stride = (size_t)a.M * a.N;
-  const int S = a.KS;
-  if (nt >= n_tiles) return;   // whole 16-lane groups leave together
-  const int col = nt * 16 + (f & 15);
-  const float g = a.gain_next[col];
-  float v[RPT][WIDE_SPLIT_MAX], h[RPT];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int m = min(m0 + rsub + 4 * i, a.M - 1);   // rows past the pass re-read its last row, never stored
-    const size_t off = (size_t)m * a.N + col;
-#pragma unroll
-    for (int k = 0; k < WIDE_SPLIT_MAX; ++k) v[i][k] = k < S ? part[k * stride + off] : 0.f;
-    h[i] = a.h[off];
-  }
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int m = m0 + rsub + 4 * i;   // uniform across the wave (a wave is 64 features of one row)
-    float y = 0.f;
-#pragma unroll
-    for (int k = 0; k < WIDE_SPLIT_MAX; ++k)
-      if (k < S) y += v[i][k];
-    const float hv = h[i] + y;
-    float s = hv * hv;
-    s += __shfl_xor(s, 8);
-    s += __shfl_xor(s, 4);
-    s += __shfl_xor(s, 2);
-    s += __shfl_xor(s, 1);
-    if (m < a.M) {
-      const size_t off = (size_t)m * a.N + col;
-      a.h[off] = hv;
-      a.xg[off] = hv * g;
-      if ((f & 15) == 0) a.ssq_out[(size_t)m * n_tiles + nt] = s;
-    }
-  }
-}
-
 // Reduce per-n-group argmax partials of one row; lowest token id wins among equal maxima.
 __global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const int* idx, int stride, int n_parts,
                                                          int* tok_out, int tok_stride) {
@@ -1026,7 +718,6 @@ size_t linear_lds_bytes(int M, int K, int NT, int KS, int S, int NJ, int kind) {
     const int nk_max = ((K >> 5) + KS - 1) / KS;
     return (size_t)nk_max * 4 * M * 32 + 64;
   }
-  if (kind == LIN_WIDE) return WIDE_LDS;
   return (size_t)(NT * KS * M * 16) * sizeof(float);
 }
 
@@ -1068,14 +759,13 @@ __global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
 
   // chunk c's items q = (ktl*4 + kg)*M + r hold x[r][32(c*CK + ktl) + 8kg .. +7]; loaded branch-free
   // (items past the chunk reload item 0 and are not written)
-  float xv[XI][8];
+  Slot xv[XI];
   auto stage_load = [&](int c) {
     const int nkc = min(HEAD_CK, KT - c * HEAD_CK), items = nkc * 4 * M;
 #pragma unroll
     for (int u = 0; u < XI; ++u) {
       const int q = u * NTH + tid, qc = q < items ? q : 0;
-      const int r = qc % M, rest = qc / M;
-      load8(a.X + (size_t)r * a.ldx + (size_t)c * HEAD_CK * 32 + rest * 8, xv[u]);
+      xv[u] = load_slot(a.X, KT, qc % M, c * HEAD_CK * 4 + qc / M);
     }
   };
   auto stage_store = [&](int c) {
@@ -1084,7 +774,7 @@ __global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
 #pragma unroll
     for (int u = 0; u < XI; ++u) {
       const int q = u * NTH + tid;
-      if (q < items) ET<T>::to_lds(buf + (size_t)q * 32, xv[u]);
+      if (q < items) store_slot(buf + (size_t)q * 32, xv[u]);
     }
   };
 
@@ -1114,7 +804,7 @@ __global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
         for (int tt = 0; tt < TT; ++tt) {
           const int m = tt * 16 + tl;
           const char* xb = m < M ? buf + ((size_t)(p * 4 + kg) * M + m) * 32 : lds + zero_off;
-          ET<T>::mma(acc[tt], wb[p], ET<T>::from_lds(xb));
+          ET<T>::mma(acc[tt], wb[p], lds_slot<T>(xb));
         }
       }
       const int nxt = c * HEAD_CK + p + P;
@@ -1152,51 +842,6 @@ __global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
 
 size_t head_chunked_lds(int M) { return 2 * (size_t)HEAD_CK * 4 * M * 32 + 32; }
 
-// a launch, optionally stamping timing events at the kernel's start and end
-template <typename K, typename... Args>
-static void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, const LaunchEvents* ev, Args... args) {
-  if (ev) hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, s, ev->start, ev->stop, 0, args...);
-  else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
-}
-
-// Workgroup width (n-tiles) of a wide pass: the candidate with the lowest rounds x width x
-// per-tile cost, one workgroup per CU (the kernel holds ~200-240 registers per lane). The per-tile
-// cost falls with width, since an activation fragment feeds WN/4 n-tiles (128-feature tiles were
-// measured about 1.35x slower per tile than 256-feature ones). The LM head keeps 16 when it ranks
-// its logits (its argmax partials are per 8 n-tiles); only the tile-local epilogues take 12 (QKV)
-// or 20 (gate/up, the head writing logits only).
-template <int EPI>
-static int wide_width(int n_tiles, int MT, bool argmax) {
-  const bool local = EPI != EPI_HEAD || !argmax;   // every epilogue group tile-local
-  const int cands[] = {16, 8, (EPI == EPI_SWIGLU || (EPI == EPI_HEAD && local)) ? 20 : 0, EPI == EPI_QKV ? 12 : 0};
-  int best = n_tiles >= 192 ? 16 : 8;
-  long long best_cost = -1;
-  for (int wn : cands) {
-    if (wn == 0 || (!local && wn != 16 && n_tiles >= 192)) continue;
-    const int per_tile = wn == 8 ? 135 : wn == 12 ? 112 : wn == 16 ? 100 : 95;
-    const long long wgs = (long long)((n_tiles + wn - 1) / wn) * MT;
-    const long long cost = (wgs + 255) / 256 * wn * per_tile;
-    if (best_cost < 0 || cost < best_cost || (cost == best_cost && wn > best)) {
-      best = wn;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
-// K-ranges of a residual projection's wide pass (8-n-tile workgroups): as many as keep the
-// workgroups of a 1024-row pass (8 token tiles) within two per CU (two 64 KB-LDS workgroups fit one
-// CU), at most WIDE_SPLIT_MAX. The count depends on the shape only, so a row's output does not
-// depend on the pass's row count. The 2560-wide projections of the 4B model (20 n-groups) take 3:
-// 480 workgroups; measured on its 1024-token prefill: 26.7 ms unsplit, 27.3 / 24.7 / 25.5 ms with
-// 2 / 3 / 4 k-ranges (2 leaves 64 CUs with two workgroups and the rest with one, 4 needs a third).
-static int wide_split(int n_tiles, int KT) {
-  constexpr int SLOTS = 2 * 256, MT_REF = 8;
-  const int ng = (n_tiles + 7) / 8;
-  const int S = std::max(1, std::min(SLOTS / (ng * MT_REF), WIDE_SPLIT_MAX));
-  return std::min(S, KT);
-}
-
 template <typename T, int PRO, int EPI>
 static void launch_linear_pe(const LinArgs& a0, int kind, hipStream_t s, const LaunchEvents* ev) {
   LinArgs a = a0;
@@ -1209,31 +854,6 @@ static void launch_linear_pe(const LinArgs& a0, int kind, hipStream_t s, const L
     const bool alias = lds < lds_x_bytes(a.M, a.K >> 5) + (size_t)(a.NJ * a.NT * a.KS * a.M + 1) * 16 * sizeof(float);
     if (alias) launch(k_linear_lds<T, PRO, EPI, true>, grid, block, lds, s, ev, a);
     else launch(k_linear_lds<T, PRO, EPI, false>, grid, block, lds, s, ev, a);
-    return;
-  }
-  if (kind == LIN_WIDE) {
-    const int MT = (a.M + WIDE_ROWS_TILE - 1) / WIDE_ROWS_TILE;
-    const int wn = wide_width<EPI>(n_tiles, MT, a.amax_val != nullptr);
-    const int NG = (n_tiles + wn - 1) / wn;
-    const dim3 grid((unsigned)((NG + 7) / 8 * 8 * MT)), block(512);
-    if constexpr (PRO == PRO_PLAIN && EPI == EPI_RESID) {
-      const int S = wn == 8 ? wide_split(n_tiles, a.K >> 5) : 1;
-      if (S > 1) {
-        a.KS = S;
-        const LaunchEvents e0{ev ? ev->start : nullptr, nullptr}, e1{nullptr, ev ? ev->stop : nullptr};
-        launch(k_linear_wide<T, PRO, EPI, 8, true>, dim3((unsigned)((NG * S + 7) / 8 * 8 * MT)), block, WIDE_LDS, s,
-               ev ? &e0 : nullptr, a);
-        const dim3 rgrid((unsigned)((n_tiles + 7) / 8), (unsigned)((a.M + WIDE_RED_ROWS - 1) / WIDE_RED_ROWS));
-        launch(k_wide_splitk_resid, rgrid, block, 0, s, ev ? &e1 : nullptr, a, (const float*)a.part);
-        return;
-      }
-    }
-    switch (wn) {
-      case 20: if constexpr (EPI == EPI_SWIGLU || EPI == EPI_HEAD) launch(k_linear_wide<T, PRO, EPI, 20, false>, grid, block, WIDE_LDS, s, ev, a); break;
-      case 12: if constexpr (EPI == EPI_QKV) launch(k_linear_wide<T, PRO, EPI, 12, false>, grid, block, WIDE_LDS, s, ev, a); break;
-      case 16: launch(k_linear_wide<T, PRO, EPI, 16, false>, grid, block, WIDE_LDS, s, ev, a); break;
-      default: launch(k_linear_wide<T, PRO, EPI, 8, false>, grid, block, WIDE_LDS, s, ev, a); break;
-    }
     return;
   }
   if (kind == LIN_SPLITK) {
@@ -1290,6 +910,10 @@ static void launch_linear_pe(const LinArgs& a0, int kind, hipStream_t s, const L
 
 template <typename T>
 void launch_linear(const LinArgs& a, int prologue, int epilogue, int kind, hipStream_t s, const LaunchEvents* ev) {
+  if (kind == LIN_WIDE) {
+    launch_linear_wide<T>(a, epilogue, s, ev);
+    return;
+  }
   if (prologue == PRO_NORM) {
     switch (epilogue) {
       case EPI_QKV: launch_linear_pe<T, PRO_NORM, EPI_QKV>(a, kind, s, ev); break;
@@ -1324,20 +948,9 @@ static bool allow_big_lds(int bytes) {
                        reinterpret_cast<const void*>(&k_linear_mfma<T, PRO, EPI, 1>),
                        reinterpret_cast<const void*>(&k_linear_mfma<T, PRO, EPI, 2>),
                        reinterpret_cast<const void*>(&k_linear_mfma<T, PRO, EPI, 3>),
-                       reinterpret_cast<const void*>(&k_linear_mfma<T, PRO, EPI, 4>),
-                       reinterpret_cast<const void*>(&k_linear_wide<T, PRO, EPI, 16, false>),
-                       reinterpret_cast<const void*>(&k_linear_wide<T, PRO, EPI, 8, false>)};
+                       reinterpret_cast<const void*>(&k_linear_mfma<T, PRO, EPI, 4>)};
   bool ok = true;
   for (const void* f : fns) ok &= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_HEAD)
-    ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(&k_linear_wide<T, PRO, EPI, 20, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
-  if constexpr (EPI == EPI_QKV)
-    ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(&k_linear_wide<T, PRO, EPI, 12, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
-  if constexpr (PRO == PRO_PLAIN && EPI == EPI_RESID)
-    ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(&k_linear_wide<T, PRO, EPI, 8, true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
   return ok;
 }
 

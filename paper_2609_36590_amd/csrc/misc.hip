@@ -76,24 +76,40 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs a) {
       a.row_rope[(size_t)m * a.head_dim + half + i] = a.rope_sin[(size_t)pos * half + i];
     }
   }
+  // a thread per 8 features; features 16j..16j+7 and 16j+8..16j+15 fall to neighbouring lanes, which
+  // add the squares of their 16 features in feature order
   const int KT = a.H >> 5;
   const T* E = reinterpret_cast<const T*>(a.E);
   const int nt = tok >> 4, rr = tok & 15;
-  for (int j = threadIdx.x; j < (a.H >> 4); j += blockDim.x) {
-    const int k0 = j * 16, kt = k0 >> 5, kg = (k0 >> 3) & 3;
-    const T* src = E + ((size_t)nt * KT + kt) * 512 + (rr + 16 * kg) * 8;
-    float v0[8], v1[8];
-    ET<T>::to_f32(ET<T>::load(src), v0);
-    ET<T>::to_f32(ET<T>::load(src + 128), v1);   // lane + 16 => next 8 features
+  float rowsum = 0.f;
+  for (int j = threadIdx.x; j < (a.H >> 3); j += blockDim.x) {
+    const int k0 = j * 8, kt = k0 >> 5, kg = (k0 >> 3) & 3;
+    float v[8], g[8];
+    ET<T>::to_f32(ET<T>::load(E + ((size_t)nt * KT + kt) * 512 + (rr + 16 * kg) * 8), v);
+    load8(a.gain + k0, g);
     float* hp = a.h + (size_t)m * a.H + k0;
-    float* xgp = a.xg + (size_t)m * a.H + k0;
-    const float* gp = a.gain + k0;
+    reinterpret_cast<float4*>(hp)[0] = make_float4(v[0], v[1], v[2], v[3]);
+    reinterpret_cast<float4*>(hp)[1] = make_float4(v[4], v[5], v[6], v[7]);
+    act_put4<T>(a.xg, KT, m, k0, make_float4(v[0] * g[0], v[1] * g[1], v[2] * g[2], v[3] * g[3]));
+    act_put4<T>(a.xg, KT, m, k0 + 4, make_float4(v[4] * g[4], v[5] * g[5], v[6] * g[6], v[7] * g[7]));
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { hp[i] = v0[i]; xgp[i] = v0[i] * gp[i]; s += v0[i] * v0[i]; }
+    for (int i = 0; i < 8; ++i) s += v[i] * v[i];
+    s = __shfl_xor(s, 1);   // the odd lane goes on from its neighbour's sum
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { hp[8 + i] = v1[i]; xgp[8 + i] = v1[i] * gp[8 + i]; s += v1[i] * v1[i]; }
-    a.ssq[(size_t)m * (a.H >> 4) + j] = s;
+    for (int i = 0; i < 8; ++i) s += v[i] * v[i];
+    if (j & 1) {
+      a.ssq[(size_t)m * (a.H >> 4) + (j >> 1)] = s;
+      rowsum += s;
+    }
+  }
+  if (a.rs) {   // a pass of more than 64 rows: the row's RMSNorm scale
+    __shared__ float s_sum[4];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) rowsum += __shfl_xor(rowsum, o);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = rowsum;
+    __syncthreads();
+    if (threadIdx.x == 0) a.rs[m] = rsqrtf((((s_sum[0] + s_sum[1]) + s_sum[2]) + s_sum[3]) / (float)a.H + a.eps);
   }
 }
 

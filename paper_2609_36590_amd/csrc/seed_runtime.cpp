@@ -68,7 +68,7 @@ struct Plan {
   std::vector<size_t> w_attn_norm, w_mlp_norm, w_qkv, w_o, w_gu, w_down;
   size_t kv_total;
   // workspace
-  size_t o_pf_o, o_pf_ml, o_wide_part, o_h, o_xg, o_ssq, o_q, o_attn, o_act, o_part, o_row_seq, o_row_pos, o_row_slot, o_row_blk, o_row_rope, o_amax_val,
+  size_t o_pf_o, o_pf_ml, o_wide_part, o_h, o_xg, o_ssq, o_rs, o_q, o_attn, o_act, o_part, o_row_seq, o_row_pos, o_row_slot, o_row_blk, o_row_rope, o_amax_val,
       o_amax_idx, o_vtok;
   size_t o_t, o_len, o_limit, o_active, o_nacc, o_bonus, o_rounds, o_counters, o_drafts, o_tokens,
       o_trace, o_log, o_bt, o_nll, o_splitk, o_splitk_rs, o_tree, o_tree_out, o_scratch, o_stamp, ws_total;
@@ -149,6 +149,7 @@ Plan make_plan(const seed_config& c) {
   p.o_h = take(R * p.H * 4);
   p.o_xg = take(R * p.H * 4);
   p.o_ssq = take(R * (p.H / 16) * 4);
+  p.o_rs = take(R * 4);
   p.o_q = take(R * p.QD * 4);
   p.o_attn = take(R * p.QD * 4);
   p.o_act = take(R * p.F * 4);
@@ -374,9 +375,10 @@ LinArgs lin_base(seed_ctx* c, int M) {
   a.nssq = p.H / 16;
   a.eps = p.cfg.rms_eps;
   a.h = c->ws<float>(p.o_h);
-  a.xg = c->ws<float>(p.o_xg);
+  a.xg = c->ws<char>(p.o_xg);
+  a.rs = a.rs_out = c->ws<float>(p.o_rs);
   a.ssq_out = c->ws<float>(p.o_ssq);
-  a.act = c->ws<float>(p.o_act);
+  a.act = c->ws<char>(p.o_act);
   a.q = c->ws<float>(p.o_q);
   a.kv = c->KV;
   a.row_pos = c->ws<int>(p.o_row_pos);
@@ -438,7 +440,6 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
                 const int* bt_override, bool cap, const SpecPass* spec = nullptr, bool tree = false,
                 int pass_pos0 = 0) {
   const Plan& p = c->p;
-  float* h = c->ws<float>(p.o_h);
   for (int li = l0; li < l1; ++li) {
     LinArgs a = lin_base(c, M);
     a.layer = li;
@@ -449,7 +450,7 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
     }
     // QKV + RoPE + KV write
     a.W = c->W + p.w_qkv[li]; a.N = p.QD + 2 * p.KVD; a.K = p.H;
-    a.X = c->ws<float>(p.o_xg); a.ldx = p.H;
+    a.X = c->ws<char>(p.o_xg);
     linear<T>(c, a, PRO_NORM, EPI_QKV, phase, SEED_OP_QKV, cap);
     // attention
     AttnArgs at;
@@ -476,7 +477,7 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
     }
     at.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)p.HD));
     at.part = c->ws<float>(p.o_part);
-    at.out = c->ws<float>(p.o_attn);
+    at.out = c->ws<char>(p.o_attn);
     at.pf_o = c->ws<float>(p.o_pf_o);
     at.pf_ml = c->ws<float>(p.o_pf_ml);
     // a one-launch pass over a long cache splits each row-block's positions over PF_SPLIT_LONG
@@ -497,27 +498,27 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
       as.R = std::min(r_step, R - r0);
       as.n_rb = cdiv(as.R, p.RB);
       as.q = at.q + (size_t)r0 * p.QD;
-      as.out = at.out + (size_t)r0 * p.QD;
+      as.out = reinterpret_cast<char*>(at.out) + (size_t)r0 * p.QD * 4;   // whole token tiles (16 rows)
       as.row_pos = at.row_pos + r0;
       as.row_slot = at.row_slot + r0;
       timed(c, phase, SEED_OP_ATTN, cap, [&](const LaunchEvents* ev) { launch_attention<T>(as, c->s, ev); });
       if (attention_needs_combine(as))
-        timed(c, phase, SEED_OP_COMBINE, cap, [&](const LaunchEvents* ev) { launch_attn_combine(as, c->s, ev); });
+        timed(c, phase, SEED_OP_COMBINE, cap, [&](const LaunchEvents* ev) { launch_attn_combine<T>(as, c->s, ev); });
     }
     // O + residual
     a = lin_base(c, M);
     a.W = c->W + p.w_o[li]; a.N = p.H; a.K = p.QD;
-    a.X = c->ws<float>(p.o_attn); a.ldx = p.QD; a.gain_next = c->wf(p.w_mlp_norm[li]);
+    a.X = c->ws<char>(p.o_attn); a.gain_next = c->wf(p.w_mlp_norm[li]);
     linear<T>(c, a, PRO_PLAIN, EPI_RESID, phase, SEED_OP_O, cap);
     // gate/up + SwiGLU
     a = lin_base(c, M);
     a.W = c->W + p.w_gu[li]; a.N = 2 * p.F; a.K = p.H;
-    a.X = c->ws<float>(p.o_xg); a.ldx = p.H;
+    a.X = c->ws<char>(p.o_xg);
     linear<T>(c, a, PRO_NORM, EPI_SWIGLU, phase, SEED_OP_GATEUP, cap);
     // down + residual
     a = lin_base(c, M);
     a.W = c->W + p.w_down[li]; a.N = p.H; a.K = p.F;
-    a.X = c->ws<float>(p.o_act); a.ldx = p.F;
+    a.X = c->ws<char>(p.o_act);
     a.gain_next = c->wf(li + 1 < p.L ? p.w_attn_norm[li + 1] : p.w_final_norm);
     linear<T>(c, a, PRO_PLAIN, EPI_RESID, phase, SEED_OP_DOWN, cap);
   }
@@ -529,7 +530,7 @@ void run_head(seed_ctx* c, int M, int* tok_out, int tok_stride, float* logits, l
   const Plan& p = c->p;
   LinArgs a = lin_base(c, M);
   a.W = c->W + p.w_embed; a.N = p.V; a.K = p.H;
-  a.X = c->ws<float>(p.o_xg); a.ldx = p.H;
+  a.X = c->ws<char>(p.o_xg);
   a.logits = logits; a.ld_logits = ld;
   if (!tok_out) a.amax_val = nullptr, a.amax_idx = nullptr;   // logits only: no argmax partials
   linear<T>(c, a, PRO_NORM, EPI_HEAD, phase, SEED_OP_HEAD, cap);
@@ -567,7 +568,8 @@ SetupArgs setup_base(seed_ctx* c, int l0) {
   s.row_blk = c->ws<int>(p.o_row_blk);
   s.row_rope = c->ws<float>(p.o_row_rope);
   s.h = c->ws<float>(p.o_h);
-  s.xg = c->ws<float>(p.o_xg);
+  s.xg = c->ws<char>(p.o_xg);
+  s.eps = p.cfg.rms_eps;
   s.gain = c->wf(l0 < p.L ? p.w_attn_norm[l0] : p.w_final_norm);
   s.ssq = c->ws<float>(p.o_ssq);
   s.rounds = c->ws<int>(p.o_rounds);
@@ -822,6 +824,7 @@ seed_status do_prefill(seed_ctx* c, const std::vector<int>& tokens_packed) {
       const int M = std::min(PREFILL_ROWS, n - s0);
       SetupArgs s = setup_base(c, 0);
       s.mode = SETUP_PREFILL; s.M = M; s.R = M; s.pf_seq = b; s.pf_pos0 = s0;
+      if (M > MAX_ROWS) s.rs = c->ws<float>(p.o_rs);
       timed(c, SEED_PHASE_PREFILL, SEED_OP_SETUP, false, [&](const LaunchEvents*) { launch_setup<T>(s, c->s); });
       run_layers<T>(c, M, 1, M, 0, p.L, SEED_PHASE_PREFILL,
                     c->ws<int>(p.o_bt) + (size_t)b * p.bt_stride, false, nullptr, false, s0);
@@ -854,6 +857,7 @@ seed_status do_spec(seed_ctx* c, int n, int block, void* skv, int skv_blocks, fl
     const int M = std::min(PREFILL_ROWS, rows - s0);
     SetupArgs s = setup_base(c, p.LD);
     s.mode = SETUP_SPEC; s.M = M; s.R = M; s.pf_seq = 0; s.pf_pos0 = s0;
+    if (M > MAX_ROWS) s.rs = c->ws<float>(p.o_rs);
     timed(c, SEED_PHASE_SPEC, SEED_OP_SETUP, false, [&](const LaunchEvents*) { launch_setup<T>(s, c->s); });
     run_layers<T>(c, M, 1, M, p.LD, p.L, SEED_PHASE_SPEC, c->ws<int>(p.o_bt), false, &sp, false, s0);
     run_head<T>(c, M, nullptr, 1, logits + (size_t)s0 * p.V, (long long)p.V, SEED_PHASE_SPEC, false);
