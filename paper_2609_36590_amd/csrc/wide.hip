@@ -27,17 +27,21 @@ namespace seedk {
 // to reproduce bit for bit.
 // Workgroup order: the token tiles of one n-group are consecutive workgroups of one XCD (workgroup
 // w runs on XCD w mod 8), so that the n-group's weights come from HBM once and from that XCD's L2
-// for its other token tiles.
+// for its other token tiles; wider passes go through all n-groups for 1024 rows at a time, so that an
+// XCD's 64 resident workgroups share activations too (4096 rows: gate/up 763 us with all 4096 rows of
+// an n-group in a row, 734 in blocks of 1024, 739 of 512, 763 of 2048).
 // ---------------------------------------------------------------------------------------------
-constexpr int WIDE_MJ = 4;   // token tiles per workgroup (64 rows)
+constexpr int WIDE_MJ = 4;    // token tiles per workgroup (64 rows)
+constexpr int WIDE_MTB = 16;  // workgroups (1024 rows) of one n-group in a row
 
 template <typename T, int EPI, int NI>
 __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
   constexpr int MJ = WIDE_MJ;
   constexpr int WN = 4 * NI;          // n-tiles per workgroup
-  constexpr int XU = MJ / 2;          // activation fragments each wave fetches per k-tile (2 planes x MJ / 4 waves)
+  constexpr int XU = MJ / 2;          // half tiles each wave fetches per k-tile (2 MJ / 4 waves)
   constexpr int SLOT = 2 * MJ * 1024;   // bytes of one LDS slot (a k-tile's activations)
-  __shared__ __attribute__((aligned(16))) char lds[2 * SLOT];
+  constexpr int ACT_IMG = EPI == EPI_SWIGLU ? MJ * NI * ACT_TILE : 0;   // the workgroup's packed outputs
+  __shared__ __attribute__((aligned(16))) char lds[2 * SLOT > ACT_IMG ? 2 * SLOT : ACT_IMG];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tl = lane & 15, kg = lane >> 4;
   const int KTF = a.K >> 5, n_tiles = a.N >> 4, m_tiles = (a.M + 15) >> 4;
@@ -45,8 +49,9 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
   // K in S k-ranges (residual projections), each (n-group, k-range) pair a virtual n-group of its own
   const int S = EPI == EPI_RESID ? a.KS : 1;
   const int b = blockIdx.x, xcd = b & 7, r = b >> 3;
-  const int mt = r % MT, gv = (r / MT) * 8 + xcd;
-  if (gv >= NG * S) return;   // padding of the grid to whole XCD rounds; the workgroup leaves together
+  const int MTB = min(MT, WIDE_MTB), per = (NG * S + 7) / 8 * MTB, mb = r / per, rb = r - mb * per;
+  const int mt = mb * MTB + rb % MTB, gv = (rb / MTB) * 8 + xcd;
+  if (gv >= NG * S || mt >= MT) return;   // padding of the grid to whole XCD rounds; the workgroup leaves together
   const int g = gv / S, ks = gv - g * S;
   const int kt0 = (ks * KTF) / S, KT = ((ks + 1) * KTF) / S - kt0;   // this workgroup's k-tiles
 
@@ -57,15 +62,23 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
 #pragma unroll
   for (int i = 0; i < NI; ++i)
     wp[i] = reinterpret_cast<const T*>(a.W) + ((size_t)min(nt0 + i, n_tiles - 1) * KTF + kt0) * 512 + lane * 8;
+  // A wave's load covers 8 rows' whole lines (half a tile, 1 KB without gaps: fragment-shaped loads of 16
+  // half lines cost the gate/up GEMM 12%). In LDS a tile is its two planes in operand order, 16 rows
+  // per k-group, with row r of k-group kg of plane p at place r ^ (4p + kg): the 8 lanes that
+  // write one line then fall on different banks, and a fragment read still covers each k-group's 256
+  // bytes whole.
   const char* xp[XU];
   char* xl[XU];
 #pragma unroll
   for (int u = 0; u < XU; ++u) {
-    const int f = u * 4 + wave;   // fragment: token tile f / 2, plane f % 2
+    const int f = u * 4 + wave, c = lane & 7;   // half tile: token tile f / 2, rows 8 (f % 2) ..; line chunk c = 4p + kg
     xp[u] = reinterpret_cast<const char*>(a.X) + ((size_t)min(mt * MJ + (f >> 1), m_tiles - 1) * KTF + kt0) * ACT_TILE +
-            tl * ACT_ROW + (f & 1) * ACT_PLANE + kg * 16;
-    xl[u] = lds + f * 1024 + lane * 16;
+            (f & 1) * 1024 + lane * 16;
+    xl[u] = lds + (f >> 1) * ACT_TILE + c * 256 + (((f & 1) * 8 + (lane >> 3)) ^ c) * 16;
   }
+  const char* br[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) br[p] = lds + (4 * p + kg) * 256 + (tl ^ (4 * p + kg)) * 16;
   typedef typename ET<T>::A WA;
   WA w0[NI], w1[NI];
   u32x4 x0[XU], x1[XU], b0[MJ][2], b1[MJ][2];
@@ -93,7 +106,7 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
     for (int j = 0; j < MJ; ++j)
 #pragma unroll
       for (int p = 0; p < 2; ++p)
-        bf[j][p] = *reinterpret_cast<const u32x4*>(lds + slot * SLOT + (j * 2 + p) * 1024 + lane * 16);
+        bf[j][p] = *reinterpret_cast<const u32x4*>(br[p] + slot * SLOT + j * ACT_TILE);
   };
   // k-tile t: operands in w and bf; x holds k-tile t + 2's activations, slot p = t & 1 is free (every
   // wave read it before the last barrier) and slot p ^ 1 holds k-tile t + 1's
@@ -175,7 +188,7 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
         float y[4], o[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) y[q] = acc[i][j][q] * rs;
-        const bool ok = live && (nt0 + i) < n_tiles;
+        const bool ok = live && nt0 + i < n_tiles;
         if constexpr (EPI == EPI_HEAD) {
           if (ok) {
             if (((uintptr_t)a.logits & 15) == 0) {   // rows are whole multiples of 16 floats
@@ -195,10 +208,10 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
               const float gv = hf ? o[q] : y[q], uv = hf ? y[q] : o[q];
               v[q] = gv / (1.f + __expf(-gv)) * uv;
             }
-            // both lanes of a pair hold the 4 values: each writes one plane
-            const int F = a.N >> 1, k = (nt0 + i) * 8 + c4;
-            if (ok)
-              ET<T>::put4_plane(act_row(a.act, F >> 5, row, k), k, make_float4(v[0], v[1], v[2], v[3]), hf);
+            // both lanes of a pair hold the 4 values: each writes one plane of them. The workgroup's
+            // 32 NI features are NI whole k-tiles of the output, assembled in LDS and copied out below
+            const int k = (wave * NI + i) * 8 + c4;
+            ET<T>::put4_plane(lds + (j * NI + (k >> 5)) * ACT_TILE + tl * ACT_ROW, k, make_float4(v[0], v[1], v[2], v[3]), hf);
           } else {   // EPI_QKV
             const int HD = a.head_dim, half = HD >> 1;
             int sec, head, jt;
@@ -234,6 +247,20 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
             }
           }
         }
+      }
+    }
+  }
+  if constexpr (EPI == EPI_SWIGLU) {
+    __syncthreads();
+    const int KTO = a.N >> 6;   // k-tiles of the output (N / 2 features)
+    for (int t = wave; t < MJ * NI; t += 4) {
+      const int m = mt * MJ + t / NI, kt = g * NI + t % NI;
+      if (m < m_tiles && kt < KTO) {
+        char* out = reinterpret_cast<char*>(a.act) + ((size_t)m * KTO + kt) * ACT_TILE + lane * 16;
+        const char* img = lds + t * ACT_TILE + lane * 16;
+        const u32x4 v0 = *reinterpret_cast<const u32x4*>(img), v1 = *reinterpret_cast<const u32x4*>(img + 1024);
+        *reinterpret_cast<u32x4*>(out) = v0;
+        *reinterpret_cast<u32x4*>(out + 1024) = v1;
       }
     }
   }
@@ -297,15 +324,18 @@ template <typename T, int EPI, int NI>
 static void launch_wide_tile(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
   const int n_tiles = a.N >> 4, m_tiles = (a.M + 15) >> 4;
   const int NG = (n_tiles + 4 * NI - 1) / (4 * NI), MT = (m_tiles + WIDE_MJ - 1) / WIDE_MJ, S = EPI == EPI_RESID ? a.KS : 1;
-  launch(k_linear_wide<T, EPI, NI>, dim3((unsigned)((NG * S + 7) / 8 * 8 * MT)), dim3(256), 0, s, ev, a);
+  const int MTB = std::min(MT, WIDE_MTB);
+  launch(k_linear_wide<T, EPI, NI>, dim3((unsigned)((NG * S + 7) / 8 * 8 * MTB * ((MT + MTB - 1) / MTB))), dim3(256), 0,
+         s, ev, a);
 }
 
 // n-tiles per wave: the candidate with the lowest rounds of one workgroup per CU x (n-tiles + a fixed
-// part for the token tiles' staging, which every n-tile of the wave shares). Measured on 1024 rows of
-// the 4B shapes, us for NI = 3 / 4 / 5 / 6: gate/up (1216 n-tiles) 189 / 170 / 166 / 183, QKV (384)
-// 65 / 78 / 88 / 65, O and down (160 in 2 k-ranges, mean) 77 / 91 / 63 / 70; 8 token tiles per
-// workgroup instead of 4 (one wave per SIMD) were slower at every width (prefill of 4 layers 2.92
-// against 2.26 ms).
+// part for the token tiles' staging, which every n-tile of the wave shares), a quarter more when there
+// is one round only (a lone workgroup on a CU has none to overlap its barriers). Measured, us for NI =
+// 3 / 4 / 5 / 6: gate/up (1216 n-tiles) of 1024 rows 189 / 170 / 166 / 183, of 4096 rows NI = 4 / 5 / 6
+// 716 / 678 / 669; QKV (384) of 1024 rows 65 / 78 / 88 / 65; O and down (160 in 2 k-ranges, mean) 77 / 91
+// / 63 / 70. 8 token tiles per workgroup instead of 4 (one wave per SIMD) were slower at every width
+// (prefill of 4 layers 2.92 against 2.26 ms).
 template <typename T, int EPI>
 static void launch_wide_epi(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
   if constexpr (sizeof(T) == 4) {   // fp32 operands take twice the registers
@@ -316,7 +346,7 @@ static void launch_wide_epi(const LinArgs& a, hipStream_t s, const LaunchEvents*
     long long best_cost = -1;
     for (int ni = 6; ni >= 1; --ni) {
       const long long wgs = (long long)((n_tiles + 4 * ni - 1) / (4 * ni)) * MT * S;
-      const long long cost = (wgs + 255) / 256 * (10 * ni + 3);
+      const long long rounds = (wgs + 255) / 256, cost = rounds * (10 * ni + 12) * (rounds == 1 ? 5 : 4);
       if (best_cost < 0 || cost < best_cost) best = ni, best_cost = cost;
     }
     switch (best) {
