@@ -438,24 +438,308 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 }
 
 // Causal attention of a wide single-sequence pass (the prompt's prefill, more than 64 rows at a
-// time). The decode kernel above spreads a row-block's positions over groups of workgroups and
-// merges their partials in a second launch, which suits a few rows over a long cache; across a
-// whole prompt it re-reads every key/value once per 32-query-vector row-block and writes a partial
-// per group. Here a workgroup owns 64 query vectors (64 / G rows of the G query heads of one KV
-// head, one 16-vector tile per wave) and each wave streams every visible 16-position tile in
-// order with an online softmax (the same per-tile contractions, masking and base-2 softmax as the
-// decode kernel), so the output is written directly: no partials, no merge launch, and each tile
-// is fetched from memory once per workgroup (the four waves read it from the CU's cache).
-// Tiles are loaded two ahead into registers; every load is issued unconditionally (a tile past the
-// last visible one reloads that tile and is fully masked), and the block table is staged in LDS so
-// that no key/value address waits on a global load.
-// The block-causal variant (SPEC: the drafting objective's decoder pass) contracts every tile with
-// both caches, the deep one below each query's block start and the pass's own one from there to
-// the query, and selects per (query, position) as the decode kernel's SPEC variant does.
-template <typename T, int HD, bool SPEC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_attention_prefill(AttnArgs a) {
+// time), bf16 caches. A workgroup owns 64 QT query vectors (64 QT / G rows of the G query heads of one
+// KV head), 16 QT per wave, and streams the visible positions in stages of 64 (4 paged blocks) with an
+// online softmax; the output is written directly. The decode kernel above spreads positions over groups
+// of workgroups and merges partials, which suits a few rows over a long cache. Here the matrix cores
+// (128 MFMAs of 16 cycles per wave and stage at QT = 2) and the softmax's vector instructions (about
+// 1500 cycles) bound it; two waves share a SIMD and overlap them, and both are cut to what is needed:
+//  * a stage's keys and values are fetched once per workgroup, a stage ahead in registers, and staged
+//    in LDS in MFMA operand order (two slots, one barrier per stage): reads and key writes are
+//    linear, and at QT = 2 the waves read 64 bytes of LDS per CU and MFMA cycle (128 at QT = 1);
+//  * values of two blocks sit side by side, so that O^T += V^T P^T takes 32 positions per MFMA with the
+//    probabilities where S^T left them (slots 0..3 of a lane: positions 4kg.. of the first block,
+//    4..7: of the second);
+//  * fragments are read a group of MFMAs ahead, and consecutive MFMAs go to different accumulators;
+//  * the running maximum is updated once per 64 positions and O is rescaled only when some lane's
+//    maximum moved (a factor of exactly 1 otherwise); row sums stay per lane until the end; stages
+//    that every query of the wave sees whole skip the mask, and stages no query sees are skipped.
+// Measured (4B heads): 1024 rows from position 0 63 -> 39 us, at 8k positions (mean) 468 -> 286 us, the
+// block-causal pass of 1023 rows 96 -> 43 us, against a kernel of 16-position tiles that rescaled on
+// every tile and contracted every block-causal tile with both caches; 4096 rows at 8k positions 1.0 ms
+// (1.1 PFLOP/s of MFMA work, counting both planes of the queries and probabilities).
+// The block-causal variant (SPEC: the drafting objective's decoder pass) streams the deep cache below
+// the last row's block start, then the pass's own cache from the first row's block start on: a query
+// sees deep positions below its block start and its own block's up to itself.
+template <int HD, bool SPEC, int QT>
+__global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a) {
+  constexpr int DS = HD / 32, DT = HD / 16, PB = 4;
+  constexpr int KCH = 2 * HD;             // 16-byte chunks of a block's keys (and of its values)
+  constexpr int CU = PB * KCH / 256;      // key (and value) chunks per thread and stage
+  constexpr int HALF = PB * KCH * 16;     // bytes of a stage's keys
+  __shared__ __attribute__((aligned(16))) char lds[2 * 2 * HALF];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tl = lane & 15, kg = lane >> 4;
+  const int rows_wg = QT * 64 / a.G;
+  const int n_rbp = (a.R + rows_wg - 1) / rows_wg;
+  // the row-blocks with the most positions first, so that the short ones fill the tail
+  const int rbp = n_rbp - 1 - (int)blockIdx.x / a.n_kv, h = (int)blockIdx.x % a.n_kv;
+  const int r0 = rbp * rows_wg, nr = min(rows_wg, a.R - r0);
+  const int maxpos = a.row_pos[r0 + nr - 1];
+  const int qstride = a.n_heads * HD;
+
+  // this lane's query vectors qv = (wave*QT + qt)*16 + tl: row qv / G, head qv % G of the KV head's
+  // group. A vector past the last row takes row 0's place and is not stored.
+  int rl[QT], gq[QT], qlo[QT], qhi[QT];   // deep cache: visible below qhi (SPEC: qlo); own cache: [qlo, qhi)
+  bool qok[QT];
+  bf16x8 qf[QT][DS][2];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    const int qv = (wave * QT + qt) * 16 + tl;
+    qok[qt] = qv < nr * a.G;
+    rl[qt] = qok[qt] ? qv / a.G : 0;
+    gq[qt] = qok[qt] ? qv - rl[qt] * a.G : 0;
+    const int pos = a.row_pos[r0 + rl[qt]];
+    qhi[qt] = pos + 1;
+    qlo[qt] = SPEC ? pos / a.s_block * a.s_block : 0;
+    const float* qp = a.q + (size_t)(r0 + rl[qt]) * qstride + (h * a.G + gq[qt]) * HD;
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) {
+      float x[8];
+      load8(qp + ds * 32 + kg * 8, x);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] *= a.scale_log2;
+      const ET<uint16_t>::B b = ET<uint16_t>::split(x);
+      qf[qt][ds][0] = b.hi;
+      qf[qt][ds][1] = b.lo;
+    }
+  }
+  // the wave's extreme bounds: of the rows' positions and (SPEC) of their block starts
+  constexpr int Q1 = QT - 1;
+  int hi_min = min(qhi[0], qhi[Q1]), hi_max = max(qhi[0], qhi[Q1]), lo_min = min(qlo[0], qlo[Q1]), lo_max = max(qlo[0], qlo[Q1]);
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    hi_min = min(hi_min, __shfl_xor(hi_min, o));
+    hi_max = max(hi_max, __shfl_xor(hi_max, o));
+    lo_min = min(lo_min, __shfl_xor(lo_min, o));
+    lo_max = max(lo_max, __shfl_xor(lo_max, o));
+  }
+  // stages: the deep cache's [0, deep_end) positions, then (SPEC) the own cache's from own0
+  const int own0 = SPEC ? a.row_pos[r0] / a.s_block * a.s_block / 16 : 0;   // first block of the own cache
+  const int deep_end = SPEC ? maxpos / a.s_block * a.s_block : maxpos + 1;
+  const int nb_deep = (deep_end + 15) >> 4, ns_deep = (nb_deep + PB - 1) / PB;
+  const int nb_all = (maxpos >> 4) + 1;
+  const int n_stages = ns_deep + (SPEC ? (nb_all - own0 + PB - 1) / PB : 0);
+  // positions split over a.pf_split workgroups: this one takes stages [s0, s1) and, when the pass is
+  // split, writes an unnormalised partial that k_prefill_merge combines (an empty range its identity)
+  const int ks = blockIdx.y, s0 = ks * n_stages / a.pf_split, s1 = (ks + 1) * n_stages / a.pf_split;
+
+  const uint16_t* deep = reinterpret_cast<const uint16_t*>(a.kv) + (size_t)h * 16 * HD;
+  const uint16_t* own = reinterpret_cast<const uint16_t*>(a.skv) + (size_t)h * 16 * HD;
+  const size_t plane = (size_t)a.n_kv * 16 * HD;   // a block's keys of all heads (its values follow)
+  u32x4 kreg[CU], vreg[CU];
+  // Loads are unconditional: stages past the last one re-read it, and blocks past the visible range are
+  // masked (the block table is padded to whole stages with the zero block; the own cache's last block is
+  // re-read). Lane i of `ids` holds the block id of block i of the next stage to load: a vector load a
+  // stage ahead, since a scalar one in flight would make every wait for LDS a wait for all of it.
+  int ids = 0;
+  auto idload = [&](int s) __attribute__((always_inline)) {
+    ids = a.bt[min(s, max(ns_deep - 1, 0)) * PB + (lane & (PB - 1))];
+  };
+  auto gload = [&](int s) __attribute__((always_inline)) {
+    const int sc = min(s, n_stages - 1);
+    const bool od = SPEC && sc >= ns_deep;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int ub = KCH == 256 ? u : u * 2 + (wave >> 1);   // the chunk's block in the stage
+      const int rem = KCH == 256 ? tid : tid & 127;
+      const int id = od ? a.s_layer * a.s_n_blocks + min(own0 + (sc - ns_deep) * PB + ub, nb_all - 1)
+                        : a.layer * a.n_blocks + __builtin_amdgcn_readlane(ids, ub);
+      const uint16_t* kb = (od ? own : deep) + (size_t)id * 2 * plane;
+      kreg[u] = *reinterpret_cast<const u32x4*>(kb + (rem & 15) * HD + (rem >> 4) * 8);
+      vreg[u] = *reinterpret_cast<const u32x4*>(kb + plane + rem * 8);
+    }
+    idload(s + 1);
+  };
+  auto lstore = [&](int slot) __attribute__((always_inline)) {
+    char* kl = lds + slot * 2 * HALF;
+    char* vl = kl + HALF;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int ch = u * 256 + tid, ub = ch / KCH, rem = ch % KCH;
+      *reinterpret_cast<u32x4*>(kl + ch * 16) = kreg[u];   // slot (block, ds, kg, position) = ch
+      // dims d, positions 8c..8c+7: kg = 2c and 2c + 1 of (pair of blocks, dt); first or second 8 bytes
+      const int d = rem >> 1, c = rem & 1;
+      char* vp = vl + (((ub >> 1) * DT + (d >> 4)) * 64 + 2 * c * 16 + (d & 15)) * 16 + (ub & 1) * 8;
+      typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+      *reinterpret_cast<u32x2*>(vp) = u32x2{vreg[u][0], vreg[u][1]};
+      *reinterpret_cast<u32x2*>(vp + 256) = u32x2{vreg[u][2], vreg[u][3]};
+    }
+  };
+  float m_c[QT], l_c[QT];
+  f32x4 o_c[QT][DT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    m_c[qt] = NEG_INF;
+    l_c[qt] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o_c[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto consume = [&](int s, int slot) __attribute__((always_inline)) {
+    const bool od = SPEC && s >= ns_deep;
+    const int p0 = od ? (own0 + (s - ns_deep) * PB) * 16 : s * PB * 16;   // the stage's first position
+    const int lim_min = SPEC && !od ? lo_min : hi_min, lim_max = SPEC && !od ? lo_max : hi_max;
+    if (p0 >= lim_max || (od && p0 + PB * 16 <= lo_min)) return;   // no query of the wave sees it
+    const char* kl = lds + slot * 2 * HALF + lane * 16;
+    const char* vl = kl + HALF;
+    // each block's fragments are read while the previous block's are multiplied (left alone, the
+    // scheduler reads one fragment at a time and waits for it)
+    f32x4 sc[PB][QT];
+    bf16x8 kf[2][4];
+    // fragment i of group g: block 2 (g / (DS/2)) + i / 2, dims 64 (g mod DS/2) + 32 (i mod 2) ..
+    auto kread = [&](bf16x8 (&f)[4], int g) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        f[i] = *reinterpret_cast<const bf16x8*>(kl + ((g / (DS / 2) * 2 + (i >> 1)) * DS + g % (DS / 2) * 2 + (i & 1)) * 1024);
+    };
+    constexpr int NKG = PB / 2 * (DS / 2);
+    kread(kf[0], 0);
+#pragma unroll
+    for (int g = 0; g < NKG; ++g) {
+      if (g + 1 < NKG) kread(kf[(g + 1) & 1], g + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const int u0 = g / (DS / 2) * 2, ds0 = g % (DS / 2) * 2;
+#pragma unroll
+      for (int ds = 0; ds < 2; ++ds)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+              const f32x4 c0 = ds0 + ds + p == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sc[u0 + u][qt];
+              sc[u0 + u][qt] =
+                  __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[g & 1][u * 2 + ds], qf[qt][ds0 + ds][p], c0, 0, 0, 0);
+            }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    constexpr int VG = DT / 2, NVG = PB / 2 * 2;   // value fragments per group; groups per stage
+    bf16x8 vf[2][VG];
+    auto vread = [&](bf16x8 (&f)[VG], int g) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < VG; ++i) f[i] = *reinterpret_cast<const bf16x8*>(vl + (g * VG + i) * 1024);
+    };
+    if (p0 + PB * 16 > lim_min || (od && p0 < lo_max)) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const int lo = od ? qlo[qt] : 0, hi = SPEC && !od ? qlo[qt] : qhi[qt];
+#pragma unroll
+        for (int u = 0; u < PB; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int pos = p0 + u * 16 + 4 * kg + i;
+            if (pos >= hi || pos < lo) sc[u][qt][i] = NEG_INF;
+          }
+      }
+    }
+    bf16x8 ph[QT][PB / 2], pl[QT][PB / 2];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      float mx = fmaxf(fmaxf(sc[0][qt][0], sc[0][qt][1]), fmaxf(sc[0][qt][2], sc[0][qt][3]));
+#pragma unroll
+      for (int u = 1; u < PB; ++u)
+        mx = fmaxf(mx, fmaxf(fmaxf(sc[u][qt][0], sc[u][qt][1]), fmaxf(sc[u][qt][2], sc[u][qt][3])));
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_n = fmaxf(m_c[qt], mx);
+      const float m_u = m_n == NEG_INF ? 0.f : m_n;   // nothing visible so far: every p is 0
+      if (__any(m_n != m_c[qt])) {
+        const float alpha = __builtin_amdgcn_exp2f(m_c[qt] - m_u);   // 0 while m_c is -inf
+        l_c[qt] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o_c[qt][dt][i] *= alpha;
+        m_c[qt] = m_n;
+      }
+      float sum = 0.f;
+#pragma unroll
+      for (int u = 0; u < PB; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {   // pairs, as the conversion takes them
+          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+          typedef __attribute__((ext_vector_type(2))) float f32x2;
+          const float p = __builtin_amdgcn_exp2f(sc[u][qt][i] - m_u), q = __builtin_amdgcn_exp2f(sc[u][qt][i + 1] - m_u);
+          sum += p;
+          sum += q;
+          const bf16x2 hi = __builtin_convertvector((f32x2{p, q}), bf16x2);
+          const uint32_t hb = __builtin_bit_cast(uint32_t, hi);
+          const bf16x2 lo = __builtin_convertvector(
+              (f32x2{p - __uint_as_float(hb << 16), q - __uint_as_float(hb & 0xFFFF0000u)}), bf16x2);
+          const int e = (u & 1) * 4 + i;
+          ph[qt][u >> 1][e] = hi[0], ph[qt][u >> 1][e + 1] = hi[1];
+          pl[qt][u >> 1][e] = lo[0], pl[qt][u >> 1][e + 1] = lo[1];
+        }
+      l_c[qt] += sum;
+    }
+    vread(vf[0], 0);
+#pragma unroll
+    for (int g = 0; g < NVG; ++g) {
+      if (g + 1 < NVG) vread(vf[(g + 1) & 1], g + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const int pr = g >> 1, dt0 = (g & 1) * VG;
+#pragma unroll
+      for (int i = 0; i < VG; ++i)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+          o_c[qt][dt0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[g & 1][i], ph[qt][pr], o_c[qt][dt0 + i], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < VG; ++i)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+          o_c[qt][dt0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[g & 1][i], pl[qt][pr], o_c[qt][dt0 + i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  if (s1 > s0) {
+    idload(s0);
+    gload(s0);
+    lstore(0);
+    gload(s0 + 1);
+    __syncthreads();
+    // slot s & 1 holds stage s; the other one was read before the last barrier
+    for (int s = s0; s < s1; ++s) {
+      const int slot = (s - s0) & 1;
+      lstore(slot ^ 1);
+      gload(s + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(s, slot);
+      __syncthreads();
+    }
+  }
+
+  // lane (qv, kg) holds dims dt*16 + 4kg .. +3 of query vector qv
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    float l = l_c[qt];
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (!qok[qt]) continue;
+    if (a.pf_split == 1) {
+      const float inv = 1.f / l;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        act_put4<uint16_t>(a.out, qstride >> 5, r0 + rl[qt], (h * a.G + gq[qt]) * HD + dt * 16 + 4 * kg,
+                           make_float4(o_c[qt][dt][0] * inv, o_c[qt][dt][1] * inv, o_c[qt][dt][2] * inv, o_c[qt][dt][3] * inv));
+    } else {
+      const size_t pidx = ((size_t)ks * a.R + r0 + rl[qt]) * a.n_heads + h * a.G + gq[qt];   // (split, row, head)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        *reinterpret_cast<float4*>(a.pf_o + pidx * HD + dt * 16 + 4 * kg) =
+            make_float4(o_c[qt][dt][0], o_c[qt][dt][1], o_c[qt][dt][2], o_c[qt][dt][3]);
+      if (kg == 0) *reinterpret_cast<float2*>(a.pf_ml + pidx * 2) = make_float2(m_c[qt], l);
+    }
+  }
+}
+
+// The same for fp32 caches: 64 query vectors per workgroup, one 16-vector tile per wave; each
+// wave streams every visible 16-position tile in order, loaded two ahead into registers. Every load is
+// issued unconditionally (a tile past the last visible one reloads that tile and is fully masked). The
+// block-causal variant contracts every tile with both caches and selects per (query, position).
+template <int HD, bool SPEC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_attention_pass_f32(AttnArgs a) {
+  typedef float T;
   constexpr int DS = HD / 32, DT = HD / 16, NC = SPEC ? 2 : 1;
-  extern __shared__ int s_bt[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tl = lane & 15, kg = lane >> 4;
   const int rows_wg = 64 / a.G;
   const int n_rbp = (a.R + rows_wg - 1) / rows_wg;
@@ -464,16 +748,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   const int r0 = rbp * rows_wg, nr = min(rows_wg, a.R - r0);
   const int maxpos = a.row_pos[r0 + nr - 1];
   const int t_last = maxpos >> 4;
-  for (int i0 = 0; i0 <= t_last; i0 += 4 * (int)blockDim.x) {   // 4 entries per thread in flight
-    int e[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) e[u] = a.bt[min(i0 + u * (int)blockDim.x + (int)threadIdx.x, t_last)];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * (int)blockDim.x + (int)threadIdx.x;
-      if (i <= t_last) s_bt[i] = e[u];
-    }
-  }
 
   // this lane's query vector qv = wave*16 + tl: row qv / G, head qv % G of the KV head's group
   const int qv = wave * 16 + tl;
@@ -506,8 +780,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     }
     return;
   }
-  __syncthreads();   // the block table is in LDS
-
   const T* kvp = reinterpret_cast<const T*>(a.kv);
   const size_t layer_base = (size_t)a.layer * a.n_blocks;
   typedef typename ET<T>::A KA;
@@ -518,7 +790,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
       const T* base = cc == 0 ? kvp : reinterpret_cast<const T*>(a.skv);
-      const size_t blk = cc == 0 ? layer_base + s_bt[tc] : (size_t)a.s_layer * a.s_n_blocks + tc;
+      const size_t blk = cc == 0 ? layer_base + a.bt[tc] : (size_t)a.s_layer * a.s_n_blocks + tc;
       const T* kp = base + ((blk * 2 + 0) * a.n_kv + h) * 16 * HD + tl * HD + kg * 8;
 #pragma unroll
       for (int ds = 0; ds < DS; ++ds) kf[cc][ds] = ET<T>::load(kp + ds * 32);
@@ -585,109 +857,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     }
   };
 
-  if constexpr (sizeof(T) == 2) {
-    // bf16 caches: each tile is fetched once per workgroup (one 16-byte key chunk and one value
-    // chunk per thread and cache) and staged in LDS, from which every wave reads its fragments,
-    // instead of each wave fetching the whole tile for itself (a quarter of the memory requests).
-    // RD register stages keep RD - 1 tiles in flight; tiles alternate between two LDS slots, one
-    // barrier per tile. Key chunk c of position row r sits at column c ^ kswz(r) of its row and
-    // value chunk c of dim row d at c ^ ((d >> 3) & 1), so the 16 rows a fragment read touches fall
-    // on distinct banks.
-    constexpr int CPR = HD / 8;            // 16-byte chunks per key row (one position)
-    constexpr int NKC = 16 * CPR;          // key chunks per tile and cache
-    constexpr int NCH = 2 * NKC;           // key and value chunks per tile and cache
-    constexpr int TB = NCH * 16;           // bytes per tile and cache
-    constexpr int CPT = NC * NCH / 256;    // chunks per thread and tile
-    static_assert(NC * NCH % 256 == 0, "whole chunks per thread");
-    constexpr int RD = 4;                  // register stages r0..r3 below
-    char* stage = reinterpret_cast<char*>(s_bt) + prefill_bt_bytes(a.bt_stride);
-    auto kswz = [](int r) { return (r * CPR / 16) % CPR; };
-    auto gload = [&](u32x4 (&rg)[CPT], int t) __attribute__((always_inline)) {
-      const int tc = min(t, t_end - 1);
-#pragma unroll
-      for (int u = 0; u < CPT; ++u) {
-        const int q = u * 256 + (int)threadIdx.x, cc = q / NCH, qq = q - cc * NCH;
-        const T* base = cc == 0 ? kvp : reinterpret_cast<const T*>(a.skv);
-        const size_t blk = cc == 0 ? layer_base + s_bt[tc] : (size_t)a.s_layer * a.s_n_blocks + tc;
-        const int r = qq / CPR, kc = (qq % CPR) ^ kswz(r);
-        const int d = (qq - NKC) >> 1, vc = ((qq - NKC) & 1) ^ ((d >> 3) & 1);
-        const T* src = qq < NKC ? base + ((blk * 2 + 0) * a.n_kv + h) * 16 * HD + r * HD + kc * 8
-                                : base + ((blk * 2 + 1) * a.n_kv + h) * HD * 16 + d * 16 + vc * 8;
-        rg[u] = *reinterpret_cast<const u32x4*>(src);
-      }
-    };
-    auto lstore = [&](const u32x4 (&rg)[CPT], int slot) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < CPT; ++u)   // chunk q = cc * NCH + qq at byte 16 q of the slot
-        *reinterpret_cast<u32x4*>(stage + (size_t)slot * NC * TB + (size_t)(u * 256 + threadIdx.x) * 16) = rg[u];
-    };
-    auto lfrag = [&](KA (&kf)[NC][DS], VA (&vf)[NC][DT], int slot) __attribute__((always_inline)) {
-      const char* sb = stage + (size_t)slot * NC * TB;
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc) {
-#pragma unroll
-        for (int ds = 0; ds < DS; ++ds)
-          kf[cc][ds].v = *reinterpret_cast<const uint4*>(sb + cc * TB + tl * (HD * 2) + ((ds * 4 + kg) ^ kswz(tl)) * 16);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const int d = dt * 16 + tl;
-          vf[cc][dt].v = *reinterpret_cast<const uint2*>(sb + cc * TB + NKC * 16 + d * 32 +
-                                                          (((kg >> 1) ^ ((d >> 3) & 1)) * 16) + (kg & 1) * 8);
-        }
-      }
-    };
-    // register stages, named so that every index is a constant (tile j lives in stage j mod RD)
-    u32x4 r0[CPT], r1[CPT], r2[CPT], r3[CPT];
-    gload(r0, t0);   // each tile's loads strictly after the previous tile's
+  KA ka[NC][DS], kb[NC][DS];
+  VA va[NC][DT], vb[NC][DT];
+  // tile 0's loads strictly before tile 1's, here as in the loop: if the scheduler issued them
+  // in the other order, the first use of tile 0 would have to wait for both tiles on every
+  // iteration
+  load_tile(ka, va, t0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_tile(kb, vb, t0 + 1);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int t = t0; t < t_end; t += 2) {
+    consume(ka, va, t);
+    load_tile(ka, va, t + 2);
     __builtin_amdgcn_sched_barrier(0);
-    gload(r1, t0 + 1);
+    consume(kb, vb, t + 1);   // past t_last: the last tile again, every position masked
+    load_tile(kb, vb, t + 3);
     __builtin_amdgcn_sched_barrier(0);
-    gload(r2, t0 + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    gload(r3, t0 + 3);
-    __builtin_amdgcn_sched_barrier(0);
-    lstore(r0, 0);
-    gload(r0, t0 + RD);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    // tile tt from slot (tt - t0) & 1 (past t_end: the last tile again, every position masked); then tile
-    // tt + 1, fetched RD - 1 tiles ago into stage `next`, into the other slot (whose previous tile
-    // every wave finished before the last barrier), and `next` refilled with tile tt + 1 + RD
-    auto step = [&](int tt, int slot, u32x4 (&next)[CPT]) __attribute__((always_inline)) {
-      KA kf[NC][DS];
-      VA vf[NC][DT];
-      lfrag(kf, vf, slot);
-      consume(kf, vf, tt);
-      __builtin_amdgcn_sched_barrier(0);
-      lstore(next, slot ^ 1);
-      gload(next, tt + 1 + RD);
-      __builtin_amdgcn_sched_barrier(0);
-      __syncthreads();
-    };
-    for (int t = t0; t < t_end; t += RD) {
-      step(t, 0, r1);
-      step(t + 1, 1, r2);
-      step(t + 2, 0, r3);
-      step(t + 3, 1, r0);
-    }
-  } else {
-    KA ka[NC][DS], kb[NC][DS];
-    VA va[NC][DT], vb[NC][DT];
-    // tile 0's loads strictly before tile 1's, here as in the loop: if the scheduler issued them
-    // in the other order, the first use of tile 0 would have to wait for both tiles on every
-    // iteration
-    load_tile(ka, va, t0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_tile(kb, vb, t0 + 1);
-    __builtin_amdgcn_sched_barrier(0);
-    for (int t = t0; t < t_end; t += 2) {
-      consume(ka, va, t);
-      load_tile(ka, va, t + 2);
-      __builtin_amdgcn_sched_barrier(0);
-      consume(kb, vb, t + 1);   // past t_last: the last tile again, every position masked
-      load_tile(kb, vb, t + 3);
-      __builtin_amdgcn_sched_barrier(0);
-    }
   }
 
   // lane (qv, kg) holds dims dt*16 + 4kg .. +3 of query vector qv
@@ -790,32 +975,50 @@ void launch_attention(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev) 
   else launch_attention_hd<T, 64>(a, s, ev);
 }
 
-// LDS of one prefill workgroup: the block table, then (bf16) two tile slots of both caches
-static size_t prefill_lds(const AttnArgs& a, bool bf16) {
-  const size_t tile = (size_t)2 * 16 * a.head_dim * 2 * (a.s_block > 0 ? 2 : 1);
-  return prefill_bt_bytes(a.bt_stride) + (bf16 ? 2 * tile : 0);
+bool attention_prefill_supported(const AttnArgs& a) {
+  return a.B == 1 && a.G >= 1 && 64 % a.G == 0 && (a.head_dim == 128 || a.head_dim == 64) && !a.tree;
 }
 
-bool attention_prefill_supported(const AttnArgs& a) {
-  // the block table must fit LDS beside the tile slots (capacities up to ~131k positions); longer
-  // ones take the split-KV kernel
-  return a.B == 1 && a.G >= 1 && 64 % a.G == 0 && (a.head_dim == 128 || a.head_dim == 64) && !a.tree &&
-         prefill_lds(a, true) <= 65536;
+static unsigned pass_workgroups(const AttnArgs& a, int qv) {   // qv query vectors per workgroup
+  const int rows_wg = qv / a.G;
+  return (unsigned)(((a.R + rows_wg - 1) / rows_wg) * a.n_kv);
+}
+
+// Query vectors per wave (16 pf_qt) and position splits of a pass. Two workgroups fit a CU, so 512 fill
+// the chip: passes with that many 128-vector workgroups take those; a pass of at most PF_SPLIT_ROWS rows
+// over a cache that began PF_SPLIT_ROWS positions before it or earlier splits its positions until there
+// are (16k-token prefill of two layers in 1024-row passes: 22.7 / 21.6 / 21.7 ms with 1 / 2 / 3 splits); the others take 64-vector workgroups, whose lengths balance the causal triangle better
+// (1024 rows from position 0: 39 us against 48).
+void attention_pass_plan(AttnArgs& a, int pos0, bool bf16) {
+  constexpr unsigned FULL = 512;
+  const unsigned w2 = pass_workgroups(a, 128), w1 = pass_workgroups(a, 64);
+  const bool may_split = pos0 >= PF_SPLIT_ROWS && a.R <= PF_SPLIT_ROWS;
+  auto splits = [&](unsigned w) { return may_split ? (int)std::min((FULL + w - 1) / w, (unsigned)PF_SPLIT_MAX) : 1; };
+  a.pf_qt = bf16 && w2 * splits(w2) >= FULL ? 2 : 1;
+  a.pf_split = splits(a.pf_qt == 2 ? w2 : w1);
+}
+
+template <typename T, int HD, bool SPEC>
+static void launch_attention_pass(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev) {
+  const dim3 grid(pass_workgroups(a, 64 * a.pf_qt), (unsigned)a.pf_split);
+  if constexpr (sizeof(T) == 2) {
+    if (a.pf_qt == 2) launch_kernel(k_attention_pass<HD, SPEC, 2>, grid, s, ev, a);
+    else launch_kernel(k_attention_pass<HD, SPEC, 1>, grid, s, ev, a);
+  } else {
+    launch_kernel(k_attention_pass_f32<HD, SPEC>, grid, s, ev, a);
+  }
 }
 
 template <typename T>
 void launch_attention_prefill(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  const int rows_wg = 64 / a.G;
-  const dim3 grid((unsigned)(((a.R + rows_wg - 1) / rows_wg) * a.n_kv), (unsigned)a.pf_split);
-  const size_t lds = prefill_lds(a, sizeof(T) == 2);
   const LaunchEvents e0{ev ? ev->start : nullptr, nullptr}, e1{nullptr, ev ? ev->stop : nullptr};
   const LaunchEvents* ea = ev ? (a.pf_split > 1 ? &e0 : ev) : nullptr;
   if (a.s_block > 0) {
-    if (a.head_dim == 128) launch_kernel(k_attention_prefill<T, 128, true>, grid, s, ea, a, lds);
-    else launch_kernel(k_attention_prefill<T, 64, true>, grid, s, ea, a, lds);
+    if (a.head_dim == 128) launch_attention_pass<T, 128, true>(a, s, ea);
+    else launch_attention_pass<T, 64, true>(a, s, ea);
   } else {
-    if (a.head_dim == 128) launch_kernel(k_attention_prefill<T, 128, false>, grid, s, ea, a, lds);
-    else launch_kernel(k_attention_prefill<T, 64, false>, grid, s, ea, a, lds);
+    if (a.head_dim == 128) launch_attention_pass<T, 128, false>(a, s, ea);
+    else launch_attention_pass<T, 64, false>(a, s, ea);
   }
   if (a.pf_split > 1) {
     const long long items = (long long)a.R * a.n_heads * (a.head_dim / 4);

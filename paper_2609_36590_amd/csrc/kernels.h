@@ -94,10 +94,10 @@ struct AttnArgs {
   const void* skv;
   int s_layer, s_n_blocks, s_block;
   int tree;               // 1: packed draft tree rows (mask by row_pos and row_slot)
-  // one-launch pass attention (launch_attention_prefill): positions split over pf_split workgroups
-  // per row-block, whose partials [pf_split][R][n_heads] (o: head_dim floats, then m and l) are
+  // one-launch pass attention (launch_attention_prefill, set by attention_pass_plan): 16 * pf_qt query
+  // vectors per wave, and positions split over pf_split workgroups per row-block, whose partials [pf_split][R][n_heads] (o: head_dim floats, then m and l) are
   // merged by a second kernel when pf_split > 1
-  int pf_split;
+  int pf_qt, pf_split;
   float* pf_o;
   float* pf_ml;
   int span;               // positions per workgroup group: 64, 128 or 256 (attention_span)
@@ -107,9 +107,6 @@ struct AttnArgs {
   float* part;            // group partials [B][n_kv][n_rb][n_groups_max][32][head_dim + 4]
   void* out;              // packed activations [M][n_heads*head_dim]
 };
-
-// bytes of a prefill attention workgroup's staged block table (16-byte aligned)
-__host__ __device__ inline int prefill_bt_bytes(int bt_stride) { return (bt_stride * 4 + 15) / 16 * 16; }
 
 // Per-pass row setup + embedding gather.
 enum SetupMode { SETUP_PREFILL = 0, SETUP_DRAFT = 1, SETUP_VERIFY = 2, SETUP_SPEC = 3, SETUP_TREE = 4 };
@@ -183,7 +180,8 @@ struct DevState {
 enum LinearKind { LIN_LDS = 0, LIN_GLOBAL = 1, LIN_SPLITK = 2, LIN_WIDE = 3 };
 constexpr int LDS_MAX_PASSES = 8;   // n-tile passes (NJ) of one k_linear_lds workgroup
 constexpr int HEAD_WIDE_NT = 16;    // n-tiles (waves) per workgroup of the LM head for 17..64 rows
-constexpr int PF_SPLIT_MAX = 4;    // position splits of the one-launch pass attention
+constexpr int PF_SPLIT_MAX = 3;     // position splits of the one-launch pass attention,
+constexpr int PF_SPLIT_ROWS = 1024;  // of passes of at most this many rows
 constexpr int WIDE_SPLIT_MAX = 4;   // k-ranges of a split wide pass (its partials: WIDE_SPLIT_MAX x rows x N floats)
 
 // Optional timing events stamped by the launches themselves (hipExtLaunchKernel): `start` at the
@@ -204,6 +202,8 @@ void launch_attention(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev =
 // Causal attention of a single-sequence pass of more than 64 rows (the prompt's prefill), written
 // directly (no partials): 64 query vectors per workgroup, every visible tile streamed in order.
 bool attention_prefill_supported(const AttnArgs& a);
+// sets pf_qt and pf_split for a pass whose first row is at position pos0
+void attention_pass_plan(AttnArgs& a, int pos0, bool bf16);
 template <typename T>
 void launch_attention_prefill(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
 // Merge of the group partials; needed when the context capacity spans more than one group.

@@ -48,9 +48,9 @@ seed_status fail(seed_status s, const std::string& msg) {
     if (e_ != hipSuccess) return fail(SEED_ERR_HIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-constexpr int PREFILL_ROWS = 1024; // rows per prefill / drafting-objective pass (tiled MFMA GEMMs)
-constexpr int PF_SPLIT_LONG = 3;   // position splits of a pass's attention beyond its first PREFILL_ROWS
-static_assert(PF_SPLIT_LONG <= seedk::PF_SPLIT_MAX, "split partials fit the workspace");
+// rows per prefill / drafting-objective pass (16k-token prefill of two 4B layers: 21.8 / 20.7 / 20.6 / 20.9
+// ms with 1024 / 2048 / 4096 / 8192)
+constexpr int PREFILL_ROWS = 4096;
 constexpr int MAX_ROWS = 64;       // rows per decode pass: max_batch * (max_draft + 1)
 constexpr int ATT_ROWS = 256;      // rows per attention launch of a wider single-sequence pass
 
@@ -113,8 +113,8 @@ Plan make_plan(const seed_config& c) {
   // attention row-blocks of one launch: a decode pass (<= MAX_ROWS rows over max_batch sequences)
   // or ATT_ROWS rows of one sequence's prefill / drafting-objective pass
   p.n_rb_max = cdiv(MAX_ROWS, p.RB);
-  p.max_rows = std::max(MAX_ROWS, PREFILL_ROWS);   // decode passes (B (d+1) <= 64), draft trees of <= 64
-                                                  // nodes, prefill and drafting-objective passes
+  // decode passes (B (d+1) <= 64), draft trees of <= 64 nodes, prefill and drafting-objective passes
+  p.max_rows = std::max(MAX_ROWS, std::min(PREFILL_ROWS, cdiv(c.max_ctx, 16) * 16));
   p.blocks_per_seq = cdiv(c.max_ctx, 16);
   p.span = seedk::attention_span(c.max_ctx, c.max_batch);
   p.bt_stride = cdiv(p.blocks_per_seq, p.span / 16) * (p.span / 16);   // whole groups, padded with block 0
@@ -160,8 +160,8 @@ Plan make_plan(const seed_config& c) {
   p.o_row_slot = take(R * 4);
   p.o_row_blk = take(R * 4);
   p.o_row_rope = take(R * p.HD * 4);
-  p.o_amax_val = take(R * (size_t)(p.V / 16) * 4);
-  p.o_amax_idx = take(R * (size_t)(p.V / 16) * 4);
+  p.o_amax_val = take((size_t)MAX_ROWS * (p.V / 16) * 4);   // wider passes rank no logits
+  p.o_amax_idx = take((size_t)MAX_ROWS * (p.V / 16) * 4);
   p.o_vtok = take(R * 4);
   p.o_t = take(B * 4);
   p.o_len = take(B * 4);
@@ -192,8 +192,9 @@ Plan make_plan(const seed_config& c) {
     p.o_splitk = take(ksn * MAX_ROWS * 4);   // only passes of at most MAX_ROWS rows split K
     p.o_splitk_rs = take((size_t)MAX_ROWS * 4);
   }
-  p.o_pf_o = take((size_t)PF_SPLIT_LONG * p.max_rows * p.QD * 4);   // split pass attention partials
-  p.o_pf_ml = take((size_t)PF_SPLIT_LONG * p.max_rows * p.NQ * 2 * 4);
+  const size_t split_rows = (size_t)PF_SPLIT_MAX * std::min(p.max_rows, PF_SPLIT_ROWS);
+  p.o_pf_o = take(split_rows * p.QD * 4);   // split pass attention partials
+  p.o_pf_ml = take(split_rows * p.NQ * 2 * 4);
   p.o_wide_part = take((size_t)seedk::WIDE_SPLIT_MAX * p.max_rows * p.H * 4);   // split wide passes (N = H)
   p.o_topk = take((size_t)TOPK_PARTS * (2 * TOPK_MAX + 2) * 4);
   p.o_tdraft = take((size_t)TREE_MAX_STEPS * (TOPK_MAX + 2) * 4 + 16);
@@ -480,11 +481,7 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
     at.out = c->ws<char>(p.o_attn);
     at.pf_o = c->ws<float>(p.o_pf_o);
     at.pf_ml = c->ws<float>(p.o_pf_ml);
-    // a one-launch pass over a long cache splits each row-block's positions over PF_SPLIT_LONG
-    // workgroups (4B 16k prefill 651 / 634 / 607 / 610 ms with 1 / 2 / 3 / 4); a pass from position 0
-    // stays whole (its 1024-token prefill 23.9 / 24.0 / 24.2 / 24.4 ms: the merge costs more than the
-    // shorter chains save)
-    at.pf_split = pass_pos0 >= PREFILL_ROWS ? PF_SPLIT_LONG : 1;
+    attention_pass_plan(at, pass_pos0, p.cfg.dtype == SEED_BF16);
     // the prompt's prefill (one sequence, more than 64 rows): one launch over all of the pass's
     // rows, written directly. Otherwise group partials and their merge; a pass wider than the
     // partial buffer (the drafting objective's) runs its rows ATT_ROWS at a time, every row

@@ -1,0 +1,58 @@
+"""The attention of wide single-sequence passes (prefill and the drafting objective's decoder pass)
+against the oracle, at its edges: row counts around a workgroup's row-block and a stage of 64 positions;
+query groups of 1, 4, 8 and 32 heads; head sizes 64 and 128; enough row-blocks for the 128-vector
+workgroups; a second pass whose positions are split over workgroups and merged (prompts longer than a
+4096-row pass), with objective blocks that straddle the two passes. The objective's logits depend on both
+variants: on the prefill's causal attention through the deep keys and values, and on the block-causal
+one. Tolerances are those of the logits everywhere: 1e-4 fp32, 2e-2 bf16.
+"""
+import numpy as np
+import pytest
+
+from gpu_common import decoder, oracle_model, say
+from oracle import seed as os_
+from paper_2609_36590_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.C1_TINY.replace(n_layers=3, n_dec_layers=2, hidden=64, ffn=64, vocab=64, k=2)
+TOL = {synth.F32: 1e-4, synth.BF16: 2e-2}
+
+
+def _check(cfg, sizes, block):
+    w = synth.make_weights(cfg, seed=11)
+    m = oracle_model(cfg, w)
+    x = synth.make_prompts(cfg.replace(prompt_len=max(sizes)), seed=13)[0]
+    dec = decoder(cfg, w, max_batch=1, max_ctx=max(sizes) + 8, max_draft=2)
+    try:
+        for n in sizes:
+            say(f"[gpu] pass attention {cfg.name} {cfg.dtype} rows={n - 1} block={block}")
+            ref, _ = os_.spec_forward(m, x[:n], block)
+            lg, _, _ = dec.spec_forward(x[:n], block)
+            err = float(np.abs(lg - ref).max())
+            say(f"[gpu]   max |logits - oracle| = {err:.3g}")
+            assert np.all(np.isfinite(lg)) and err <= TOL[cfg.dtype]
+    finally:
+        dec.close()
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("heads,kv,hd", [(2, 2, 64), (8, 2, 64), (8, 1, 128), (32, 1, 64)])
+def test_row_blocks_and_stages(heads, kv, hd, dtype):
+    cfg = BASE.replace(name=f"pass-{heads}-{kv}-{hd}", n_heads=heads, n_kv_heads=kv, head_dim=hd, dtype=dtype)
+    _check(cfg, (66, 80, 81, 129, 130, 193), 7)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_workgroups_of_128_vectors(hd):
+    # 2 heads per KV head: 64 rows per workgroup, 32 row-blocks and a ragged one x 16 KV heads = 528
+    cfg = BASE.replace(name=f"pass-wide-{hd}", n_layers=2, n_dec_layers=1, n_heads=32, n_kv_heads=16, head_dim=hd,
+                       dtype=synth.BF16)
+    _check(cfg, (2090,), 33)
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_second_pass_splits_positions(dtype):
+    # passes of 4096 and 103 rows; blocks of 30 cross row 4096
+    cfg = BASE.replace(name="pass-split", n_layers=2, n_dec_layers=1, n_heads=4, n_kv_heads=1, head_dim=64, dtype=dtype)
+    _check(cfg, (4200,), 30)
