@@ -437,8 +437,8 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
   }
 }
 
-// Causal attention of a wide single-sequence pass (the prompt's prefill, more than 64 rows at a
-// time), bf16 caches. A workgroup owns 64 QT query vectors (64 QT / G rows of the G query heads of one
+// Causal attention of a pass of more than 64 rows (the prompts' prefill; several sequences may share the
+// pass, each attending to its own cache), bf16 caches. A workgroup owns 64 QT query vectors (64 QT / G rows of the G query heads of one
 // KV head), 16 QT per wave, and streams the visible positions in stages of 64 (4 paged blocks) with an
 // online softmax; the output is written directly. The decode kernel above spreads positions over groups
 // of workgroups and merges partials, which suits a few rows over a long cache. Here the matrix cores
@@ -462,7 +462,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 // the last row's block start, then the pass's own cache from the first row's block start on: a query
 // sees deep positions below its block start and its own block's up to itself.
 template <int HD, bool SPEC, int QT>
-__global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a) {
+__global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a, PassSegs sg) {
   constexpr int DS = HD / 32, DT = HD / 16, PB = 4;
   constexpr int KCH = 2 * HD;             // 16-byte chunks of a block's keys (and of its values)
   constexpr int CU = PB * KCH / 256;      // key (and value) chunks per thread and stage
@@ -470,10 +470,14 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) char lds[2 * 2 * HALF];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tl = lane & 15, kg = lane >> 4;
   const int rows_wg = QT * 64 / a.G;
-  const int n_rbp = (a.R + rows_wg - 1) / rows_wg;
+  // this workgroup's segment of the pass: rows row_b .. row_e - 1, its sequence's block table
+  const int row_b = sg.row0[blockIdx.z], row_e = row_b + sg.rows[blockIdx.z];
+  const int* bt = a.bt + (size_t)sg.seq[blockIdx.z] * a.bt_stride;
+  const int n_rbp = (row_e - row_b + rows_wg - 1) / rows_wg;
   // the row-blocks with the most positions first, so that the short ones fill the tail
   const int rbp = n_rbp - 1 - (int)blockIdx.x / a.n_kv, h = (int)blockIdx.x % a.n_kv;
-  const int r0 = rbp * rows_wg, nr = min(rows_wg, a.R - r0);
+  if (rbp < 0) return;   // the grid is as wide as the longest segment
+  const int r0 = row_b + rbp * rows_wg, nr = min(rows_wg, row_e - r0);
   const int maxpos = a.row_pos[r0 + nr - 1];
   const int qstride = a.n_heads * HD;
 
@@ -533,7 +537,7 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a) {
   // stage ahead, since a scalar one in flight would make every wait for LDS a wait for all of it.
   int ids = 0;
   auto idload = [&](int s) __attribute__((always_inline)) {
-    ids = a.bt[min(s, max(ns_deep - 1, 0)) * PB + (lane & (PB - 1))];
+    ids = bt[min(s, max(ns_deep - 1, 0)) * PB + (lane & (PB - 1))];
   };
   auto gload = [&](int s) __attribute__((always_inline)) {
     const int sc = min(s, n_stages - 1);
@@ -737,15 +741,18 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a) {
 // issued unconditionally (a tile past the last visible one reloads that tile and is fully masked). The
 // block-causal variant contracts every tile with both caches and selects per (query, position).
 template <int HD, bool SPEC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_attention_pass_f32(AttnArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_attention_pass_f32(AttnArgs a, PassSegs sg) {
   typedef float T;
   constexpr int DS = HD / 32, DT = HD / 16, NC = SPEC ? 2 : 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tl = lane & 15, kg = lane >> 4;
   const int rows_wg = 64 / a.G;
-  const int n_rbp = (a.R + rows_wg - 1) / rows_wg;
+  const int row_b = sg.row0[blockIdx.z], row_e = row_b + sg.rows[blockIdx.z];
+  const int* bt = a.bt + (size_t)sg.seq[blockIdx.z] * a.bt_stride;
+  const int n_rbp = (row_e - row_b + rows_wg - 1) / rows_wg;
   // the row-blocks with the most tiles first, so that the short ones fill the tail
   const int rbp = n_rbp - 1 - (int)blockIdx.x / a.n_kv, h = (int)blockIdx.x % a.n_kv;
-  const int r0 = rbp * rows_wg, nr = min(rows_wg, a.R - r0);
+  if (rbp < 0) return;
+  const int r0 = row_b + rbp * rows_wg, nr = min(rows_wg, row_e - r0);
   const int maxpos = a.row_pos[r0 + nr - 1];
   const int t_last = maxpos >> 4;
 
@@ -790,7 +797,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
       const T* base = cc == 0 ? kvp : reinterpret_cast<const T*>(a.skv);
-      const size_t blk = cc == 0 ? layer_base + a.bt[tc] : (size_t)a.s_layer * a.s_n_blocks + tc;
+      const size_t blk = cc == 0 ? layer_base + bt[tc] : (size_t)a.s_layer * a.s_n_blocks + tc;
       const T* kp = base + ((blk * 2 + 0) * a.n_kv + h) * 16 * HD + tl * HD + kg * 8;
 #pragma unroll
       for (int ds = 0; ds < DS; ++ds) kf[cc][ds] = ET<T>::load(kp + ds * 32);
@@ -979,46 +986,55 @@ bool attention_prefill_supported(const AttnArgs& a) {
   return a.B == 1 && a.G >= 1 && 64 % a.G == 0 && (a.head_dim == 128 || a.head_dim == 64) && !a.tree;
 }
 
-static unsigned pass_workgroups(const AttnArgs& a, int qv) {   // qv query vectors per workgroup
+static unsigned pass_workgroups(const AttnArgs& a, int rows, int qv) {   // qv query vectors per workgroup
   const int rows_wg = qv / a.G;
-  return (unsigned)(((a.R + rows_wg - 1) / rows_wg) * a.n_kv);
+  return (unsigned)(((rows + rows_wg - 1) / rows_wg) * a.n_kv);
 }
 
 // Query vectors per wave (16 pf_qt) and position splits of a pass. Two workgroups fit a CU, so 512 fill
 // the chip: passes with that many 128-vector workgroups take those; a pass of at most PF_SPLIT_ROWS rows
 // over a cache that began PF_SPLIT_ROWS positions before it or earlier splits its positions until there
-// are (16k-token prefill of two layers in 1024-row passes: 22.7 / 21.6 / 21.7 ms with 1 / 2 / 3 splits); the others take 64-vector workgroups, whose lengths balance the causal triangle better
-// (1024 rows from position 0: 39 us against 48).
-void attention_pass_plan(AttnArgs& a, int pos0, bool bf16) {
+// are (16k-token prefill of two layers in 1024-row passes: 22.7 / 21.6 / 21.7 ms with 1 / 2 / 3 splits);
+// the others take 64-vector workgroups, whose lengths balance the causal triangle better (1024 rows from
+// position 0: 39 us against 48). Only a pass of one segment splits. Without a split a row's result does
+// not depend on pf_qt (stages are absolute positions, a skipped rescale is one by exactly 1), so a
+// sequence's cache is the same whichever sequences share its pass.
+void attention_pass_plan(AttnArgs& a, const PassSegs& sg, bool bf16) {
   constexpr unsigned FULL = 512;
-  const unsigned w2 = pass_workgroups(a, 128), w1 = pass_workgroups(a, 64);
-  const bool may_split = pos0 >= PF_SPLIT_ROWS && a.R <= PF_SPLIT_ROWS;
+  unsigned w2 = 0, w1 = 0;
+  for (int i = 0; i < sg.n; ++i) {
+    w2 += pass_workgroups(a, sg.rows[i], 128);
+    w1 += pass_workgroups(a, sg.rows[i], 64);
+  }
+  const bool may_split = sg.n == 1 && sg.pos0[0] >= PF_SPLIT_ROWS && sg.rows[0] <= PF_SPLIT_ROWS;
   auto splits = [&](unsigned w) { return may_split ? (int)std::min((FULL + w - 1) / w, (unsigned)PF_SPLIT_MAX) : 1; };
   a.pf_qt = bf16 && w2 * splits(w2) >= FULL ? 2 : 1;
   a.pf_split = splits(a.pf_qt == 2 ? w2 : w1);
 }
 
 template <typename T, int HD, bool SPEC>
-static void launch_attention_pass(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  const dim3 grid(pass_workgroups(a, 64 * a.pf_qt), (unsigned)a.pf_split);
+static void launch_attention_pass(const AttnArgs& a, const PassSegs& sg, hipStream_t s, const LaunchEvents* ev) {
+  unsigned gx = 0;
+  for (int i = 0; i < sg.n; ++i) gx = std::max(gx, pass_workgroups(a, sg.rows[i], 64 * a.pf_qt));
+  const dim3 grid(gx, (unsigned)a.pf_split, (unsigned)sg.n), block(256);
   if constexpr (sizeof(T) == 2) {
-    if (a.pf_qt == 2) launch_kernel(k_attention_pass<HD, SPEC, 2>, grid, s, ev, a);
-    else launch_kernel(k_attention_pass<HD, SPEC, 1>, grid, s, ev, a);
+    if (a.pf_qt == 2) launch(k_attention_pass<HD, SPEC, 2>, grid, block, 0, s, ev, a, sg);
+    else launch(k_attention_pass<HD, SPEC, 1>, grid, block, 0, s, ev, a, sg);
   } else {
-    launch_kernel(k_attention_pass_f32<HD, SPEC>, grid, s, ev, a);
+    launch(k_attention_pass_f32<HD, SPEC>, grid, block, 0, s, ev, a, sg);
   }
 }
 
 template <typename T>
-void launch_attention_prefill(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev) {
+void launch_attention_prefill(const AttnArgs& a, const PassSegs& sg, hipStream_t s, const LaunchEvents* ev) {
   const LaunchEvents e0{ev ? ev->start : nullptr, nullptr}, e1{nullptr, ev ? ev->stop : nullptr};
   const LaunchEvents* ea = ev ? (a.pf_split > 1 ? &e0 : ev) : nullptr;
   if (a.s_block > 0) {
-    if (a.head_dim == 128) launch_attention_pass<T, 128, true>(a, s, ea);
-    else launch_attention_pass<T, 64, true>(a, s, ea);
+    if (a.head_dim == 128) launch_attention_pass<T, 128, true>(a, sg, s, ea);
+    else launch_attention_pass<T, 64, true>(a, sg, s, ea);
   } else {
-    if (a.head_dim == 128) launch_attention_pass<T, 128, false>(a, s, ea);
-    else launch_attention_pass<T, 64, false>(a, s, ea);
+    if (a.head_dim == 128) launch_attention_pass<T, 128, false>(a, sg, s, ea);
+    else launch_attention_pass<T, 64, false>(a, sg, s, ea);
   }
   if (a.pf_split > 1) {
     const long long items = (long long)a.R * a.n_heads * (a.head_dim / 4);
@@ -1040,7 +1056,7 @@ template void launch_attention<uint16_t>(const AttnArgs&, hipStream_t, const Lau
 template void launch_attention<float>(const AttnArgs&, hipStream_t, const LaunchEvents*);
 template void launch_attn_combine<uint16_t>(const AttnArgs&, hipStream_t, const LaunchEvents*);
 template void launch_attn_combine<float>(const AttnArgs&, hipStream_t, const LaunchEvents*);
-template void launch_attention_prefill<uint16_t>(const AttnArgs&, hipStream_t, const LaunchEvents*);
-template void launch_attention_prefill<float>(const AttnArgs&, hipStream_t, const LaunchEvents*);
+template void launch_attention_prefill<uint16_t>(const AttnArgs&, const PassSegs&, hipStream_t, const LaunchEvents*);
+template void launch_attention_prefill<float>(const AttnArgs&, const PassSegs&, hipStream_t, const LaunchEvents*);
 
 }  // namespace seedk

@@ -108,6 +108,14 @@ struct AttnArgs {
   void* out;              // packed activations [M][n_heads*head_dim]
 };
 
+// Sequences that share a wide pass, one after the other: rows row0 .. row0 + rows - 1 of the pass are
+// consecutive positions of sequence seq from pos0 on.
+constexpr int PASS_SEGS = 64;
+struct PassSegs {
+  int n;
+  int row0[PASS_SEGS], rows[PASS_SEGS], seq[PASS_SEGS], pos0[PASS_SEGS];
+};
+
 // Per-pass row setup + embedding gather.
 enum SetupMode { SETUP_PREFILL = 0, SETUP_DRAFT = 1, SETUP_VERIFY = 2, SETUP_SPEC = 3, SETUP_TREE = 4 };
 
@@ -120,7 +128,6 @@ struct SetupArgs {
   int step;               // SETUP_DRAFT: draft step i (>= 1)
   const int* tokens;      // committed tokens [B][tstride]
   int tstride;
-  int pf_seq, pf_pos0;    // SETUP_PREFILL, SETUP_SPEC (rows at positions pf_pos0..)
   int sim_accept;         // SETUP_VERIFY / SETUP_TREE: -1 or forced acceptance length
   const int* trace;       // [B][tstride] greedy trace by absolute position
   int vocab;
@@ -199,13 +206,13 @@ void launch_linear_wide(const LinArgs& a, int epilogue, hipStream_t s, const Lau
 // Attention partials per group of span positions (the final output when the rows see one group).
 template <typename T>
 void launch_attention(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
-// Causal attention of a single-sequence pass of more than 64 rows (the prompt's prefill), written
-// directly (no partials): 64 query vectors per workgroup, every visible tile streamed in order.
+// Causal (a.s_block > 0: block-causal) attention of a pass of more than 64 rows, every segment's rows over
+// its own sequence's cache, written directly.
 bool attention_prefill_supported(const AttnArgs& a);
-// sets pf_qt and pf_split for a pass whose first row is at position pos0
-void attention_pass_plan(AttnArgs& a, int pos0, bool bf16);
+// sets pf_qt and pf_split of a pass
+void attention_pass_plan(AttnArgs& a, const PassSegs& sg, bool bf16);
 template <typename T>
-void launch_attention_prefill(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
+void launch_attention_prefill(const AttnArgs& a, const PassSegs& sg, hipStream_t s, const LaunchEvents* ev = nullptr);
 // Merge of the group partials; needed when the context capacity spans more than one group.
 bool attention_needs_combine(const AttnArgs& a);
 // Positions per attention group for a context capacity and batch capacity (fixed per decoder, so
@@ -214,7 +221,7 @@ int attention_span(int max_ctx, int max_batch);
 template <typename T>
 void launch_attn_combine(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
 template <typename T>
-void launch_setup(const SetupArgs& a, hipStream_t s);
+void launch_setup(const SetupArgs& a, const PassSegs& sg, hipStream_t s);   // sg: SETUP_PREFILL, SETUP_SPEC
 void launch_accept(const DevState& st, int B, int k, hipStream_t s);
 // Tree acceptance for one sequence (packed tree of n nodes: tokens, parents, depths; the verifier
 // argmax per node in st.vtok) and the move of an accepted leaf's keys/values in every layer to the

@@ -12,7 +12,7 @@ namespace seedk {
 // the packed table into the fp32 residual stream, and write its per-16-feature sums of squares.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(256) k_setup(SetupArgs a) {
+__global__ void __launch_bounds__(256) k_setup(SetupArgs a, PassSegs sg) {
   const int m = blockIdx.x;
   __shared__ int s_tok, s_pos, s_seq, s_slot;
   if (a.stamp && m == 0 && threadIdx.x == 0) {
@@ -23,8 +23,10 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs a) {
   if (threadIdx.x == 0) {
     int b, pos, tok, slot = -1;
     if (a.mode == SETUP_PREFILL || a.mode == SETUP_SPEC) {
-      b = a.pf_seq;
-      pos = a.pf_pos0 + m;
+      int i = 0;
+      while (i + 1 < sg.n && m >= sg.row0[i + 1]) ++i;
+      b = sg.seq[i];
+      pos = sg.pos0[i] + m - sg.row0[i];
       tok = a.tokens[b * a.tstride + pos];
     } else if (a.mode == SETUP_DRAFT) {
       b = m;
@@ -348,8 +350,8 @@ __global__ void k_fill_u32(uint32_t* dst, uint32_t v, long long n) {
 // Launchers.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
-void launch_setup(const SetupArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_setup<T>), dim3(a.M), dim3(256), 0, s, a);
+void launch_setup(const SetupArgs& a, const PassSegs& sg, hipStream_t s) {
+  hipLaunchKernelGGL((k_setup<T>), dim3(a.M), dim3(256), 0, s, a, sg);
 }
 
 void launch_accept(const DevState& st, int B, int k, hipStream_t s) {
@@ -391,8 +393,8 @@ void launch_fill_u32(void* dst, unsigned value, long long n_words, hipStream_t s
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<uint32_t*>(dst), value, n_words);
 }
 
-template void launch_setup<uint16_t>(const SetupArgs&, hipStream_t);
-template void launch_setup<float>(const SetupArgs&, hipStream_t);
+template void launch_setup<uint16_t>(const SetupArgs&, const PassSegs&, hipStream_t);
+template void launch_setup<float>(const SetupArgs&, const PassSegs&, hipStream_t);
 template void launch_pack<uint16_t>(const void*, void*, const int*, int, int, hipStream_t);
 template void launch_pack<float>(const void*, void*, const int*, int, int, hipStream_t);
 
