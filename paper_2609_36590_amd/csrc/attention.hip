@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     if (n_groups == 1) {
       // the only group: the merge of groups reduces to o / l for it (weight 1), so finish here
       const int rl = qv / a.G, gq = qv - rl * a.G;
-      act_put4<T>(a.out, qstride >> 5, mrow0 + rl, (h * a.G + gq) * HD + d,
+      act_put4<T>(a.out, qstride >> 5, a.frag, mrow0 + rl, (h * a.G + gq) * HD + d,
                   make_float4(o_r[0] / l_r, o_r[1] / l_r, o_r[2] / l_r, o_r[3] / l_r));
     } else {
       float* pp = part + (size_t)qv * PS;
@@ -432,7 +432,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
   }
   if (j == 0) {
     const int rl = qv / a.G, gq = qv - rl * a.G;
-    act_put4<T>(a.out, a.n_heads * HD >> 5, mrow0 + rl, (h * a.G + gq) * HD + d,
+    act_put4<T>(a.out, a.n_heads * HD >> 5, a.frag, mrow0 + rl, (h * a.G + gq) * HD + d,
                 make_float4(o_r[0] / l_r, o_r[1] / l_r, o_r[2] / l_r, o_r[3] / l_r));
   }
 }
@@ -723,7 +723,7 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a, PassSegs 
       const float inv = 1.f / l;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
-        act_put4<uint16_t>(a.out, qstride >> 5, r0 + rl[qt], (h * a.G + gq[qt]) * HD + dt * 16 + 4 * kg,
+        act_put4<uint16_t>(a.out, qstride >> 5, true, r0 + rl[qt], (h * a.G + gq[qt]) * HD + dt * 16 + 4 * kg,
                            make_float4(o_c[qt][dt][0] * inv, o_c[qt][dt][1] * inv, o_c[qt][dt][2] * inv, o_c[qt][dt][3] * inv));
     } else {
       const size_t pidx = ((size_t)ks * a.R + r0 + rl[qt]) * a.n_heads + h * a.G + gq[qt];   // (split, row, head)
@@ -887,7 +887,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     const float inv = 1.f / l_c;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      act_put4<T>(a.out, qstride >> 5, r0 + rl, (h * a.G + gq) * HD + dt * 16 + 4 * kg,
+      act_put4<T>(a.out, qstride >> 5, true, r0 + rl, (h * a.G + gq) * HD + dt * 16 + 4 * kg,
                   make_float4(o_c[dt][0] * inv, o_c[dt][1] * inv, o_c[dt][2] * inv, o_c[dt][3] * inv));
   } else if (qok) {
 #pragma unroll
@@ -918,7 +918,7 @@ __global__ void __launch_bounds__(256) k_prefill_merge(AttnArgs a) {
   }
   const float inv = 1.f / l;
   const int row = (int)(rh / a.n_heads), head = (int)(rh - (long long)row * a.n_heads);
-  act_put4<T>(a.out, a.n_heads * a.head_dim >> 5, row, head * a.head_dim + d,
+  act_put4<T>(a.out, a.n_heads * a.head_dim >> 5, true, row, head * a.head_dim + d,
               make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv));
 }
 

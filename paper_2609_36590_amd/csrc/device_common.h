@@ -83,8 +83,8 @@ struct ET<uint16_t> {
   __device__ static B join(const uint4 p0, const uint4 p1) {
     return B{__builtin_bit_cast(bf16x8, p0), __builtin_bit_cast(bf16x8, p1)};
   }
-  // 4 consecutive values (k a multiple of 4) of a packed activation row
-  __device__ static void put4(char* row, int k, const float4 x) {
+  // 4 consecutive values (k a multiple of 4) of a packed activation slot, plane stride ps
+  __device__ static void put4(char* slot, int ps, int k, const float4 x) {
     const float v[4] = {x.x, x.y, x.z, x.w};
     bf16x4 h, l;
 #pragma unroll
@@ -93,12 +93,12 @@ struct ET<uint16_t> {
       h[j] = t;
       l[j] = (__bf16)(v[j] - (float)t);
     }
-    char* p = row + (k & 31) * 2;
+    char* p = slot + (k & 7) * 2;
     *reinterpret_cast<bf16x4*>(p) = h;
-    *reinterpret_cast<bf16x4*>(p + ACT_PLANE) = l;
+    *reinterpret_cast<bf16x4*>(p + ps) = l;
   }
   // one plane's share of put4
-  __device__ static void put4_plane(char* row, int k, const float4 x, int plane) {
+  __device__ static void put4_plane(char* slot, int ps, int k, const float4 x, int plane) {
     const float v[4] = {x.x, x.y, x.z, x.w};
     bf16x4 o;
 #pragma unroll
@@ -106,13 +106,7 @@ struct ET<uint16_t> {
       const __bf16 t = (__bf16)v[j];
       o[j] = plane ? (__bf16)(v[j] - (float)t) : t;
     }
-    *reinterpret_cast<bf16x4*>(row + plane * ACT_PLANE + (k & 31) * 2) = o;
-  }
-  __device__ static void put1(char* row, int k, float x) {
-    const __bf16 h = (__bf16)x;
-    char* p = row + (k & 31) * 2;
-    *reinterpret_cast<__bf16*>(p) = h;
-    *reinterpret_cast<__bf16*>(p + ACT_PLANE) = (__bf16)(x - (float)h);
+    *reinterpret_cast<bf16x4*>(slot + plane * ps + (k & 7) * 2) = o;
   }
 };
 
@@ -156,28 +150,19 @@ struct ET<float> {
     const float4 u = __builtin_bit_cast(float4, p0), v = __builtin_bit_cast(float4, p1);
     return B{{u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w}};
   }
-  __device__ static void put4(char* row, int k, const float4 x) {
-    *reinterpret_cast<float4*>(row + ((k >> 2) & 1) * ACT_PLANE + ((k >> 3) & 3) * 16) = x;
+  __device__ static void put4(char* slot, int ps, int k, const float4 x) {
+    *reinterpret_cast<float4*>(slot + ((k >> 2) & 1) * ps) = x;
   }
-  __device__ static void put4_plane(char* row, int k, const float4 x, int plane) {
-    if (plane == ((k >> 2) & 1)) put4(row, k, x);
-  }
-  __device__ static void put1(char* row, int k, float x) {
-    *reinterpret_cast<float*>(row + ((k >> 2) & 1) * ACT_PLANE + ((k >> 3) & 3) * 16 + (k & 3) * 4) = x;
+  __device__ static void put4_plane(char* slot, int ps, int k, const float4 x, int plane) {
+    if (plane == ((k >> 2) & 1)) put4(slot, ps, k, x);
   }
 };
 
-// Packed activations (layout in kernels.h): the line holding x[row][k] of a matrix of KT k-tiles.
-__device__ __forceinline__ char* act_row(void* base, int KT, int row, int k) {
-  return reinterpret_cast<char*>(base) + ((size_t)(row >> 4) * KT + (k >> 5)) * ACT_TILE + (row & 15) * ACT_ROW;
-}
+// Packed activations (layout in kernels.h): x[row][k..k+3] of a matrix of KT k-tiles.
 template <typename T>
-__device__ __forceinline__ void act_put4(void* base, int KT, int row, int k, const float4 x) {
-  ET<T>::put4(act_row(base, KT, row, k), k, x);
-}
-template <typename T>
-__device__ __forceinline__ void act_put1(void* base, int KT, int row, int k, float x) {
-  ET<T>::put1(act_row(base, KT, row, k), k, x);
+__device__ __forceinline__ void act_put4(void* base, int KT, bool frag, int row, int k, const float4 x) {
+  char* tile = reinterpret_cast<char*>(base) + ((size_t)(row >> 4) * KT + (k >> 5)) * ACT_TILE;
+  ET<T>::put4(tile + act_slot(frag, row & 15, (k >> 3) & 3), act_plane(frag), k, x);
 }
 
 __device__ __forceinline__ void load8(const float* p, float x[8]) {
@@ -196,6 +181,38 @@ __device__ __forceinline__ void qkv_tile(const LinArgs& a, int nt, int& sec, int
   else { sec = 2; lt = nt - q_tiles - k_tiles; }
   head = lt / tpd;
   j = lt - head * tpd;
+}
+
+// Epilogue of n-tiles g*NT .. of all M rows, whose finished values are Y[lt * ys + m * 16 + c]: logits (nullable), and
+// the n-group's argmax of each row (lowest token id among equal maxima; k_argmax_finalize reduces the
+// groups; none when the caller wants the logits only).
+__device__ __forceinline__ void head_epilogue(const LinArgs& a, int g, int NT, const float* Y, int ys) {
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nthr >> 6;
+  const int M = a.M, n_tiles = a.N >> 4, nts = min(NT, n_tiles - g * NT), id0 = g * NT * 16;
+  if (a.logits) {
+    for (int e = tid; e < nts * M * 16; e += nthr) {
+      const int lt = e / (M * 16), r = e - lt * M * 16;
+      a.logits[(long long)(r >> 4) * a.ld_logits + id0 + lt * 16 + (r & 15)] = Y[lt * ys + r];
+    }
+  }
+  for (int m = wave; a.amax_val && m < M; m += nw) {   // one wave per row, lane-strided candidates, then a butterfly
+    float best = NEG_INF;
+    int bi = -1;
+    for (int jc = lane; jc < nts * 16; jc += 64) {
+      const float v = Y[(jc >> 4) * ys + m * 16 + (jc & 15)];
+      if (bi < 0 || v > best) { best = v; bi = id0 + jc; }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const float ov = __shfl_xor(best, o);
+      const int oi = __shfl_xor(bi, o);
+      if (oi >= 0 && (bi < 0 || ov > best || (ov == best && oi < bi))) { best = ov; bi = oi; }
+    }
+    if (lane == 0) {
+      a.amax_val[(size_t)m * a.amax_stride + g] = best;
+      a.amax_idx[(size_t)m * a.amax_stride + g] = bi;
+    }
+  }
 }
 
 // Online-softmax merge (base 2) of a partial (m_c, l_c, o_c) into a running (m_r, l_r, o_r).

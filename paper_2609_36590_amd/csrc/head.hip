@@ -1,0 +1,389 @@
+// The LM head (vocabulary-wide linear layer with RMSNorm, logits and argmax): weights streamed once, a
+// wave per n-tile (16 tokens of the vocabulary) over all of K, activation rows staged in LDS as MFMA
+// B-operand slots.
+//
+//  * k_head_lds      rows that fit LDS whole (M <= 16)
+//  * k_head_chunked  up to 64 rows, staged in double-buffered chunks of K
+//
+// Both accumulate every logit as one MFMA chain in k order, so a row's logits are bit-identical however
+// many rows share the pass: verifying d drafts gives the same logits, row by row, as plain greedy
+// decoding (d = 0). Small vocabularies take the row kernel (rows.hip) for every row count instead.
+#include "device_common.h"
+
+#include <algorithm>
+
+namespace seedk {
+
+// RMSNorm scale of row m from its per-16-feature sums of squares. Lane partials (lane-strided,
+// pre-loaded in ssv when available) are combined by a fixed xor tree, so the value does not
+// depend on which wave computes it or on how many rows share the pass.
+__device__ __forceinline__ float wave_row_scale(const LinArgs& a, int m, const float* ssv, bool pre) {
+  const int lane = threadIdx.x & 63;
+  float s;
+  if (pre) {
+    s = ((ssv[0] + ssv[1]) + ssv[2]) + ssv[3];
+  } else {
+    s = 0.f;
+    for (int j = lane; j < a.nssq; j += 64) s += a.ssq[(size_t)m * a.nssq + j];
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  return rsqrtf(s / (float)a.K + a.eps);
+}
+
+__device__ __forceinline__ bool preload_row_ssq(const LinArgs& a, int m, float ssv[4]) {
+  const int lane = threadIdx.x & 63;
+  if (m >= a.M || a.nssq > 256) return false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int j = lane + 64 * i;
+    ssv[i] = j < a.nssq ? a.ssq[(size_t)m * a.nssq + j] : 0.f;
+  }
+  return true;
+}
+
+// A staged B-operand slot: 32 bytes of LDS holding one row's 8 values of k-group kg of k-tile kt
+// (rest = kt * 4 + kg), the two 16-byte halves of the packed activation slot side by side.
+struct Slot {
+  uint4 p0, p1;
+};
+__device__ __forceinline__ Slot load_slot(const void* X, int KT, bool frag, int row, int rest) {
+  const char* p = reinterpret_cast<const char*>(X) + ((size_t)(row >> 4) * KT + (rest >> 2)) * ACT_TILE +
+                  act_slot(frag, row & 15, rest & 3);
+  return Slot{*reinterpret_cast<const uint4*>(p), *reinterpret_cast<const uint4*>(p + act_plane(frag))};
+}
+__device__ __forceinline__ void store_slot(char* p, const Slot& v) {
+  reinterpret_cast<uint4*>(p)[0] = v.p0;
+  reinterpret_cast<uint4*>(p)[1] = v.p1;
+}
+template <typename T>
+__device__ __forceinline__ typename ET<T>::B lds_slot(const char* p) {
+  return ET<T>::join(reinterpret_cast<const uint4*>(p)[0], reinterpret_cast<const uint4*>(p)[1]);
+}
+
+__host__ __device__ inline size_t lds_x_bytes(int M, int nkt) { return (size_t)nkt * 4 * M * 32 + 32; }
+
+// ---------------------------------------------------------------------------------------------
+// M <= 16 rows (one MFMA tile): the workgroup (8 waves, one n-tile each) issues its first weight
+// tiles, then stages the activation rows into LDS: slot (kt, kg, r) = 32 bytes, the two planes of
+// x[r][32kt + 8kg .. +7], plus one zero slot for the token columns r >= M. Waves then stream weight
+// tiles with P in flight, reading their B operands from LDS.
+// ---------------------------------------------------------------------------------------------
+template <typename T>
+__global__ void __launch_bounds__(64 * HEAD_NT) k_head_lds(LinArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int P = 8;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int KT = a.K >> 5, n_tiles = a.N >> 4, M = a.M;
+  const int tl = lane & 15, kg = lane >> 4;
+  const int nt = blockIdx.x * HEAD_NT + wave;
+  const int nk = nt < n_tiles ? KT : 0;   // weight tiles this wave streams
+  const T* w0 = reinterpret_cast<const T*>(a.W) + (size_t)min(nt, n_tiles - 1) * KT * 512 + lane * 8;
+
+  // ---- weight prefetch ----
+  typename ET<T>::A wb[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (p < nk) wb[p] = ET<T>::load_nt(w0 + (size_t)p * 512);
+  float ssv[4] = {0.f, 0.f, 0.f, 0.f};
+  const bool pre = preload_row_ssq(a, wave, ssv);
+
+  // ---- stage X into LDS ----
+  const size_t zero_off = (size_t)KT * 4 * M * 32;
+  float* Y = reinterpret_cast<float*>(lds + lds_x_bytes(M, KT));   // [HEAD_NT][M][16], then the row scales
+  float* s_rs = Y + (size_t)HEAD_NT * M * 16;
+  {
+    // two batches of 2 slots per thread per round trip: both batches' loads are issued before
+    // either is written, so a workgroup whose rows take several batches (O at 5 rows, the LM head
+    // at more than 3) pays half the round trips. Loads are branch-free (slots past the end reload
+    // the last one and are not written) and none is issued after a wait: a load under a branch
+    // makes the compiler wait for every load in flight before each write, and a surplus load
+    // issued after the first wait would add a round trip to the one-batch case.
+    const int items = KT * 4 * M, bs = 2 * (int)blockDim.x;
+    Slot xa[2], xb[2];
+    auto ld = [&](Slot (&xv)[2], int q0) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int q = min(q0 + u * (int)blockDim.x + tid, items - 1);
+        xv[u] = load_slot(a.X, KT, false, q % M, q / M);
+      }
+    };
+    auto st = [&](const Slot (&xv)[2], int q0) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int q = q0 + u * (int)blockDim.x + tid;
+        if (q < items) store_slot(lds + (size_t)q * 32, xv[u]);
+      }
+    };
+    if (items <= bs) {   // one batch (both paths finish their loads before they merge)
+      ld(xa, 0);
+      st(xa, 0);
+    } else {
+      for (int q0 = 0; q0 < items; q0 += 2 * bs) {
+        ld(xa, q0);
+        ld(xb, q0 + bs);
+        st(xa, q0);
+        st(xb, q0 + bs);
+      }
+    }
+    if (tid < 2) *reinterpret_cast<float4*>(lds + zero_off + tid * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  __syncthreads();
+
+  // ---- stream ----
+  const bool live_col = tl < M;
+  const char* xa = lds + (live_col ? ((size_t)kg * M + tl) * 32 : zero_off);
+  const size_t xs = live_col ? (size_t)4 * M * 32 : 0;  // bytes per k-tile
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto consume = [&](int slot, int j) { ET<T>::mma(acc, wb[slot], lds_slot<T>(xa + j * xs)); };
+  int s0 = 0;
+  for (; s0 + 2 * P <= nk; s0 += P) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      consume(p, s0 + p);
+      wb[p] = ET<T>::load_nt(w0 + (size_t)(s0 + p + P) * 512);
+      // keep each refill next to its consumption (the scheduler would otherwise sink all refills
+      // below the last MFMA and drain the pipeline once per P tiles)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    if (s0 + p < nk) {
+      consume(p, s0 + p);
+      if (s0 + p + P < nk) wb[p] = ET<T>::load_nt(w0 + (size_t)(s0 + p + P) * 512);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (s0 + P + p < nk) consume(p, s0 + P + p);
+
+  // ---- RMSNorm row scales, epilogue ----
+  for (int m = wave; m < M; m += HEAD_NT) {
+    const float r = wave_row_scale(a, m, ssv, pre && m == wave);
+    if (lane == 0) s_rs[m] = r;
+  }
+  __syncthreads();
+  if (live_col) {
+    const float rs = s_rs[tl];
+    *reinterpret_cast<float4*>(Y + ((size_t)wave * M + tl) * 16 + 4 * kg) =
+        make_float4(acc[0] * rs, acc[1] * rs, acc[2] * rs, acc[3] * rs);
+  }
+  __syncthreads();
+  head_epilogue(a, blockIdx.x, HEAD_NT, Y, M * 16);
+}
+
+// ---------------------------------------------------------------------------------------------
+// LM head for 16 < M <= 64 rows (batched verification, draft trees of more than 16 nodes): the
+// activation rows of all M tokens do not fit LDS whole (4 bytes per element as MFMA B slots), so
+// they are staged in chunks of HEAD_CK k-tiles, double-buffered: the loads of chunk c+1 are issued
+// before chunk c is consumed and written to the other buffer after it. Each of the 8 waves
+// streams one n-tile over all of K in k order (KS = 1, as the narrow kernel does for any M), for TT
+// token tiles of 16 rows, so every row's logits are bit-identical to a pass of fewer rows. A
+// workgroup has HEAD_WIDE_NT = 16 waves (n-tiles), so the 40 staged rows of a batch-8 verification
+// are read by 594 workgroups instead of 1187 (the argmax partials are per 16-n-tile group; the
+// maximum over them is the same).
+// ---------------------------------------------------------------------------------------------
+constexpr int HEAD_CK = 8;   // k-tiles per staged chunk (= the weight ring depth)
+
+template <typename T, int TT, int NW>
+__global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ float s_rs[64];
+  constexpr int P = HEAD_CK;
+  constexpr int NTH = NW * 64;
+  constexpr int XI = (HEAD_CK * 4 * 16 * TT + NTH - 1) / NTH;   // staged items per thread and chunk
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int KT = a.K >> 5, n_tiles = a.N >> 4, M = a.M;
+  const int tl = lane & 15, kg = lane >> 4;
+  const int nt = blockIdx.x * NW + wave;
+  const T* w0 = reinterpret_cast<const T*>(a.W) + (size_t)(nt < n_tiles ? nt : 0) * KT * 512 + lane * 8;
+  const size_t chunk_bytes = (size_t)HEAD_CK * 4 * M * 32;
+  const size_t zero_off = 2 * chunk_bytes;
+  const int NC = (KT + HEAD_CK - 1) / HEAD_CK;
+
+  float ssv[4] = {0.f, 0.f, 0.f, 0.f};
+  const bool pre = preload_row_ssq(a, wave, ssv);
+
+  // chunk c's items q = (ktl*4 + kg)*M + r hold x[r][32(c*CK + ktl) + 8kg .. +7]; loaded branch-free
+  // (items past the chunk reload item 0 and are not written)
+  Slot xv[XI];
+  auto stage_load = [&](int c) {
+    const int nkc = min(HEAD_CK, KT - c * HEAD_CK), items = nkc * 4 * M;
+#pragma unroll
+    for (int u = 0; u < XI; ++u) {
+      const int q = u * NTH + tid, qc = q < items ? q : 0;
+      xv[u] = load_slot(a.X, KT, act_frag(M), qc % M, c * HEAD_CK * 4 + qc / M);
+    }
+  };
+  auto stage_store = [&](int c) {
+    const int nkc = min(HEAD_CK, KT - c * HEAD_CK), items = nkc * 4 * M;
+    char* buf = lds + (c & 1) * chunk_bytes;
+#pragma unroll
+    for (int u = 0; u < XI; ++u) {
+      const int q = u * NTH + tid;
+      if (q < items) store_slot(buf + (size_t)q * 32, xv[u]);
+    }
+  };
+
+  stage_load(0);
+  typename ET<T>::A wb[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) wb[p] = ET<T>::load_nt(w0 + (size_t)min(p, KT - 1) * 512);
+  stage_store(0);
+  if (tid < 2) *reinterpret_cast<float4*>(lds + zero_off + tid * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
+  __syncthreads();
+
+  f32x4 acc[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // every load below is issued unconditionally (the last chunk is reloaded past the end, weight
+  // tiles past K re-read the last one, neither is consumed): a load under a data-dependent branch
+  // makes the compiler's wait counts assume the path without it, and every refill would then wait
+  // for the whole ring
+  for (int c = 0; c < NC; ++c) {
+    stage_load(min(c + 1, NC - 1));
+    const char* buf = lds + (c & 1) * chunk_bytes;
+    const int nkc = min(HEAD_CK, KT - c * HEAD_CK);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      if (p < nkc) {
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          const int m = tt * 16 + tl;
+          const char* xb = m < M ? buf + ((size_t)(p * 4 + kg) * M + m) * 32 : lds + zero_off;
+          ET<T>::mma(acc[tt], wb[p], lds_slot<T>(xb));
+        }
+      }
+      const int nxt = c * HEAD_CK + p + P;
+      wb[p] = ET<T>::load_nt(w0 + (size_t)min(nxt, KT - 1) * 512);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (c + 1 < NC) stage_store(c + 1);
+    __syncthreads();
+  }
+
+  // lane (tl, kg) holds features 4kg..4kg+3 of token tt*16+tl: Y[wave][m][16] over the buffers
+  float* Y = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {
+    const int m = tt * 16 + tl;
+    if (m < M) {
+      float* dst = Y + ((size_t)wave * M + m) * 16 + 4 * kg;
+      dst[0] = acc[tt][0]; dst[1] = acc[tt][1]; dst[2] = acc[tt][2]; dst[3] = acc[tt][3];
+    }
+  }
+  for (int m = wave; m < M; m += NW) {
+    const float r = wave_row_scale(a, m, ssv, pre && m == wave);
+    if (lane == 0) s_rs[m] = r;
+  }
+  __syncthreads();
+  const int per = M * 16;
+  for (int e = tid; e < NW * per; e += blockDim.x) {
+    Y[e] *= s_rs[(e % per) >> 4];
+  }
+  __syncthreads();
+  head_epilogue(a, blockIdx.x, NW, Y, M * 16);
+}
+
+// Reduce per-n-group argmax partials of one row; lowest token id wins among equal maxima.
+__global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const int* idx, int stride, int n_parts,
+                                                         int* tok_out, int tok_stride) {
+  const int m = blockIdx.x, tid = threadIdx.x;
+  __shared__ float s_v[256];
+  __shared__ int s_i[256];
+  float best = NEG_INF;
+  int bi = -1;
+  for (int j = tid; j < n_parts; j += blockDim.x) {
+    const float v = val[(size_t)m * stride + j];
+    const int i = idx[(size_t)m * stride + j];
+    if (i >= 0 && (bi < 0 || v > best || (v == best && i < bi))) { best = v; bi = i; }
+  }
+  s_v[tid] = best;
+  s_i[tid] = bi;
+  __syncthreads();
+  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
+    if (tid < o) {
+      const float v = s_v[tid + o];
+      const int i = s_i[tid + o];
+      if (i >= 0 && (s_i[tid] < 0 || v > s_v[tid] || (v == s_v[tid] && i < s_i[tid]))) { s_v[tid] = v; s_i[tid] = i; }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) tok_out[m * tok_stride] = s_i[0] < 0 ? 0 : s_i[0];
+}
+
+// ---------------------------------------------------------------------------------------------
+// Launchers.
+// ---------------------------------------------------------------------------------------------
+static size_t g_lds_limit = 65536;   // dynamic LDS one workgroup may use (set by configure_kernels)
+
+static size_t head_lds_bytes(int M, int K) { return lds_x_bytes(M, K >> 5) + (size_t)(HEAD_NT * M + 1) * 16 * sizeof(float); }
+static size_t head_chunked_lds(int M) { return 2 * (size_t)HEAD_CK * 4 * M * 32 + 32; }
+
+// n-tiles per argmax partial (per workgroup): 8 where the rows fit LDS whole, else the chunked kernel's 16
+int head_group(int M, int N, int K) {
+  if (head_by_rows(N)) return ROWS_HEAD_NT;
+  return M <= 16 && head_lds_bytes(M, K) <= g_lds_limit ? HEAD_NT : HEAD_WIDE_NT;
+}
+
+template <typename T>
+static void launch_head(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
+  const int n_tiles = a.N >> 4, NT = head_group(a.M, a.N, a.K);
+  const dim3 grid((n_tiles + NT - 1) / NT), block(64 * NT);
+  if (NT == HEAD_NT) {
+    launch(k_head_lds<T>, grid, block, head_lds_bytes(a.M, a.K), s, ev, a);
+    return;
+  }
+  const size_t lds = head_chunked_lds(a.M);
+  switch ((a.M + 15) / 16) {
+    case 1: launch(k_linear_head_chunked<T, 1, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
+    case 2: launch(k_linear_head_chunked<T, 2, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
+    case 3: launch(k_linear_head_chunked<T, 3, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
+    default: launch(k_linear_head_chunked<T, 4, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
+  }
+}
+
+template <typename T>
+void launch_linear(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev) {
+  if (a.M > 64) launch_linear_wide<T>(a, epilogue, s, ev);
+  else if (epilogue == EPI_HEAD && !head_by_rows(a.N)) launch_head<T>(a, s, ev);
+  else launch_linear_rows<T>(a, epilogue, s, ev);
+}
+
+void launch_argmax_finalize(const float* val, const int* idx, int stride, int n_parts, int M, int* tok_out,
+                            int tok_stride, hipStream_t s) {
+  hipLaunchKernelGGL(k_argmax_finalize, dim3(M), dim3(256), 0, s, val, idx, stride, n_parts, tok_out, tok_stride);
+}
+
+// Dynamic LDS available to one workgroup: the device's per-block limit, raised to the opt-in limit
+// when every kernel accepted it (failed opt-ins are cleared and ignored).
+template <typename T>
+static bool allow_big_lds(int bytes) {
+  const void* fns[] = {reinterpret_cast<const void*>(&k_head_lds<T>),
+                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 1, HEAD_WIDE_NT>),
+                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 2, HEAD_WIDE_NT>),
+                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 3, HEAD_WIDE_NT>),
+                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 4, HEAD_WIDE_NT>)};
+  bool ok = true;
+  for (const void* f : fns) ok &= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+  return ok && rows_allow_lds<T>();
+}
+
+hipError_t configure_kernels(int bf16) {
+  int dev = 0, base = 0, optin = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
+  if (hipDeviceGetAttribute(&base, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && base > 0)
+    g_lds_limit = (size_t)base;
+  if (hipDeviceGetAttribute(&optin, hipDeviceAttributeSharedMemPerBlockOptin, dev) == hipSuccess &&
+      (size_t)optin > g_lds_limit) {
+    if (bf16 ? allow_big_lds<uint16_t>(optin) : allow_big_lds<float>(optin)) g_lds_limit = (size_t)optin;
+  }
+  (void)hipGetLastError();
+  return hipSuccess;
+}
+
+template void launch_linear<uint16_t>(const LinArgs&, int, hipStream_t, const LaunchEvents*);
+template void launch_linear<float>(const LinArgs&, int, hipStream_t, const LaunchEvents*);
+
+}  // namespace seedk

@@ -23,29 +23,32 @@ namespace seedk {
 
 // Packed activations. The inputs of the linear kernels (x * gain, attention output, SwiGLU output;
 // M rows x K features) are stored by their producers as MFMA B operands: tiles of 16 rows x 32
-// features, tile (mt, kt) at byte offset (mt * (K/32) + kt) * ACT_TILE. A row of a tile is one 128-byte
-// line: two planes of four 16-byte slots, slot kg of plane p for features 8kg .. 8kg+7: bf16 models
-// keep the 8 values' bf16 hi halves in plane 0 and their lo halves in plane 1, fp32 models values
-// 0..3 and 4..7. Either way the slot pair (row, kg) is one lane's operand of a 16x16x32 contraction; a
-// pass of one row reads whole lines, and a full tile is 2 KB without gaps.
-constexpr int ACT_TILE = 2048, ACT_ROW = 128, ACT_PLANE = 64;
+// features, tile (mt, kt) at byte offset (mt * (K/32) + kt) * ACT_TILE. Row r of a tile has two planes of
+// four 16-byte slots, slot kg of plane p for features 8kg .. 8kg+7: bf16 models keep the 8 values' bf16
+// hi halves in plane 0 and their lo halves in plane 1, fp32 models values 0..3 and 4..7. Either way the
+// slots (r, kg) of both planes are one lane's operand of a 16x16x32 contraction. Passes of at most 16 rows
+// keep a row's slots in one 128-byte line (one row reads whole lines: 4 draft steps 998 us, 1033 in
+// operand order); passes of more rows keep them in operand order, so that a plane is one wave's 1 KB
+// load without gaps (8 x 5 rows through 4 layers: 655 us, 695 as lines).
+constexpr int ACT_TILE = 2048;
+__host__ __device__ inline bool act_frag(int M) { return M > 16; }
+__host__ __device__ inline int act_plane(bool frag) { return frag ? 1024 : 64; }
+__host__ __device__ inline int act_slot(bool frag, int row16, int kg) {
+  return frag ? kg * 256 + row16 * 16 : row16 * 128 + kg * 16;
+}
 
-enum Prologue { PRO_NORM = 0, PRO_PLAIN = 1 };
 enum Epilogue { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
 
-// Arguments of the weight-streaming linear kernels (MFMA skinny GEMM and VALU GEMV).
+// Arguments of the linear kernels.
 struct LinArgs {
   const void* W;          // packed weights
   int N, K;               // output features, input features
   int M;                  // activation rows in this pass
-  int NT, KS;             // n-tiles per workgroup pass, K-splits per n-tile
-  int S;                  // the KS partial sums are added in S consecutive groups of KS/S, group
-                          // by group in order (k_linear_lds: S == 1)
-  int NJ;                 // LDS kernel: passes per workgroup (n-group blockIdx.x + j*gridDim.x)
+  int KS;                 // K-ranges, added in order (set by the launchers, from the weight shape)
   // input
-  const void* X;          // packed activations [M][K]; PRO_NORM: x*g formed by the producer
-  const float* rs;        // LIN_WIDE with PRO_NORM: RMSNorm row scales [M]
-  const float* ssq;       // PRO_NORM: [M][nssq] partial sums of squares of x (per 16 features)
+  const void* X;          // packed activations [M][K]; of the RMSNormed layers x*g, formed by the producer
+  const float* rs;        // passes of more than 64 rows: RMSNorm row scales [M]
+  const float* ssq;       // RMSNormed layers: [M][nssq] partial sums of squares of x (per 16 features)
   int nssq;
   float eps;
   // EPI_RESID: h[m][n] += y, xg[m][n] = h[m][n] * gain_next[n] (input of the next RMSNorm
@@ -54,7 +57,7 @@ struct LinArgs {
   void* xg;               // packed
   const float* gain_next;
   float* ssq_out;
-  float* rs_out;          // LIN_WIDE: the updated rows' RMSNorm scales [M] (in place of ssq_out)
+  float* rs_out;          // passes of more than 64 rows: the updated rows' RMSNorm scales [M] (in place of ssq_out)
   // EPI_SWIGLU: act[m][f] = silu(gate) * up, f = nt*8 + c
   void* act;              // packed
   // EPI_QKV
@@ -71,8 +74,7 @@ struct LinArgs {
   float* amax_val;        // per-workgroup argmax partials [M][amax_stride]
   int* amax_idx;
   int amax_stride;
-  float* part;            // LIN_SPLITK: k-range partials [KS][M][N]
-  float* part_rs;         // LIN_SPLITK with the RMSNorm prologue: row scales [M]
+  float* part;            // passes of more than 64 rows: k-range partials [KS][M][N]
 };
 
 // Arguments of the split-KV paged attention kernel and its combine kernel.
@@ -97,6 +99,7 @@ struct AttnArgs {
   // one-launch pass attention (launch_attention_prefill, set by attention_pass_plan): 16 * pf_qt query
   // vectors per wave, and positions split over pf_split workgroups per row-block, whose partials [pf_split][R][n_heads] (o: head_dim floats, then m and l) are
   // merged by a second kernel when pf_split > 1
+  int frag;               // layout of out: act_frag(rows of the pass)
   int pf_qt, pf_split;
   float* pf_o;
   float* pf_ml;
@@ -181,14 +184,16 @@ struct DevState {
   int stamp_cap;
 };
 
-// Kernel choice for a linear launch: weights streamed with the activation rows staged in LDS as
-// MFMA fragments (M <= 16 and the rows fit), split-K across workgroups for up to 64 rows, the
-// compute-bound tiled GEMM (LIN_WIDE) for wider passes, else activation fragments from global memory.
-enum LinearKind { LIN_LDS = 0, LIN_GLOBAL = 1, LIN_SPLITK = 2, LIN_WIDE = 3 };
-constexpr int LDS_MAX_PASSES = 8;   // n-tile passes (NJ) of one k_linear_lds workgroup
-constexpr int HEAD_WIDE_NT = 16;    // n-tiles (waves) per workgroup of the LM head for 17..64 rows
+// n-tiles per workgroup of the LM head's kernels (one argmax partial each): rows that fit LDS whole, rows
+// staged in chunks, and small vocabularies.
+constexpr int HEAD_NT = 8, HEAD_WIDE_NT = 16, ROWS_HEAD_NT = 2;
+// Small vocabularies split K over waves like the other projections: at 1024 tokens the head's kernels
+// would have 8 workgroups, each wave a chain over all of K (5 rows 19 us, 40 rows 55).
+__host__ __device__ inline bool head_by_rows(int N) { return N < 32768; }
+int head_group(int M, int N, int K);   // n-tiles per argmax partial of a head launch
 constexpr int PF_SPLIT_MAX = 3;     // position splits of the one-launch pass attention,
 constexpr int PF_SPLIT_ROWS = 1024;  // of passes of at most this many rows
+constexpr int ROWS_KS_MAX = 16;     // k-ranges of a decode pass's projection (waves of a workgroup)
 constexpr int WIDE_SPLIT_MAX = 4;   // k-ranges of a split wide pass (its partials: WIDE_SPLIT_MAX x rows x N floats)
 
 // Optional timing events stamped by the launches themselves (hipExtLaunchKernel): `start` at the
@@ -197,12 +202,16 @@ struct LaunchEvents {
   hipEvent_t start, stop;
 };
 
+// Linear layer with its epilogue (inputs of QKV, gate/up and the head are RMSNormed): passes of at most
+// 64 rows stream the weights (rows.hip, head.hip), wider ones are compute-bound (wide.hip).
 template <typename T>
-void launch_linear(const LinArgs& a, int prologue, int epilogue, int kind, hipStream_t s,
-                   const LaunchEvents* ev = nullptr);
-// LIN_WIDE: passes of more than 64 rows (wide.hip).
+void launch_linear(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev = nullptr);
+template <typename T>
+void launch_linear_rows(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev);
 template <typename T>
 void launch_linear_wide(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev);
+template <typename T>
+bool rows_allow_lds();
 // Attention partials per group of span positions (the final output when the rows see one group).
 template <typename T>
 void launch_attention(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
@@ -278,10 +287,4 @@ void launch_fill_u32(void* dst, unsigned value, long long n_words, hipStream_t s
 
 // allow the linear kernels to use more than 64 KB of LDS (once per process and dtype)
 hipError_t configure_kernels(int bf16);
-// dynamic LDS bytes one linear workgroup may use (valid after configure_kernels)
-size_t linear_lds_limit();
-
-// dynamic LDS bytes needed by launch_linear for a given shape
-size_t linear_lds_bytes(int M, int K, int NT, int KS, int S, int NJ, int kind);
-
 }  // namespace seedk

@@ -13,7 +13,8 @@ namespace seedk {
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256) k_setup(SetupArgs a, PassSegs sg) {
-  const int m = blockIdx.x;
+  // workgroup b runs on XCD b mod 8: 8 neighbouring rows, whose slots share lines in operand order, on one
+  const int bx = blockIdx.x, m = (bx & ~63) + 64 <= a.M ? (bx & ~63) + (bx & 7) * 8 + ((bx >> 3) & 7) : bx;
   __shared__ int s_tok, s_pos, s_seq, s_slot;
   if (a.stamp && m == 0 && threadIdx.x == 0) {
     const long long now = (long long)__builtin_amdgcn_s_memrealtime();
@@ -92,8 +93,8 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs a, PassSegs sg) {
     float* hp = a.h + (size_t)m * a.H + k0;
     reinterpret_cast<float4*>(hp)[0] = make_float4(v[0], v[1], v[2], v[3]);
     reinterpret_cast<float4*>(hp)[1] = make_float4(v[4], v[5], v[6], v[7]);
-    act_put4<T>(a.xg, KT, m, k0, make_float4(v[0] * g[0], v[1] * g[1], v[2] * g[2], v[3] * g[3]));
-    act_put4<T>(a.xg, KT, m, k0 + 4, make_float4(v[4] * g[4], v[5] * g[5], v[6] * g[6], v[7] * g[7]));
+    act_put4<T>(a.xg, KT, act_frag(a.M), m, k0, make_float4(v[0] * g[0], v[1] * g[1], v[2] * g[2], v[3] * g[3]));
+    act_put4<T>(a.xg, KT, act_frag(a.M), m, k0 + 4, make_float4(v[4] * g[4], v[5] * g[5], v[6] * g[6], v[7] * g[7]));
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += v[i] * v[i];

@@ -71,7 +71,7 @@ struct Plan {
   size_t o_pf_o, o_pf_ml, o_wide_part, o_h, o_xg, o_ssq, o_rs, o_q, o_attn, o_act, o_part, o_row_seq, o_row_pos, o_row_slot, o_row_blk, o_row_rope, o_amax_val,
       o_amax_idx, o_vtok;
   size_t o_t, o_len, o_limit, o_active, o_nacc, o_bonus, o_rounds, o_counters, o_drafts, o_tokens,
-      o_trace, o_log, o_bt, o_nll, o_splitk, o_splitk_rs, o_tree, o_tree_out, o_scratch, o_stamp, ws_total;
+      o_trace, o_log, o_bt, o_nll, o_tree, o_tree_out, o_scratch, o_stamp, ws_total;
   // dynamic drafting: top-k partials, the round's drafting state, one step's drafter logits
   size_t o_topk, o_tdraft, o_dlog;
 };
@@ -99,8 +99,6 @@ seed_status validate(const seed_config* c) {
   if (!(c->rope_base > 0.f) || !(c->rms_eps >= 0.f)) return fail(SEED_ERR_ARG, "rope_base must be > 0 and rms_eps >= 0");
   return SEED_OK;
 }
-
-void tile_policy(int N, int K, bool head, int& NT, int& KS, int& S, int& NJ);
 
 Plan make_plan(const seed_config& c) {
   Plan p;
@@ -180,22 +178,11 @@ Plan make_plan(const seed_config& c) {
   p.o_nll = take((size_t)c.max_ctx * 4);
   p.o_tree = take((3 * MAX_ROWS + 1) * 4);
   p.o_tree_out = take((2 + MAX_ROWS + 2) * 4);
-  {
-    // k-range partials of the split-K path (passes of more than 16 rows): KS x rows x N floats
-    size_t ksn = 0;
-    const int shapes[4][2] = {{p.QD + 2 * p.KVD, p.H}, {p.H, p.QD}, {2 * p.F, p.H}, {p.H, p.F}};
-    for (const auto& sh : shapes) {
-      int NT, KS, S, NJ;
-      tile_policy(sh[0], sh[1], false, NT, KS, S, NJ);
-      ksn = std::max(ksn, (size_t)KS * sh[0]);
-    }
-    p.o_splitk = take(ksn * MAX_ROWS * 4);   // only passes of at most MAX_ROWS rows split K
-    p.o_splitk_rs = take((size_t)MAX_ROWS * 4);
-  }
   const size_t split_rows = (size_t)PF_SPLIT_MAX * std::min(p.max_rows, PF_SPLIT_ROWS);
   p.o_pf_o = take(split_rows * p.QD * 4);   // split pass attention partials
   p.o_pf_ml = take(split_rows * p.NQ * 2 * 4);
-  p.o_wide_part = take((size_t)seedk::WIDE_SPLIT_MAX * p.max_rows * p.H * 4);   // split wide passes (N = H)
+  // k-range partials of the residual projections (N = H): wide passes, and decode passes of 17..64 rows
+  p.o_wide_part = take(std::max((size_t)seedk::WIDE_SPLIT_MAX * p.max_rows, (size_t)seedk::ROWS_KS_MAX * MAX_ROWS) * p.H * 4);
   p.o_topk = take((size_t)TOPK_PARTS * (2 * TOPK_MAX + 2) * 4);
   p.o_tdraft = take((size_t)TREE_MAX_STEPS * (TOPK_MAX + 2) * 4 + 16);
   p.o_dlog = take((size_t)p.V * 4);
@@ -317,32 +304,6 @@ void timed(seed_ctx* c, int phase, int op, bool capturing, F&& fn) {
 // ---------------------------------------------------------------------------------------------
 // launch helpers
 // ---------------------------------------------------------------------------------------------
-// Waves per workgroup and how they split the work; a function of the weight shape only, so a
-// row's reduction order never depends on how many rows share the pass (measured on MI355X):
-//   head (N = vocab): one n-tile per wave over the full K, 8 n-tiles per workgroup.
-//   N >= 4096 (QKV, gate/up): 8 K-splits, 2 n-tiles per workgroup pass, and as many passes per
-//     workgroup as keep the grid near 200 workgroups (the LDS kernel stages the activations once
-//     per workgroup).
-//   smaller N (O, down): one n-tile per workgroup, K split in ranges of about 16 k-tiles (<= 16).
-void tile_policy(int N, int K, bool head, int& NT, int& KS, int& S, int& NJ) {
-  const int KT = K / 32, n_tiles = N / 16;
-  S = 1;
-  NJ = 1;
-  if (head) {
-    KS = 1;
-    NT = 8;
-    return;
-  }
-  if (n_tiles >= 256) {
-    KS = std::min(8, KT);
-    NT = 2;
-    NJ = std::min(LDS_MAX_PASSES, std::max(1, (cdiv(n_tiles, NT) + 100) / 200));
-    return;
-  }
-  KS = std::min(16, std::max(1, KT / 16));
-  NT = 1;
-}
-
 DevState dev_state(seed_ctx* c) {
   const Plan& p = c->p;
   DevState st;
@@ -393,38 +354,13 @@ LinArgs lin_base(seed_ctx* c, int M) {
   a.amax_val = c->ws<float>(p.o_amax_val);
   a.amax_idx = c->ws<int>(p.o_amax_idx);
   a.amax_stride = p.V / 16;
-  a.part = c->ws<float>(p.o_splitk);
-  a.part_rs = c->ws<float>(p.o_splitk_rs);
+  a.part = c->ws<float>(p.o_wide_part);
   return a;
 }
 
-// Kernel for one linear launch: activation rows staged in LDS when they fit (M <= 16); passes of
-// more rows split K across workgroups (each stages its k-range only) and add the range partials
-// in a second kernel; otherwise activation fragments are read from global memory.
-// Measured on MI355X (4B-scale shapes, M = 1..16): staging the rows in LDS wins while a workgroup
-// stages at most 9 x 4096 activations; beyond that the split-K kernel (each workgroup stages one
-// k-range) is faster than both the LDS kernel and the global-fragment kernel.
-int linear_kind(const LinArgs& a, bool head) {
-  if (a.M > MAX_ROWS) return LIN_WIDE;   // prefill / drafting-objective passes: compute-bound tiles
-  if (a.M <= 16 && (head || (long long)a.M * a.K <= 9 * 4096) &&
-      linear_lds_bytes(a.M, a.K, a.NT, a.KS, a.S, a.NJ, LIN_LDS) <= linear_lds_limit())
-    return LIN_LDS;
-  if (!head && linear_lds_bytes(a.M, a.K, a.NT, a.KS, a.S, a.NJ, LIN_SPLITK) <= linear_lds_limit())
-    return LIN_SPLITK;
-  return LIN_GLOBAL;
-}
-
-// n-tiles per workgroup of the LM head: 8, or HEAD_WIDE_NT for the 17..64-row passes (the chunked
-// kernel), where each workgroup stages every row; the argmax partials are per such group
-int head_nt(int M) { return (M > 16 && M <= MAX_ROWS) ? HEAD_WIDE_NT : 8; }
-
 template <typename T>
-void linear(seed_ctx* c, LinArgs a, int pro, int epi, int phase, int op, bool cap) {
-  tile_policy(a.N, a.K, epi == EPI_HEAD, a.NT, a.KS, a.S, a.NJ);
-  if (epi == EPI_HEAD) a.NT = head_nt(a.M);
-  const int kind = linear_kind(a, epi == EPI_HEAD);
-  if (kind == LIN_WIDE) a.part = c->ws<float>(c->p.o_wide_part);
-  timed(c, phase, op, cap, [&](const LaunchEvents* ev) { launch_linear<T>(a, pro, epi, kind, c->s, ev); });
+void linear(seed_ctx* c, const LinArgs& a, int epi, int phase, int op, bool cap) {
+  timed(c, phase, op, cap, [&](const LaunchEvents* ev) { launch_linear<T>(a, epi, c->s, ev); });
 }
 
 // The block-causal decoder pass of the speculative drafting objective: its keys/values go to a
@@ -452,7 +388,7 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
     // QKV + RoPE + KV write
     a.W = c->W + p.w_qkv[li]; a.N = p.QD + 2 * p.KVD; a.K = p.H;
     a.X = c->ws<char>(p.o_xg);
-    linear<T>(c, a, PRO_NORM, EPI_QKV, phase, SEED_OP_QKV, cap);
+    linear<T>(c, a, EPI_QKV, phase, SEED_OP_QKV, cap);
     // attention
     AttnArgs at;
     std::memset(&at, 0, sizeof(at));
@@ -479,6 +415,7 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
     at.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)p.HD));
     at.part = c->ws<float>(p.o_part);
     at.out = c->ws<char>(p.o_attn);
+    at.frag = act_frag(M);
     at.pf_o = c->ws<float>(p.o_pf_o);
     at.pf_ml = c->ws<float>(p.o_pf_ml);
     // wide passes: one launch over all of the pass's rows, written directly. Otherwise group partials and
@@ -508,18 +445,18 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
     a = lin_base(c, M);
     a.W = c->W + p.w_o[li]; a.N = p.H; a.K = p.QD;
     a.X = c->ws<char>(p.o_attn); a.gain_next = c->wf(p.w_mlp_norm[li]);
-    linear<T>(c, a, PRO_PLAIN, EPI_RESID, phase, SEED_OP_O, cap);
+    linear<T>(c, a, EPI_RESID, phase, SEED_OP_O, cap);
     // gate/up + SwiGLU
     a = lin_base(c, M);
     a.W = c->W + p.w_gu[li]; a.N = 2 * p.F; a.K = p.H;
     a.X = c->ws<char>(p.o_xg);
-    linear<T>(c, a, PRO_NORM, EPI_SWIGLU, phase, SEED_OP_GATEUP, cap);
+    linear<T>(c, a, EPI_SWIGLU, phase, SEED_OP_GATEUP, cap);
     // down + residual
     a = lin_base(c, M);
     a.W = c->W + p.w_down[li]; a.N = p.H; a.K = p.F;
     a.X = c->ws<char>(p.o_act);
     a.gain_next = c->wf(li + 1 < p.L ? p.w_attn_norm[li + 1] : p.w_final_norm);
-    linear<T>(c, a, PRO_PLAIN, EPI_RESID, phase, SEED_OP_DOWN, cap);
+    linear<T>(c, a, EPI_RESID, phase, SEED_OP_DOWN, cap);
   }
 }
 
@@ -532,8 +469,8 @@ void run_head(seed_ctx* c, int M, int* tok_out, int tok_stride, float* logits, l
   a.X = c->ws<char>(p.o_xg);
   a.logits = logits; a.ld_logits = ld;
   if (!tok_out) a.amax_val = nullptr, a.amax_idx = nullptr;   // logits only: no argmax partials
-  linear<T>(c, a, PRO_NORM, EPI_HEAD, phase, SEED_OP_HEAD, cap);
-  const int parts = cdiv(p.V / 16, head_nt(M));   // one argmax partial per n-group
+  linear<T>(c, a, EPI_HEAD, phase, SEED_OP_HEAD, cap);
+  const int parts = cdiv(p.V / 16, head_group(M, p.V, p.H));   // one argmax partial per n-group
   if (!tok_out) return;   // the caller ranks the logits itself (dynamic drafting)
   timed(c, phase, SEED_OP_HEAD_ARGMAX, cap, [&](const LaunchEvents*) {
     launch_argmax_finalize(a.amax_val, a.amax_idx, a.amax_stride, parts, M, tok_out, tok_stride, c->s);

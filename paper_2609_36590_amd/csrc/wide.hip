@@ -38,7 +38,7 @@ template <typename T, int EPI, int NI>
 __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
   constexpr int MJ = WIDE_MJ;
   constexpr int WN = 4 * NI;          // n-tiles per workgroup
-  constexpr int XU = MJ / 2;          // half tiles each wave fetches per k-tile (2 MJ / 4 waves)
+  constexpr int XU = MJ / 2;          // fragments each wave fetches per k-tile (2 planes x MJ / 4 waves)
   constexpr int SLOT = 2 * MJ * 1024;   // bytes of one LDS slot (a k-tile's activations)
   constexpr int ACT_IMG = EPI == EPI_SWIGLU ? MJ * NI * ACT_TILE : 0;   // the workgroup's packed outputs
   __shared__ __attribute__((aligned(16))) char lds[2 * SLOT > ACT_IMG ? 2 * SLOT : ACT_IMG];
@@ -62,23 +62,15 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
 #pragma unroll
   for (int i = 0; i < NI; ++i)
     wp[i] = reinterpret_cast<const T*>(a.W) + ((size_t)min(nt0 + i, n_tiles - 1) * KTF + kt0) * 512 + lane * 8;
-  // A wave's load covers 8 rows' whole lines (half a tile, 1 KB without gaps: fragment-shaped loads of 16
-  // half lines cost the gate/up GEMM 12%). In LDS a tile is its two planes in operand order, 16 rows
-  // per k-group, with row r of k-group kg of plane p at place r ^ (4p + kg): the 8 lanes that
-  // write one line then fall on different banks, and a fragment read still covers each k-group's 256
-  // bytes whole.
   const char* xp[XU];
   char* xl[XU];
 #pragma unroll
   for (int u = 0; u < XU; ++u) {
-    const int f = u * 4 + wave, c = lane & 7;   // half tile: token tile f / 2, rows 8 (f % 2) ..; line chunk c = 4p + kg
+    const int f = u * 4 + wave;   // fragment: token tile f / 2, plane f % 2
     xp[u] = reinterpret_cast<const char*>(a.X) + ((size_t)min(mt * MJ + (f >> 1), m_tiles - 1) * KTF + kt0) * ACT_TILE +
             (f & 1) * 1024 + lane * 16;
-    xl[u] = lds + (f >> 1) * ACT_TILE + c * 256 + (((f & 1) * 8 + (lane >> 3)) ^ c) * 16;
+    xl[u] = lds + f * 1024 + lane * 16;
   }
-  const char* br[2];
-#pragma unroll
-  for (int p = 0; p < 2; ++p) br[p] = lds + (4 * p + kg) * 256 + (tl ^ (4 * p + kg)) * 16;
   typedef typename ET<T>::A WA;
   WA w0[NI], w1[NI];
   u32x4 x0[XU], x1[XU], b0[MJ][2], b1[MJ][2];
@@ -106,7 +98,7 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
     for (int j = 0; j < MJ; ++j)
 #pragma unroll
       for (int p = 0; p < 2; ++p)
-        bf[j][p] = *reinterpret_cast<const u32x4*>(br[p] + slot * SLOT + j * ACT_TILE);
+        bf[j][p] = *reinterpret_cast<const u32x4*>(lds + slot * SLOT + (j * 2 + p) * 1024 + lane * 16);
   };
   // k-tile t: operands in w and bf; x holds k-tile t + 2's activations, slot p = t & 1 is free (every
   // wave read it before the last barrier) and slot p ^ 1 holds k-tile t + 1's
@@ -211,7 +203,8 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
             // both lanes of a pair hold the 4 values: each writes one plane of them. The workgroup's
             // 32 NI features are NI whole k-tiles of the output, assembled in LDS and copied out below
             const int k = (wave * NI + i) * 8 + c4;
-            ET<T>::put4_plane(lds + (j * NI + (k >> 5)) * ACT_TILE + tl * ACT_ROW, k, make_float4(v[0], v[1], v[2], v[3]), hf);
+            ET<T>::put4_plane(lds + (j * NI + (k >> 5)) * ACT_TILE + act_slot(true, tl, (k >> 3) & 3), act_plane(true), k,
+                              make_float4(v[0], v[1], v[2], v[3]), hf);
           } else {   // EPI_QKV
             const int HD = a.head_dim, half = HD >> 1;
             int sec, head, jt;
@@ -267,26 +260,28 @@ __global__ void __launch_bounds__(256, 2) k_linear_wide(LinArgs a) {
 }
 
 // Residual update of a wide pass: the k-range partials added in k-range order from 0, h += y, the
-// packed x * gain of the next norm's consumer and that norm's row scale. A wave takes a whole row (so
-// that the row's sum of squares needs no other kernel); a workgroup 4 rows of one token tile, the 4
-// workgroups of a token tile on one XCD.
+// packed x * gain of the next norm's consumer and that norm's row scale. A workgroup takes 4 whole rows (so
+// that their sums of squares need no other kernel), each wave a quarter of the features, 16 lanes to a
+// row (4 rows' slots side by side); the 4 workgroups of a token tile are on one XCD (their slots share
+// lines). Bound by memory: 12 us for 1024 rows x 2560 (52 MB).
 template <typename T>
 __global__ void __launch_bounds__(256) k_wide_resid(LinArgs a) {
+  __shared__ float s_ss[4][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b = blockIdx.x, idx = b >> 3;
-  const int m = ((idx >> 2) * 8 + (b & 7)) * 16 + (idx & 3) * 4 + wave;
-  if (m >= a.M) return;
+  const int b = blockIdx.x, idx = b >> 3, rr = lane >> 4;
+  const int m = ((idx >> 2) * 8 + (b & 7)) * 16 + (idx & 3) * 4 + rr, mc = min(m, a.M - 1);   // rows past the pass: never stored
   const int N = a.N, S = a.KS;
   const size_t stride = (size_t)a.M * N;
-  const float* pp = a.part + (size_t)m * N;
-  float* hp = a.h + (size_t)m * N;
+  const float* pp = a.part + (size_t)mc * N;
+  float* hp = a.h + (size_t)mc * N;
   float ss = 0.f;
-  constexpr int U = 4;   // 256-feature steps in flight
-  for (int f0 = 0; f0 < N; f0 += 256 * U) {
+  constexpr int U = 5;   // 64-feature steps in flight
+  const int steps = (N + 63) / 64, w0 = wave * steps / 4, w1 = (wave + 1) * steps / 4;
+  for (int t0 = w0; t0 < w1; t0 += U) {
     float4 v[U][WIDE_SPLIT_MAX], hv[U], gv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int f = min(f0 + u * 256 + lane * 4, N - 4);   // steps past the row re-read its end, never stored
+      const int f = min((t0 + u) * 64 + (lane & 15) * 4, N - 4);   // steps past the row re-read its end, never stored
 #pragma unroll
       for (int k = 0; k < WIDE_SPLIT_MAX; ++k)
         if (k < S) v[u][k] = *reinterpret_cast<const float4*>(pp + k * stride + f);
@@ -295,22 +290,25 @@ __global__ void __launch_bounds__(256) k_wide_resid(LinArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int f = f0 + u * 256 + lane * 4;
+      const int f = (t0 + u) * 64 + (lane & 15) * 4;
       float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int k = 0; k < WIDE_SPLIT_MAX; ++k)
         if (k < S) y.x += v[u][k].x, y.y += v[u][k].y, y.z += v[u][k].z, y.w += v[u][k].w;
       const float4 h = make_float4(hv[u].x + y.x, hv[u].y + y.y, hv[u].z + y.z, hv[u].w + y.w);
-      if (f < N) {
+      if (t0 + u < w1 && f < N && m < a.M) {
         *reinterpret_cast<float4*>(hp + f) = h;
-        act_put4<T>(a.xg, N >> 5, m, f, make_float4(h.x * gv[u].x, h.y * gv[u].y, h.z * gv[u].z, h.w * gv[u].w));
+        act_put4<T>(a.xg, N >> 5, true, m, f, make_float4(h.x * gv[u].x, h.y * gv[u].y, h.z * gv[u].z, h.w * gv[u].w));
         ss += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
       }
     }
   }
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
-  if (lane == 0) a.rs_out[m] = rsqrtf(ss / (float)N + a.eps);
+  for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
+  if ((lane & 15) == 0) s_ss[wave][rr] = ss;
+  __syncthreads();
+  if (wave == 0 && (lane & 15) == 0 && m < a.M)
+    a.rs_out[m] = rsqrtf((((s_ss[0][rr] + s_ss[1][rr]) + s_ss[2][rr]) + s_ss[3][rr]) / (float)N + a.eps);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,0 +1,50 @@
+"""The linear kernels of decode passes (rows.hip, head.hip) at the edges of their tiles, against the oracle:
+row counts around each token tile up to 64; features that leave n-tiles of a workgroup empty; K of one
+k-tile, of odd numbers of them, and long enough that its ranges go to several workgroups (an odd number
+of ranges among them); the head of small vocabularies and of ones from 32768 tokens on (rows staged
+whole, and in chunks). Every verification's logits against the full forward of prompt and drafts.
+Tolerances are those of the logits everywhere: 1e-4 fp32, 2e-2 bf16.
+"""
+import numpy as np
+import pytest
+
+from gpu_common import decoder, oracle_model, say
+from oracle import model as om
+from paper_2609_36590_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.C1_TINY.replace(n_layers=2, n_dec_layers=1)
+SHAPES = {
+    "one-k-tile": dict(hidden=32, n_heads=1, n_kv_heads=1, head_dim=64, ffn=32, vocab=16),
+    # down: 145 k-tiles in 9 ranges; gate/up: 580 n-tiles
+    "long-k": dict(hidden=96, n_heads=3, n_kv_heads=1, head_dim=64, ffn=4640, vocab=592),
+    # QKV: 272 n-tiles of 9 k-tiles, O: 128 k-tiles; a head of 2049 n-tiles
+    "heads": dict(hidden=288, n_heads=32, n_kv_heads=1, head_dim=128, ffn=8192, vocab=32784),
+}
+ROWS = ((1, 0), (1, 4), (1, 15), (17, 0), (8, 3), (11, 2), (12, 3), (7, 6), (16, 3))   # sequences, drafts
+
+
+@pytest.mark.parametrize("dtype,tol", [(synth.F32, 1e-4), (synth.BF16, 2e-2)], ids=["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_verification_rows(shape, dtype, tol):
+    cfg = BASE.replace(name="rows-" + shape, dtype=dtype, **SHAPES[shape])
+    w = synth.make_weights(cfg, seed=6)
+    m = oracle_model(cfg, w)
+    g = np.random.default_rng(8)
+    for batch, k in ROWS:
+        prompts = [g.integers(0, cfg.vocab, 2 + b % 5).astype(np.int32) for b in range(batch)]
+        drafts = g.integers(0, cfg.vocab, (batch, k)).astype(np.int32)
+        dec = decoder(cfg, w, max_batch=batch, max_ctx=32, max_draft=k)
+        try:
+            say(f"[gpu] rows {shape} {dtype} {batch} x {k + 1}")
+            dec.prefill(prompts)
+            _, _, lg = dec.verify(k, drafts=drafts if k else None, logits=True)
+            err = 0.0
+            for b in range(batch):
+                ref = om.full_forward(m, np.concatenate([prompts[b], drafts[b]]))[len(prompts[b]) - 1:]
+                err = max(err, float(np.abs(lg[b] - ref).max()))
+            say(f"[gpu]   max |logits - oracle| = {err:.3g}")
+            assert np.all(np.isfinite(lg)) and err <= tol
+        finally:
+            dec.close()
