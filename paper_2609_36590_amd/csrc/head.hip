@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
 
 // Reduce per-n-group argmax partials of one row; lowest token id wins among equal maxima.
 __global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const int* idx, int stride, int n_parts,
-                                                         int* tok_out, int tok_stride) {
+                                                         int* tok_out, int tok_stride, int* host_out, int host_stride) {
   const int m = blockIdx.x, tid = threadIdx.x;
   __shared__ float s_v[256];
   __shared__ int s_i[256];
@@ -310,7 +310,11 @@ __global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const
     }
     __syncthreads();
   }
-  if (tid == 0) tok_out[m * tok_stride] = s_i[0] < 0 ? 0 : s_i[0];
+  if (tid == 0) {
+    const int tok = s_i[0] < 0 ? 0 : s_i[0];
+    tok_out[m * tok_stride] = tok;
+    if (host_out) host_out[m * host_stride] = tok;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -352,8 +356,9 @@ void launch_linear(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEv
 }
 
 void launch_argmax_finalize(const float* val, const int* idx, int stride, int n_parts, int M, int* tok_out,
-                            int tok_stride, hipStream_t s) {
-  hipLaunchKernelGGL(k_argmax_finalize, dim3(M), dim3(256), 0, s, val, idx, stride, n_parts, tok_out, tok_stride);
+                            int tok_stride, int* host_out, int host_stride, hipStream_t s) {
+  hipLaunchKernelGGL(k_argmax_finalize, dim3(M), dim3(256), 0, s, val, idx, stride, n_parts, tok_out, tok_stride, host_out,
+                     host_stride);
 }
 
 // Dynamic LDS available to one workgroup: the device's per-block limit, raised to the opt-in limit

@@ -139,8 +139,12 @@ struct SetupArgs {
   int* row_seq;
   int* row_pos;
   int* row_slot;          // [M] cache slot of the row's keys/values
-  int* tree_tok;          // SETUP_TREE: node tokens [M] (node 0 = the pending token)
-  const int* tree_depth;  // SETUP_TREE: node depths [M] (rotary position t-1 + depth)
+  // nullable host-visible inputs of a call, copied to the device arrays by the rows that read them:
+  // SETUP_VERIFY drafts [M / R][R - 1]; SETUP_TREE tokens, parents and depths of the nodes, each [64]
+  const int* host_drafts;
+  const int* host_tree;
+  int* tree_tok;          // SETUP_TREE: node tokens [M] (node 0 = the pending token), then parents at [64..]
+  int* tree_depth;        // SETUP_TREE: node depths [M] (rotary position t-1 + depth)
   // per-row KV block and RoPE row for the pass's QKV epilogues
   const int* bt;          // block tables [B][bt_stride]
   int bt_stride;
@@ -180,6 +184,8 @@ struct DevState {
   int log_cap;
   const int* vtok;        // [B*R] verifier argmax per row
   int eos;
+  int* hres;              // nullable, host-visible: the acceptance kernel's result per sequence, n_accept [64],
+                          // bonus [64], t [64]; of a tree out[0..65] (path length, bonus, path nodes)
   long long* stamp;       // nullable [stamp_cap][3]: the acceptance kernels write column 2 when done
   int stamp_cap;
 };
@@ -278,8 +284,9 @@ int tree_topk_chunk(int V);
 void launch_row_nll(const float* logits, int rows, int V, const int* target, float* nll, hipStream_t s);
 // Reduce the head's per-workgroup argmax partials of M rows; row m's token goes to
 // tok_out[m * tok_stride] (lowest token id among equal maxima).
+// (and to the host-visible host_out[m * host_stride], if given).
 void launch_argmax_finalize(const float* val, const int* idx, int stride, int n_parts, int M, int* tok_out,
-                            int tok_stride, hipStream_t s);
+                            int tok_stride, int* host_out, int host_stride, hipStream_t s);
 template <typename T>
 void launch_pack(const void* src, void* dst, const int* dst_row, int rows, int K, hipStream_t s);
 void launch_to_f32(const void* src, int src_is_bf16, float* dst, long long n, hipStream_t s);

@@ -37,6 +37,11 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs a, PassSegs sg) {
       // packed draft tree (Tree-Based Verification): node m at rotary position p + depth,
       // cached at slot p + m
       b = 0;
+      if (a.host_tree) {
+        a.tree_tok[m] = a.host_tree[m];
+        a.tree_tok[64 + m] = a.host_tree[64 + m];
+        a.tree_depth[m] = a.host_tree[128 + m];
+      }
       pos = a.t[0] - 1 + a.tree_depth[m];
       slot = a.t[0] - 1 + m;
       tok = a.tree_tok[m];
@@ -50,7 +55,12 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs a, PassSegs sg) {
       b = m / a.R;
       const int r = m - b * a.R;
       pos = a.t[b] - 1 + r;
-      tok = a.drafts[b * a.dstride + r];
+      if (a.host_drafts && r >= 1) {
+        tok = a.host_drafts[b * (a.R - 1) + r - 1];
+        a.drafts[b * a.dstride + r] = tok;
+      } else {
+        tok = a.drafts[b * a.dstride + r];
+      }
       if (a.sim_accept >= 0 && r >= 1 && r <= a.sim_accept + 1) {
         const int tr = a.trace[b * a.tstride + pos];
         tok = (r <= a.sim_accept) ? tr : (tr + 1) % a.vocab;
@@ -154,6 +164,11 @@ __global__ void __launch_bounds__(64) k_accept(DevState st, int B, int k) {
       logv = n;
     }
     if (s_round < st.log_cap) st.nacc_log[(size_t)s_round * B + b] = logv;
+    if (st.hres) {
+      st.hres[b] = st.nacc[b];
+      st.hres[64 + b] = st.bonus[b];
+      st.hres[128 + b] = st.t[b];
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -216,6 +231,8 @@ __global__ void __launch_bounds__(64) k_accept_tree(DevState st, int n, const in
     out[1] = bonus;
     logv = len;
   }
+  if (st.hres)
+    for (int i = 0; i < 2 + out[0]; ++i) st.hres[i] = out[i];
   if (s_round < st.log_cap) st.nacc_log[s_round] = logv;
   *st.rounds = s_round + 1;
   if (st.stamp && s_round < st.stamp_cap) st.stamp[(size_t)s_round * 3 + 2] = (long long)__builtin_amdgcn_s_memrealtime();

@@ -52,6 +52,10 @@ seed_status fail(seed_status s, const std::string& msg) {
 // ms with 1024 / 2048 / 4096 / 8192)
 constexpr int PREFILL_ROWS = 4096;
 constexpr int MAX_ROWS = 64;       // rows per decode pass: max_batch * (max_draft + 1)
+// the context's pinned host memory: tree status, then what a call hands to its kernels (drafts, a tree) and
+// gets back from them (accepted lengths, bonus tokens, committed lengths; draft tokens; a tree's path), so
+// that no call waits for a copy of a few words
+constexpr int HSTAT_IN = 64, HSTAT_OUT = HSTAT_IN + 64 * 16, HSTAT_INTS = HSTAT_OUT + 64 * 16;
 constexpr int ATT_ROWS = 256;      // rows per attention launch of a wider single-sequence pass
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -245,7 +249,7 @@ struct seed_ctx {
   std::map<int, hipGraphExec_t> tree_step_graphs;
   std::map<std::tuple<int, int, int>, hipGraphExec_t> tree_verify_graphs;   // (nodes, eos, sim_accept)
   seed_tree_opts tree_key{};
-  int* hstat = nullptr;       // host pointer
+  int* hstat = nullptr;       // host pointer (HSTAT_INTS: the status, then a call's inputs and results)
   int* hstat_dev = nullptr;   // its device address
   char* scratch_dev = nullptr;   // this device's copy of `scratch` (nullptr if unavailable)
 
@@ -323,6 +327,7 @@ DevState dev_state(seed_ctx* c) {
   st.log_cap = p.log_cap;
   st.vtok = c->ws<int>(p.o_vtok);
   st.eos = c->eos;
+  st.hres = nullptr;
   st.stamp = c->ws<long long>(p.o_stamp);
   st.stamp_cap = p.log_cap;
   return st;
@@ -462,7 +467,7 @@ void run_layers(seed_ctx* c, int M, int B, int R, int l0, int l1, int phase,
 
 template <typename T>
 void run_head(seed_ctx* c, int M, int* tok_out, int tok_stride, float* logits, long long ld,
-              int phase, bool cap) {
+              int phase, bool cap, int* host_out = nullptr, int host_stride = 0) {
   const Plan& p = c->p;
   LinArgs a = lin_base(c, M);
   a.W = c->W + p.w_embed; a.N = p.V; a.K = p.H;
@@ -473,7 +478,8 @@ void run_head(seed_ctx* c, int M, int* tok_out, int tok_stride, float* logits, l
   const int parts = cdiv(p.V / 16, head_group(M, p.V, p.H));   // one argmax partial per n-group
   if (!tok_out) return;   // the caller ranks the logits itself (dynamic drafting)
   timed(c, phase, SEED_OP_HEAD_ARGMAX, cap, [&](const LaunchEvents*) {
-    launch_argmax_finalize(a.amax_val, a.amax_idx, a.amax_stride, parts, M, tok_out, tok_stride, c->s);
+    launch_argmax_finalize(a.amax_val, a.amax_idx, a.amax_stride, parts, M, tok_out, tok_stride, host_out, host_stride,
+                           c->s);
   });
 }
 
@@ -522,7 +528,7 @@ void stamp_phase(seed_ctx* c, SetupArgs& s, int col) {
 
 // Drafting phase: k decoder-only steps for every sequence.
 template <typename T>
-void enqueue_draft(seed_ctx* c, int k, float* logits, bool cap) {
+void enqueue_draft(seed_ctx* c, int k, float* logits, bool cap, int* host_drafts = nullptr) {
   const Plan& p = c->p;
   const int B = c->B;
   for (int i = 1; i <= k; ++i) {
@@ -532,22 +538,26 @@ void enqueue_draft(seed_ctx* c, int k, float* logits, bool cap) {
     timed(c, SEED_PHASE_DRAFT, SEED_OP_SETUP, cap, [&](const LaunchEvents*) { launch_setup<T>(s, PassSegs{}, c->s); });
     run_layers<T>(c, B, B, 1, p.LD, p.L, SEED_PHASE_DRAFT, nullptr, cap);
     run_head<T>(c, B, c->ws<int>(p.o_drafts) + i, p.dstride,
-                logits ? logits + (size_t)(i - 1) * p.V : nullptr, (long long)k * p.V, SEED_PHASE_DRAFT, cap);
+                logits ? logits + (size_t)(i - 1) * p.V : nullptr, (long long)k * p.V, SEED_PHASE_DRAFT, cap,
+                host_drafts ? host_drafts + i - 1 : nullptr, k);
   }
 }
 
 // Verification phase + acceptance/commit.
 template <typename T>
-void enqueue_verify(seed_ctx* c, int k, int sim_accept, float* logits, bool cap) {
+void enqueue_verify(seed_ctx* c, int k, int sim_accept, float* logits, bool cap, const int* host_drafts = nullptr,
+                    int* host_res = nullptr) {
   const Plan& p = c->p;
   const int B = c->B, R = k + 1, M = B * R;
   SetupArgs s = setup_base(c, 0);
   s.mode = SETUP_VERIFY; s.M = M; s.R = R; s.sim_accept = sim_accept;
+  s.host_drafts = host_drafts;
   stamp_phase(c, s, 1);
   timed(c, SEED_PHASE_VERIFY, SEED_OP_SETUP, cap, [&](const LaunchEvents*) { launch_setup<T>(s, PassSegs{}, c->s); });
   run_layers<T>(c, M, B, R, 0, p.L, SEED_PHASE_VERIFY, nullptr, cap);
   run_head<T>(c, M, c->ws<int>(p.o_vtok), 1, logits, (long long)p.V, SEED_PHASE_VERIFY, cap);
   DevState st = dev_state(c);
+  st.hres = host_res;
   timed(c, SEED_PHASE_VERIFY, SEED_OP_ACCEPT, cap, [&](const LaunchEvents*) { launch_accept(st, B, k, c->s); });
 }
 
@@ -560,7 +570,7 @@ void enqueue_round(seed_ctx* c, int k, int sim_accept, bool cap) {
 // ---------------------------------------------------------------------------------------------
 // block tables
 // ---------------------------------------------------------------------------------------------
-seed_status ensure_blocks(seed_ctx* c, int b, int positions) {
+seed_status ensure_blocks(seed_ctx* c, int b, int positions, bool upload = true) {
   const Plan& p = c->p;
   positions = std::min(positions, p.cfg.max_ctx);
   const int need = cdiv(positions, 16);
@@ -573,6 +583,7 @@ seed_status ensure_blocks(seed_ctx* c, int b, int positions) {
     c->free_blocks.pop_back();
     c->bt_host[(size_t)b * p.bt_stride + v.size() - 1] = v.back();
   }
+  if (!upload) return SEED_OK;
   int* dst = c->ws<int>(p.o_bt) + (size_t)b * p.bt_stride + first;
   HIPCHK(hipMemcpyAsync(dst, c->bt_host.data() + (size_t)b * p.bt_stride + first, (need - first) * sizeof(int),
                         hipMemcpyHostToDevice, c->s));
@@ -731,26 +742,23 @@ template <typename T>
 seed_status do_prefill(seed_ctx* c, const std::vector<int>& tokens_packed) {
   const Plan& p = c->p;
   const int B = c->B;
-  // committed tokens + state
-  std::vector<int> tok_rows((size_t)B * p.tstride, 0);
-  std::vector<int> t(B), len(B), limit(B), active(B, 1), drafts((size_t)B * p.dstride, 0);
+  // committed tokens + state: the decode state's arrays from the committed lengths to the tokens are one
+  // region of the workspace, written with one copy (rounds and counters among them start at zero)
+  std::vector<char> state(p.o_trace - p.o_t, 0);
+  auto at = [&](size_t off) { return reinterpret_cast<int*>(state.data() + (off - p.o_t)); };
   size_t o = 0;
   for (int b = 0; b < B; ++b) {
-    std::copy(tokens_packed.begin() + o, tokens_packed.begin() + o + c->lens[b], tok_rows.begin() + (size_t)b * p.tstride);
+    std::copy(tokens_packed.begin() + o, tokens_packed.begin() + o + c->lens[b], at(p.o_tokens) + (size_t)b * p.tstride);
     o += c->lens[b];
-    t[b] = len[b] = c->lens[b];
-    limit[b] = p.cfg.max_ctx;
-    drafts[(size_t)b * p.dstride] = tok_rows[(size_t)b * p.tstride + c->lens[b] - 1];
+    at(p.o_t)[b] = at(p.o_len)[b] = c->lens[b];
+    at(p.o_limit)[b] = p.cfg.max_ctx;
+    at(p.o_active)[b] = 1;
+    at(p.o_drafts)[(size_t)b * p.dstride] = tokens_packed[o - 1];
   }
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_tokens), tok_rows.data(), tok_rows.size() * 4, hipMemcpyHostToDevice, c->s));
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_t), t.data(), B * 4, hipMemcpyHostToDevice, c->s));
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_len), len.data(), B * 4, hipMemcpyHostToDevice, c->s));
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_limit), limit.data(), B * 4, hipMemcpyHostToDevice, c->s));
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_active), active.data(), B * 4, hipMemcpyHostToDevice, c->s));
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_drafts), drafts.data(), drafts.size() * 4, hipMemcpyHostToDevice, c->s));
-  launch_fill_u32(c->ws<int>(p.o_rounds), 0, 1, c->s);
+  // tokens of sequences the call does not have are never read
+  const size_t bytes = p.o_tokens - p.o_t + (size_t)B * p.tstride * 4;
+  HIPCHK(hipMemcpyAsync(c->WS + p.o_t, state.data(), bytes, hipMemcpyHostToDevice, c->s));
   launch_fill_u32(c->ws<int>(p.o_stamp), 0, (long long)p.log_cap * 6, c->s);
-  launch_fill_u32(c->ws<long long>(p.o_counters), 0, 4, c->s);
   HIPCHK(hipGetLastError());
   // run the full model over X[0..t-2]; X[t-1] stays pending (its cache entry would be dropped
   // by the first truncation anyway, and causality makes the kept entries identical)
@@ -913,9 +921,12 @@ seed_status start_sequences(seed_ctx* c, int32_t B, const int32_t* lens, int ext
   c->prefilled = false;
   reset_blocks(c);
   for (int b = 0; b < B; ++b) {
-    seed_status st = ensure_blocks(c, b, lens[b] + extra);
+    seed_status st = ensure_blocks(c, b, lens[b] + extra, false);
     if (st != SEED_OK) return st;
   }
+  // every sequence's table in one copy
+  HIPCHK(hipMemcpyAsync(c->ws<int>(c->p.o_bt), c->bt_host.data(), (size_t)B * c->p.bt_stride * sizeof(int),
+                        hipMemcpyHostToDevice, c->s));
   return SEED_OK;
 }
 
@@ -955,10 +966,12 @@ seed_status run_rounds(seed_ctx* c, int k, int n, bool use_graph) {
 // node rows through every layer with the tree attention mask, the LM head (logits optional),
 // then tree acceptance, commit and the move of an accepted leaf's cache entries.
 template <typename T>
-void enqueue_verify_tree(seed_ctx* c, int n, float* logits, bool cap) {
+void enqueue_verify_tree(seed_ctx* c, int n, float* logits, bool cap, const int* host_tree = nullptr,
+                         int* host_res = nullptr) {
   const Plan& p = c->p;
   SetupArgs s = setup_base(c, 0);
   s.mode = SETUP_TREE; s.M = n; s.R = n; s.sim_accept = c->sim_accept;
+  s.host_tree = host_tree;
   s.tree_tok = c->ws<int>(p.o_tree);
   s.tree_depth = c->ws<int>(p.o_tree) + 2 * MAX_ROWS;
   stamp_phase(c, s, 1);
@@ -966,6 +979,7 @@ void enqueue_verify_tree(seed_ctx* c, int n, float* logits, bool cap) {
   run_layers<T>(c, n, 1, n, 0, p.L, SEED_PHASE_VERIFY, nullptr, cap, nullptr, true);
   run_head<T>(c, n, c->ws<int>(p.o_vtok), 1, logits, (long long)p.V, SEED_PHASE_VERIFY, cap);
   DevState st = dev_state(c);
+  st.hres = host_res;
   timed(c, SEED_PHASE_VERIFY, SEED_OP_ACCEPT, cap, [&](const LaunchEvents*) {
     launch_accept_tree(st, n, c->ws<int>(p.o_tree), c->ws<int>(p.o_tree) + MAX_ROWS, c->ws<int>(p.o_tree) + 2 * MAX_ROWS,
                        c->ws<int>(p.o_tree_out), c->KV, p.L, p.n_blocks, p.NKV, p.HD, p.esize, c->ws<int>(p.o_bt),
@@ -1215,7 +1229,7 @@ seed_status seed_create(const seed_config* cfg, void* hip_stream, void* weight_a
   hipError_t e = hipMemcpyAsync(c->wf(p.w_rope_cos), cs.data(), cs.size() * 4, hipMemcpyHostToDevice, c->s);
   if (e == hipSuccess) e = hipMemcpyAsync(c->wf(p.w_rope_sin), sn.data(), sn.size() * 4, hipMemcpyHostToDevice, c->s);
   if (e == hipSuccess) e = hipStreamSynchronize(c->s);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&c->hstat, 256, hipHostMallocCoherent);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&c->hstat, HSTAT_INTS * sizeof(int), hipHostMallocCoherent);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->hstat_dev, c->hstat, 0);
   if (e == hipSuccess) {
     // once per device, with the device current: the address of this GPU's `scratch`
@@ -1309,15 +1323,13 @@ seed_status seed_draft(seed_ctx* c, int32_t k, int32_t* drafts, float* logits) {
   seed_status st = check_step(c, k, (int64_t)k + 1);
   if (st != SEED_OK) return st;
   if (k < 1) return fail(SEED_ERR_ARG, "seed_draft needs k >= 1");
-  if (c->p.cfg.dtype == SEED_BF16) enqueue_draft<uint16_t>(c, k, logits, false);
-  else enqueue_draft<float>(c, k, logits, false);
+  int* const hd = drafts ? c->hstat_dev + HSTAT_OUT : nullptr;
+  if (c->p.cfg.dtype == SEED_BF16) enqueue_draft<uint16_t>(c, k, logits, false, hd);
+  else enqueue_draft<float>(c, k, logits, false, hd);
   HIPCHK(hipGetLastError());
   if (drafts) {
-    std::vector<int> d((size_t)c->B * c->p.dstride);
-    HIPCHK(hipMemcpyAsync(d.data(), c->ws<int>(c->p.o_drafts), d.size() * 4, hipMemcpyDeviceToHost, c->s));
     HIPCHK(hipStreamSynchronize(c->s));
-    for (int b = 0; b < c->B; ++b)
-      for (int i = 0; i < k; ++i) drafts[b * k + i] = d[(size_t)b * c->p.dstride + 1 + i];
+    std::copy(c->hstat + HSTAT_OUT, c->hstat + HSTAT_OUT + c->B * k, drafts);
   }
   c->drafts_k = k;
   return SEED_OK;
@@ -1330,23 +1342,19 @@ seed_status seed_verify(seed_ctx* c, int32_t k, const int32_t* drafts, int32_t* 
   if (drafts) {
     for (int i = 0; i < c->B * k; ++i)
       if (drafts[i] < 0 || drafts[i] >= p.V) return fail(SEED_ERR_ARG, "draft token out of range");
-    for (int b = 0; b < c->B; ++b)
-      if (k > 0)
-        HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_drafts) + (size_t)b * p.dstride + 1, drafts + (size_t)b * k, k * 4,
-                              hipMemcpyHostToDevice, c->s));
+    std::copy(drafts, drafts + c->B * k, c->hstat + HSTAT_IN);
   } else if (k > 0 && c->drafts_k != k) {
     return fail(SEED_ERR_STATE, "no drafts of length k since the last commit (call seed_draft or pass drafts)");
   }
-  if (p.cfg.dtype == SEED_BF16) enqueue_verify<uint16_t>(c, k, -1, logits, false);
-  else enqueue_verify<float>(c, k, -1, logits, false);
+  const int* hd = drafts ? c->hstat_dev + HSTAT_IN : nullptr;
+  if (p.cfg.dtype == SEED_BF16) enqueue_verify<uint16_t>(c, k, -1, logits, false, hd, c->hstat_dev + HSTAT_OUT);
+  else enqueue_verify<float>(c, k, -1, logits, false, hd, c->hstat_dev + HSTAT_OUT);
   HIPCHK(hipGetLastError());
-  std::vector<int> na(c->B), bo(c->B);
-  HIPCHK(hipMemcpyAsync(na.data(), c->ws<int>(p.o_nacc), c->B * 4, hipMemcpyDeviceToHost, c->s));
-  HIPCHK(hipMemcpyAsync(bo.data(), c->ws<int>(p.o_bonus), c->B * 4, hipMemcpyDeviceToHost, c->s));
-  st = read_t(c);
-  if (st != SEED_OK) return st;
-  if (n_accept) std::copy(na.begin(), na.end(), n_accept);
-  if (bonus) std::copy(bo.begin(), bo.end(), bonus);
+  HIPCHK(hipStreamSynchronize(c->s));
+  const int* res = c->hstat + HSTAT_OUT;
+  if (n_accept) std::copy(res, res + c->B, n_accept);
+  if (bonus) std::copy(res + 64, res + 64 + c->B, bonus);
+  c->t_upper.assign(res + 128, res + 128 + c->B);
   c->drafts_k = -1;
   return SEED_OK;
 }
@@ -1505,17 +1513,16 @@ seed_status seed_verify_tree(seed_ctx* c, int32_t n, const int32_t* tokens, cons
   if ((int64_t)c->t_upper[0] + n + 1 > p.cfg.max_ctx) return fail(SEED_ERR_CAPACITY, "the tree would pass max_ctx");
   st = ensure_blocks(c, 0, c->t_upper[0] + n + 1);
   if (st != SEED_OK) return st;
-  HIPCHK(hipMemcpyAsync(c->ws<int>(p.o_tree), host.data(), host.size() * 4, hipMemcpyHostToDevice, c->s));
-  if (p.cfg.dtype == SEED_BF16) enqueue_verify_tree<uint16_t>(c, n, logits, false);
-  else enqueue_verify_tree<float>(c, n, logits, false);
+  std::copy(host.begin(), host.end(), c->hstat + HSTAT_IN);
+  int* const out = c->hstat + HSTAT_OUT;
+  if (p.cfg.dtype == SEED_BF16) enqueue_verify_tree<uint16_t>(c, n, logits, false, c->hstat_dev + HSTAT_IN, c->hstat_dev + HSTAT_OUT);
+  else enqueue_verify_tree<float>(c, n, logits, false, c->hstat_dev + HSTAT_IN, c->hstat_dev + HSTAT_OUT);
   HIPCHK(hipGetLastError());
-  std::vector<int> out(2 + MAX_ROWS);
-  HIPCHK(hipMemcpyAsync(out.data(), c->ws<int>(p.o_tree_out), out.size() * 4, hipMemcpyDeviceToHost, c->s));
-  st = read_t(c);
-  if (st != SEED_OK) return st;
+  HIPCHK(hipStreamSynchronize(c->s));
+  c->t_upper[0] = c->hstat[5];   // the committed length, as the acceptance kernel reports it
   if (path_len) *path_len = out[0];
   if (bonus) *bonus = out[1];
-  if (path) std::copy(out.begin() + 2, out.begin() + 2 + out[0], path);
+  if (path) std::copy(out + 2, out + 2 + out[0], path);
   c->drafts_k = -1;
   return SEED_OK;
 }
