@@ -174,116 +174,130 @@ __global__ void __launch_bounds__(64 * HEAD_NT) k_head_lds(LinArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// LM head for 16 < M <= 64 rows (batched verification, draft trees of more than 16 nodes): the
-// activation rows of all M tokens do not fit LDS whole (4 bytes per element as MFMA B slots), so
-// they are staged in chunks of HEAD_CK k-tiles, double-buffered: the loads of chunk c+1 are issued
-// before chunk c is consumed and written to the other buffer after it. Each of the 8 waves
-// streams one n-tile over all of K in k order (KS = 1, as the narrow kernel does for any M), for TT
-// token tiles of 16 rows, so every row's logits are bit-identical to a pass of fewer rows. A
-// workgroup has HEAD_WIDE_NT = 16 waves (n-tiles), so the 40 staged rows of a batch-8 verification
-// are read by 594 workgroups instead of 1187 (the argmax partials are per 16-n-tile group; the
-// maximum over them is the same).
+// Up to 64 rows (batched verification, draft trees): the rows of all M tokens do not fit LDS whole, so they
+// are staged in chunks of HEAD_CK k-tiles, double-buffered: the loads of chunk c+1 are issued before chunk
+// c is consumed and written to the other buffer after it. The 8 waves of a workgroup take NT n-tiles
+// each (8 NT neighbouring ones together), so that a staged fragment serves NT weight tiles and a
+// vocabulary of 151936 makes one round of 238 workgroups; D k-tiles of weights are in flight. Every load
+// is unconditional and clamped (surplus ones re-read the last k-tile and are never consumed): under a
+// data-dependent branch the compiler's wait counts assume the path without it, and every refill would
+// wait for the whole ring. Bound by the weight stream and the one barrier per chunk: 31 rows of the
+// 28-layer shape (622 MB) 146 -> 120 us (5.2 TB/s) against 16 waves of one n-tile each, 594 workgroups in 2.3
+// rounds; 8 k-tiles of weights in flight instead of 4 changed nothing (125 us).
 // ---------------------------------------------------------------------------------------------
-constexpr int HEAD_CK = 8;   // k-tiles per staged chunk (= the weight ring depth)
+constexpr int HEAD_CK = 8;   // k-tiles per staged chunk
 
-template <typename T, int TT, int NW>
-__global__ void __launch_bounds__(NW * 64) k_linear_head_chunked(LinArgs a) {
+template <typename T, int TT, int NT, int D>
+__global__ void __launch_bounds__(64 * HEAD_NT) k_head_chunked(LinArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ float s_rs[64];
-  constexpr int P = HEAD_CK;
-  constexpr int NTH = NW * 64;
-  constexpr int XI = (HEAD_CK * 4 * 16 * TT + NTH - 1) / NTH;   // staged items per thread and chunk
+  constexpr int NTH = 64 * HEAD_NT;
+  constexpr int TILES = TT * HEAD_CK, CHUNK = TILES * ACT_TILE, XI = CHUNK / 16 / NTH;   // pieces per thread and chunk
+  static_assert(HEAD_CK % D == 0 && CHUNK % (16 * NTH) == 0, "ring slots and pieces are static");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int KT = a.K >> 5, n_tiles = a.N >> 4, M = a.M;
+  const int KT = a.K >> 5, n_tiles = a.N >> 4, M = a.M, m_tiles = (M + 15) >> 4;
   const int tl = lane & 15, kg = lane >> 4;
-  const int nt = blockIdx.x * NW + wave;
-  const T* w0 = reinterpret_cast<const T*>(a.W) + (size_t)(nt < n_tiles ? nt : 0) * KT * 512 + lane * 8;
-  const size_t chunk_bytes = (size_t)HEAD_CK * 4 * M * 32;
-  const size_t zero_off = 2 * chunk_bytes;
+  const int nt0 = blockIdx.x * NT * HEAD_NT + wave;   // this wave's n-tiles: nt0 + i * HEAD_NT
   const int NC = (KT + HEAD_CK - 1) / HEAD_CK;
 
-  float ssv[4] = {0.f, 0.f, 0.f, 0.f};
-  const bool pre = preload_row_ssq(a, wave, ssv);
+  // ---- the rows' sums of squares: rows wave, wave + 8, .. ----
+  float ssv[64 / HEAD_NT][4];
+#pragma unroll
+  for (int r = 0; r < 64 / HEAD_NT; ++r)
+    if (r * HEAD_NT < M) preload_row_ssq(a, min(wave + r * HEAD_NT, M - 1), ssv[r]);
+  __builtin_amdgcn_sched_barrier(0);
 
-  // chunk c's items q = (ktl*4 + kg)*M + r hold x[r][32(c*CK + ktl) + 8kg .. +7]; loaded branch-free
-  // (items past the chunk reload item 0 and are not written)
-  Slot xv[XI];
-  auto stage_load = [&](int c) {
-    const int nkc = min(HEAD_CK, KT - c * HEAD_CK), items = nkc * 4 * M;
+  // chunk c: tile (mt, ktl) at (mt * HEAD_CK + ktl) * ACT_TILE of its buffer
+  u32x4 xv[XI];
+  auto stage_load = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < XI; ++u) {
-      const int q = u * NTH + tid, qc = q < items ? q : 0;
-      xv[u] = load_slot(a.X, KT, act_frag(M), qc % M, c * HEAD_CK * 4 + qc / M);
+      const int o = (u * NTH + tid) * 16, tile = o / ACT_TILE;
+      const int mt = min(tile / HEAD_CK, m_tiles - 1), kt = min(c * HEAD_CK + tile % HEAD_CK, KT - 1);
+      xv[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(a.X) + ((size_t)mt * KT + kt) * ACT_TILE + o % ACT_TILE);
     }
   };
-  auto stage_store = [&](int c) {
-    const int nkc = min(HEAD_CK, KT - c * HEAD_CK), items = nkc * 4 * M;
-    char* buf = lds + (c & 1) * chunk_bytes;
+  auto stage_store = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < XI; ++u) {
-      const int q = u * NTH + tid;
-      if (q < items) store_slot(buf + (size_t)q * 32, xv[u]);
-    }
+    for (int u = 0; u < XI; ++u)
+      *reinterpret_cast<u32x4*>(lds + (size_t)(c & 1) * CHUNK + (size_t)(u * NTH + tid) * 16) = xv[u];
   };
-
+  const T* wp[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+    wp[i] = reinterpret_cast<const T*>(a.W) + (size_t)min(nt0 + i * HEAD_NT, n_tiles - 1) * KT * 512 + lane * 8;
+  typename ET<T>::A w[D][NT];
+  auto wload = [&](typename ET<T>::A (&wv)[NT], int kt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) wv[i] = ET<T>::load_nt(wp[i] + (size_t)min(kt, KT - 1) * 512);
+    __builtin_amdgcn_sched_barrier(0);
+  };
   stage_load(0);
-  typename ET<T>::A wb[P];
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int p = 0; p < P; ++p) wb[p] = ET<T>::load_nt(w0 + (size_t)min(p, KT - 1) * 512);
+  for (int p = 0; p < D; ++p) wload(w[p], p);
+#pragma unroll
+  for (int r = 0; r < 64 / HEAD_NT; ++r) {
+    const int m = wave + r * HEAD_NT;
+    if (r * HEAD_NT < M) {
+      const float rs = wave_row_scale(a, min(m, M - 1), ssv[r], a.nssq <= 256);
+      if (lane == 0 && m < M) s_rs[m] = rs;
+    }
+  }
   stage_store(0);
-  if (tid < 2) *reinterpret_cast<float4*>(lds + zero_off + tid * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
 
-  f32x4 acc[TT];
+  f32x4 acc[NT][TT];
 #pragma unroll
-  for (int tt = 0; tt < TT; ++tt) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // every load below is issued unconditionally (the last chunk is reloaded past the end, weight
-  // tiles past K re-read the last one, neither is consumed): a load under a data-dependent branch
-  // makes the compiler's wait counts assume the path without it, and every refill would then wait
-  // for the whole ring
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fo = act_slot(act_frag(M), tl, kg), fp = act_plane(act_frag(M));
   for (int c = 0; c < NC; ++c) {
-    stage_load(min(c + 1, NC - 1));
-    const char* buf = lds + (c & 1) * chunk_bytes;
+    stage_load(c + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const char* buf = lds + (size_t)(c & 1) * CHUNK + fo;
     const int nkc = min(HEAD_CK, KT - c * HEAD_CK);
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
+    for (int p = 0; p < HEAD_CK; ++p) {
       if (p < nkc) {
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-          const int m = tt * 16 + tl;
-          const char* xb = m < M ? buf + ((size_t)(p * 4 + kg) * M + m) * 32 : lds + zero_off;
-          ET<T>::mma(acc[tt], wb[p], lds_slot<T>(xb));
+        for (int q = 0; q < 2; ++q) {
+          u32x4 xb[TT];
+#pragma unroll
+          for (int t = 0; t < TT; ++t)
+            xb[t] = *reinterpret_cast<const u32x4*>(buf + (t * HEAD_CK + p) * ACT_TILE + q * fp);
+#pragma unroll
+          for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) ET<T>::mma_plane(acc[i][t], w[p % D][i], xb[t], q);
         }
       }
-      const int nxt = c * HEAD_CK + p + P;
-      wb[p] = ET<T>::load_nt(w0 + (size_t)min(nxt, KT - 1) * 512);
-      __builtin_amdgcn_sched_barrier(0);
+      wload(w[p % D], c * HEAD_CK + p + D);
     }
-    if (c + 1 < NC) stage_store(c + 1);
+    stage_store(c + 1);
     __syncthreads();
   }
 
-  // lane (tl, kg) holds features 4kg..4kg+3 of token tt*16+tl: Y[wave][m][16] over the buffers
+  // lane (tl, kg) holds features 4kg..4kg+3 of token t*16+tl: Y[wave][m][16] over the buffers, one of the
+  // waves' NT n-tiles at a time (8 neighbouring n-tiles together)
   float* Y = reinterpret_cast<float*>(lds);
 #pragma unroll
-  for (int tt = 0; tt < TT; ++tt) {
-    const int m = tt * 16 + tl;
-    if (m < M) {
-      float* dst = Y + ((size_t)wave * M + m) * 16 + 4 * kg;
-      dst[0] = acc[tt][0]; dst[1] = acc[tt][1]; dst[2] = acc[tt][2]; dst[3] = acc[tt][3];
+  for (int i = 0; i < NT; ++i) {
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      const int m = t * 16 + tl;
+      if (m < M) {
+        const float rs = s_rs[m];
+        *reinterpret_cast<float4*>(Y + ((size_t)wave * M + m) * 16 + 4 * kg) =
+            make_float4(acc[i][t][0] * rs, acc[i][t][1] * rs, acc[i][t][2] * rs, acc[i][t][3] * rs);
+      }
     }
+    __syncthreads();
+    const int g = blockIdx.x * NT + i;
+    if (g * HEAD_NT < n_tiles) head_epilogue(a, g, HEAD_NT, Y, M * 16);
+    __syncthreads();
   }
-  for (int m = wave; m < M; m += NW) {
-    const float r = wave_row_scale(a, m, ssv, pre && m == wave);
-    if (lane == 0) s_rs[m] = r;
-  }
-  __syncthreads();
-  const int per = M * 16;
-  for (int e = tid; e < NW * per; e += blockDim.x) {
-    Y[e] *= s_rs[(e % per) >> 4];
-  }
-  __syncthreads();
-  head_epilogue(a, blockIdx.x, NW, Y, M * 16);
 }
 
 // Reduce per-n-group argmax partials of one row; lowest token id wins among equal maxima.
@@ -323,28 +337,40 @@ __global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const
 static size_t g_lds_limit = 65536;   // dynamic LDS one workgroup may use (set by configure_kernels)
 
 static size_t head_lds_bytes(int M, int K) { return lds_x_bytes(M, K >> 5) + (size_t)(HEAD_NT * M + 1) * 16 * sizeof(float); }
-static size_t head_chunked_lds(int M) { return 2 * (size_t)HEAD_CK * 4 * M * 32 + 32; }
+// n-tiles per argmax partial
+int head_group(int N) { return head_by_rows(N) ? ROWS_HEAD_NT : HEAD_NT; }
 
-// n-tiles per argmax partial (per workgroup): 8 where the rows fit LDS whole, else the chunked kernel's 16
-int head_group(int M, int N, int K) {
-  if (head_by_rows(N)) return ROWS_HEAD_NT;
-  return M <= 16 && head_lds_bytes(M, K) <= g_lds_limit ? HEAD_NT : HEAD_WIDE_NT;
+template <typename T, int TT, int NT>
+static void launch_head_chunked(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
+  const int n_tiles = a.N >> 4, per = NT * HEAD_NT;
+  launch(k_head_chunked<T, TT, NT, 4>, dim3((n_tiles + per - 1) / per), dim3(64 * HEAD_NT), 2 * (size_t)TT * HEAD_CK * ACT_TILE,
+         s, ev, a);
+}
+
+// n-tiles per wave: 5 where a round of one workgroup per CU takes the whole vocabulary, or nearly (it is the
+// largest whose sums and operands fit the registers of two waves per SIMD), else 1
+template <typename T, int TT>
+static void launch_head_tt(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
+  if constexpr (sizeof(T) == 2) {
+    if ((a.N >> 4) >= 128 * 5 * HEAD_NT) {
+      launch_head_chunked<T, TT, 5>(a, s, ev);
+      return;
+    }
+  }
+  launch_head_chunked<T, TT, 1>(a, s, ev);
 }
 
 template <typename T>
 static void launch_head(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  const int n_tiles = a.N >> 4, NT = head_group(a.M, a.N, a.K);
-  const dim3 grid((n_tiles + NT - 1) / NT), block(64 * NT);
-  if (NT == HEAD_NT) {
-    launch(k_head_lds<T>, grid, block, head_lds_bytes(a.M, a.K), s, ev, a);
+  if (a.M <= 16 && head_lds_bytes(a.M, a.K) <= g_lds_limit) {
+    launch(k_head_lds<T>, dim3(((a.N >> 4) + HEAD_NT - 1) / HEAD_NT), dim3(64 * HEAD_NT), head_lds_bytes(a.M, a.K), s, ev, a);
     return;
   }
-  const size_t lds = head_chunked_lds(a.M);
   switch ((a.M + 15) / 16) {
-    case 1: launch(k_linear_head_chunked<T, 1, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
-    case 2: launch(k_linear_head_chunked<T, 2, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
-    case 3: launch(k_linear_head_chunked<T, 3, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
-    default: launch(k_linear_head_chunked<T, 4, HEAD_WIDE_NT>, grid, block, lds, s, ev, a); break;
+    case 1: launch_head_tt<T, 1>(a, s, ev); break;
+    case 2: launch_head_tt<T, 2>(a, s, ev); break;
+    case 3: launch_head_tt<T, 3>(a, s, ev); break;
+    default: launch_head_tt<T, 4>(a, s, ev); break;
   }
 }
 
@@ -365,11 +391,10 @@ void launch_argmax_finalize(const float* val, const int* idx, int stride, int n_
 // when every kernel accepted it (failed opt-ins are cleared and ignored).
 template <typename T>
 static bool allow_big_lds(int bytes) {
-  const void* fns[] = {reinterpret_cast<const void*>(&k_head_lds<T>),
-                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 1, HEAD_WIDE_NT>),
-                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 2, HEAD_WIDE_NT>),
-                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 3, HEAD_WIDE_NT>),
-                       reinterpret_cast<const void*>(&k_linear_head_chunked<T, 4, HEAD_WIDE_NT>)};
+  const void* fns[] = {reinterpret_cast<const void*>(&k_head_lds<T>), reinterpret_cast<const void*>(&k_head_chunked<T, 3, 1, 4>),
+                       reinterpret_cast<const void*>(&k_head_chunked<T, 4, 1, 4>),
+                       reinterpret_cast<const void*>(&k_head_chunked<T, 3, sizeof(T) == 2 ? 5 : 1, 4>),
+                       reinterpret_cast<const void*>(&k_head_chunked<T, 4, sizeof(T) == 2 ? 5 : 1, 4>)};
   bool ok = true;
   for (const void* f : fns) ok &= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
   return ok && rows_allow_lds<T>();

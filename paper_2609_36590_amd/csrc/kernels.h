@@ -190,13 +190,12 @@ struct DevState {
   int stamp_cap;
 };
 
-// n-tiles per workgroup of the LM head's kernels (one argmax partial each): rows that fit LDS whole, rows
-// staged in chunks, and small vocabularies.
-constexpr int HEAD_NT = 8, HEAD_WIDE_NT = 16, ROWS_HEAD_NT = 2;
+// n-tiles per argmax partial of the LM head: of its own kernels (waves of a workgroup), and of small vocabularies.
+constexpr int HEAD_NT = 8, ROWS_HEAD_NT = 2;
 // Small vocabularies split K over waves like the other projections: at 1024 tokens the head's kernels
 // would have 8 workgroups, each wave a chain over all of K (5 rows 19 us, 40 rows 55).
 __host__ __device__ inline bool head_by_rows(int N) { return N < 32768; }
-int head_group(int M, int N, int K);   // n-tiles per argmax partial of a head launch
+int head_group(int N);   // n-tiles per argmax partial
 constexpr int PF_SPLIT_MAX = 3;     // position splits of the one-launch pass attention,
 constexpr int PF_SPLIT_ROWS = 1024;  // of passes of at most this many rows
 constexpr int ROWS_KS_MAX = 16;     // k-ranges of a decode pass's projection (waves of a workgroup)

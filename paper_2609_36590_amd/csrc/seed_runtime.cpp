@@ -475,7 +475,7 @@ void run_head(seed_ctx* c, int M, int* tok_out, int tok_stride, float* logits, l
   a.logits = logits; a.ld_logits = ld;
   if (!tok_out) a.amax_val = nullptr, a.amax_idx = nullptr;   // logits only: no argmax partials
   linear<T>(c, a, EPI_HEAD, phase, SEED_OP_HEAD, cap);
-  const int parts = cdiv(p.V / 16, head_group(M, p.V, p.H));   // one argmax partial per n-group
+  const int parts = cdiv(p.V / 16, head_group(p.V));   // one argmax partial per n-group
   if (!tok_out) return;   // the caller ranks the logits itself (dynamic drafting)
   timed(c, phase, SEED_OP_HEAD_ARGMAX, cap, [&](const LaunchEvents*) {
     launch_argmax_finalize(a.amax_val, a.amax_idx, a.amax_stride, parts, M, tok_out, tok_stride, host_out, host_stride,
