@@ -300,32 +300,46 @@ __global__ void __launch_bounds__(64 * HEAD_NT) k_head_chunked(LinArgs a) {
   }
 }
 
-// Reduce per-n-group argmax partials of one row; lowest token id wins among equal maxima.
+// Reduce per-n-group argmax partials of one row; lowest token id wins among equal maxima. One round trip for
+// up to 2048 partials (151936 tokens make 1187): 8 clamped loads in flight per thread, then butterflies.
 __global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const int* idx, int stride, int n_parts,
                                                          int* tok_out, int tok_stride, int* host_out, int host_stride) {
-  const int m = blockIdx.x, tid = threadIdx.x;
-  __shared__ float s_v[256];
-  __shared__ int s_i[256];
+  constexpr int U = 8;
+  const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ float s_v[4];
+  __shared__ int s_i[4];
   float best = NEG_INF;
   int bi = -1;
-  for (int j = tid; j < n_parts; j += blockDim.x) {
-    const float v = val[(size_t)m * stride + j];
-    const int i = idx[(size_t)m * stride + j];
+  auto take = [&](float v, int i) {
     if (i >= 0 && (bi < 0 || v > best || (v == best && i < bi))) { best = v; bi = i; }
-  }
-  s_v[tid] = best;
-  s_i[tid] = bi;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if (tid < o) {
-      const float v = s_v[tid + o];
-      const int i = s_i[tid + o];
-      if (i >= 0 && (s_i[tid] < 0 || v > s_v[tid] || (v == s_v[tid] && i < s_i[tid]))) { s_v[tid] = v; s_i[tid] = i; }
+  };
+  for (int j0 = 0; j0 < n_parts; j0 += U * 256) {
+    float v[U];
+    int i[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = min(j0 + u * 256 + tid, n_parts - 1);   // a partial taken twice changes nothing
+      v[u] = val[(size_t)m * stride + j];
+      i[u] = idx[(size_t)m * stride + j];
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) take(v[u], i[u]);
   }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const float ov = __shfl_xor(best, o);
+    const int oi = __shfl_xor(bi, o);
+    take(ov, oi);
+  }
+  if (lane == 0) {
+    s_v[wave] = best;
+    s_i[wave] = bi;
+  }
+  __syncthreads();
   if (tid == 0) {
-    const int tok = s_i[0] < 0 ? 0 : s_i[0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) take(s_v[w], s_i[w]);
+    const int tok = bi < 0 ? 0 : bi;
     tok_out[m * tok_stride] = tok;
     if (host_out) host_out[m * host_stride] = tok;
   }

@@ -48,3 +48,21 @@ def test_verification_rows(shape, dtype, tol):
             assert np.all(np.isfinite(lg)) and err <= tol
         finally:
             dec.close()
+
+
+@pytest.mark.parametrize("vocab", [16, 32784, 262160])
+def test_argmax_over_many_groups(vocab):
+    """Partial maxima of 1, 257 and 2049 vocabulary groups (one more than one pass over them holds); every
+    13 tokens share their logits bit for bit, so the lowest id has to win across groups."""
+    cfg = BASE.replace(name=f"argmax-{vocab}", hidden=32, n_heads=1, n_kv_heads=1, head_dim=64, ffn=32, vocab=vocab)
+    w = synth.make_weights(cfg, seed=7)
+    w["embed"] = np.ascontiguousarray(w["embed"][np.arange(vocab) % 13])
+    dec = decoder(cfg, w, max_batch=2, max_ctx=32, max_draft=4)
+    try:
+        say(f"[gpu] argmax over {vocab} tokens")
+        dec.prefill([np.arange(3, dtype=np.int32), np.arange(7, dtype=np.int32)])
+        d, lg = dec.draft(4, logits=True)
+        assert d.max() < 13
+        assert np.array_equal(d, lg.argmax(-1))
+    finally:
+        dec.close()
