@@ -385,7 +385,7 @@ def split_sweep(torch, out_md):
 # ------------------------------------------------------------------------------------------
 # forward pass of the speculative drafting objective (Algorithm 1) on the 4B model
 # ------------------------------------------------------------------------------------------
-SPEC_ROWS = 1024   # rows per pass of the GPU path (its prefill chunk, tiled MFMA GEMMs)
+SPEC_ROWS = 4096   # rows per pass of the GPU path (its prefill chunk, tiled MFMA GEMMs)
 
 
 def spec_sweep(torch, out_md, reps=5):
@@ -452,7 +452,7 @@ def spec_sweep(torch, out_md, reps=5):
              "visible positions x heads x head_dim per row and layer); at 1023 rows it is ~1000 FLOP per",
              "weight byte, past the bf16 ridge (2.5 PFLOP/s / 8 TB/s = 312 FLOP/B), so its roofline is",
              "the dense bf16 MFMA peak (2.5 PFLOP/s). The prefill (36 layers over 1024 rows, same rule)",
-             f"likewise. The GPU path takes {SPEC_ROWS} rows per pass (tiled MFMA GEMMs; each n-group's",
+             f"likewise. The GPU path takes up to {SPEC_ROWS} rows per pass (tiled MFMA GEMMs; each n-group's",
              "weights come from HBM once per pass and are shared by its row tiles through the XCD's L2),",
              "so the decoder layers and the head are streamed once per pass (`streamed` bytes below: the",
              "weights once, 1.18 GB per pass, plus the keys/values each row reads).", "",
