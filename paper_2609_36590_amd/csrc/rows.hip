@@ -327,7 +327,9 @@ static void launch_rows(const LinArgs& a, hipStream_t s, const LaunchEvents* ev)
 
 // More than 8 k-ranges (a long K into a narrow N: the down projection): two ranges per workgroup, NT n-tiles
 // each, and a reduction. All ranges in one workgroup would give 160 workgroups at the 4B shape, each
-// reading every row's activations: 15.2 us at 5 rows and 31.5 at 40, against 10.2 + 4.5 and 14.0 + 5.1.
+// reading every row's activations: 15.2 us at 5 rows and 31.5 at 40, against 10.2 + 4.5 and 14.0 + 5.1. Fewer rows gain
+// nothing from it either: verification of 2 rows (36 layers) 2.141 ms as it is, 2.173 in one launch; a draft
+// step 235 and 237 us.
 template <typename T, int NT, int TT, int D>
 static void launch_rows_part(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
   const int n_tiles = a.N >> 4;
