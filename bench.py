@@ -81,7 +81,7 @@ def step_bytes(cfg, M, L, layers):
 # ------------------------------------------------------------------------------------------
 # HBM traffic from rocprofv3 counters (FETCH_SIZE / WRITE_SIZE), measured offline
 # ------------------------------------------------------------------------------------------
-KERNEL_SOURCES = ("rows.hip", "head.hip", "wide.hip", "attention.hip", "misc.hip", "device_common.h", "kernels.h")
+KERNEL_SOURCES = ("rows.hip", "head.hip", "wide.hip", "attention.hip", "misc.hip", "device_common.h", "kernels.h", "dispatch.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_4B-36L_k4_b1.md")
 
 

@@ -1,0 +1,78 @@
+// Launch rules of the linear kernels: which variant, k-ranges, tiles and grid a pass takes, as plain host
+// functions of sizes and types, so that they can be checked over every accepted shape without a GPU.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+
+namespace seedk {
+
+enum Epilogue { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
+
+constexpr int ROWS_HEAD_NT = 2;     // n-tiles per argmax partial of a small vocabulary's head (rows.hip)
+constexpr int ROWS_KS_MAX = 16;     // k-ranges of a decode pass's projection
+constexpr int ROWS_THREADS = 512;   // largest workgroup of k_linear_rows (its launch bounds),
+constexpr int ROWS_PART_THREADS = 128;   // of the form whose k-ranges go to several workgroups
+constexpr size_t ROWS_LDS = 150 * 1024;   // partial sums of one workgroup
+
+inline size_t rows_lds(int NT, int KS, int M) { return (size_t)NT * KS * M * 16 * sizeof(float); }
+
+// K-ranges, a function of the weight shape only: 8 where N gives the chip enough workgroups (QKV, gate/up)
+// and for a small vocabulary's head; else ranges of about 16 k-tiles, at most 8, the waves of one workgroup.
+// Only the residual projections have a form with more (16: rows_plan's part).
+inline int rows_ks(int n_tiles, int KT, int epilogue) {
+  if (n_tiles >= 256 || epilogue == EPI_HEAD) return std::min(8, KT);
+  return std::min(epilogue == EPI_RESID ? ROWS_KS_MAX : ROWS_THREADS / 64, std::max(1, KT / 16));
+}
+
+// n-tiles per workgroup: the fewest rounds of one workgroup per CU x (n-tiles + half a tile's time to
+// start), among those whose partial sums fit LDS (5 only up to 48 rows: its sums and operands fill the
+// registers). Measured at 5 rows, us for NT = 1 / 2 / 3 / 5: gate/up of the 4B shape (1216 n-tiles) 19.9 /
+// 20.9 / 20.0 / 17.9, QKV (384) 10.3 / 9.0 / 10.7 / 13.2, O (160) 8.2 / 10.4 / 12.4 / 16.6; at 8 rows gate/up of
+// the 28-layer shape (768) 16.9 / 15.6 / 11.9 / 13.5.
+inline int rows_nt(int n_tiles, int KS, int M) {
+  const int cands[] = {5, 3, 2, 1};
+  int best = 1;
+  long long best_cost = -1;
+  for (int nt : cands) {
+    if (rows_lds(nt, KS, M) > ROWS_LDS || (nt == 5 && M > 48)) continue;
+    const long long cost = (((n_tiles + nt - 1) / nt + 255) / 256) * (2 * nt + 1);
+    if (best_cost < 0 || cost < best_cost) best = nt, best_cost = cost;
+  }
+  return best;
+}
+
+// A decode pass's projection (M <= 64 rows, N x K weights of esize bytes): its k-ranges, n-tiles per
+// workgroup and grid. part: the k-ranges go to several workgroups, two each, and a second kernel adds them.
+struct RowsPlan {
+  int KS, NT;
+  bool part;
+  int gx, gy, threads;
+  size_t lds;
+};
+
+inline RowsPlan rows_plan(int N, int K, int M, int epilogue, int esize) {
+  const int n_tiles = N >> 4;
+  RowsPlan p;
+  p.KS = rows_ks(n_tiles, K >> 5, epilogue);
+  // More than 8 k-ranges (a long K into a narrow N: the down projection): two ranges per workgroup, NT n-tiles
+  // each, and a reduction. All ranges in one workgroup would give 160 workgroups at the 4B shape, each
+  // reading every row's activations: 15.2 us at 5 rows and 31.5 at 40, against 10.2 + 4.5 and 14.0 + 5.1. Fewer rows gain
+  // nothing from it either: verification of 2 rows (36 layers) 2.141 ms as it is, 2.173 in one launch; a draft
+  // step 235 and 237 us.
+  p.part = epilogue == EPI_RESID && p.KS > 8;
+  if (p.part)
+    // 5 n-tiles where that still makes about two waves per CU, else 2 (28-layer down, 128 x 12 ranges, 31
+    // rows: 11.0 us with 2, 11.7 with 3; 4B down, 160 x 16, 40 rows: 22.4 / 17.0 / 14.0 with 2 / 3 / 5)
+    p.NT = esize == 2 && (n_tiles + 4) / 5 * p.KS >= 480 ? 5 : 2;
+  else if (epilogue == EPI_HEAD)
+    p.NT = ROWS_HEAD_NT;
+  else
+    p.NT = esize == 4 ? 1 : rows_nt(n_tiles, p.KS, M);   // fp32 operands take twice the registers
+  p.gx = (n_tiles + p.NT - 1) / p.NT;
+  p.gy = p.part ? (p.KS + 1) / 2 : 1;
+  p.threads = p.part ? ROWS_PART_THREADS : 64 * p.KS;
+  p.lds = p.part ? 0 : rows_lds(p.NT, p.KS, M);
+  return p;
+}
+
+}  // namespace seedk

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dispatch.h"
+
 namespace seedk {
 
 // ---------------------------------------------------------------------------------------------
@@ -36,8 +38,6 @@ __host__ __device__ inline int act_plane(bool frag) { return frag ? 1024 : 64; }
 __host__ __device__ inline int act_slot(bool frag, int row16, int kg) {
   return frag ? kg * 256 + row16 * 16 : row16 * 128 + kg * 16;
 }
-
-enum Epilogue { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
 
 // Arguments of the linear kernels.
 struct LinArgs {
@@ -190,15 +190,14 @@ struct DevState {
   int stamp_cap;
 };
 
-// n-tiles per argmax partial of the LM head: of its own kernels (waves of a workgroup), and of small vocabularies.
-constexpr int HEAD_NT = 8, ROWS_HEAD_NT = 2;
+// n-tiles per argmax partial of the LM head's own kernels (waves of a workgroup); ROWS_HEAD_NT of small vocabularies
+constexpr int HEAD_NT = 8;
 // Small vocabularies split K over waves like the other projections: at 1024 tokens the head's kernels
 // would have 8 workgroups, each wave a chain over all of K (5 rows 19 us, 40 rows 55).
 __host__ __device__ inline bool head_by_rows(int N) { return N < 32768; }
 int head_group(int N);   // n-tiles per argmax partial
 constexpr int PF_SPLIT_MAX = 3;     // position splits of the one-launch pass attention,
 constexpr int PF_SPLIT_ROWS = 1024;  // of passes of at most this many rows
-constexpr int ROWS_KS_MAX = 16;     // k-ranges of a decode pass's projection (waves of a workgroup)
 constexpr int WIDE_SPLIT_MAX = 4;   // k-ranges of a split wide pass (its partials: WIDE_SPLIT_MAX x rows x N floats)
 
 // Optional timing events stamped by the launches themselves (hipExtLaunchKernel): `start` at the

@@ -301,110 +301,72 @@ __global__ void __launch_bounds__(256) k_rows_reduce(LinArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Launcher.
+// Launchers (rows_plan in dispatch.h).
 // ---------------------------------------------------------------------------------------------
-static constexpr size_t ROWS_LDS = 150 * 1024;   // partial sums of one workgroup
-
-static size_t rows_lds(int NT, int KS, int M) { return (size_t)NT * KS * M * 16 * sizeof(float); }
-
-// K-ranges, a function of the weight shape only: 8 where N gives the chip enough workgroups (QKV, gate/up)
-// and for a small vocabulary's head; else ranges of about 16 k-tiles, at most 16.
-static int rows_ks(int n_tiles, int KT, int epilogue) {
-  if (n_tiles >= 256 || epilogue == EPI_HEAD) return std::min(8, KT);
-  return std::min(ROWS_KS_MAX, std::max(1, KT / 16));
-}
-
 // k-tiles in flight per wave: what 256 registers (8 waves per CU) leave beside the sums
 static constexpr int rows_depth(int NT, int TT) {
   return NT == 5 ? (TT == 1 ? 5 : TT == 2 ? 4 : 3) : NT == 3 ? (TT <= 2 ? 5 : 3) : NT == 2 && TT == 4 ? 4 : 5;
 }
 
 template <typename T, int EPI, int NT, int TT, int D>
-static void launch_rows(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  launch(k_linear_rows<T, EPI, NT, TT, D, 512, false>, dim3(((a.N >> 4) + NT - 1) / NT), dim3(64 * a.KS),
-         rows_lds(NT, a.KS, a.M), s, ev, a);
+static void launch_rows(const LinArgs& a, const RowsPlan& p, hipStream_t s, const LaunchEvents* ev) {
+  launch(k_linear_rows<T, EPI, NT, TT, D, ROWS_THREADS, false>, dim3(p.gx), dim3(p.threads), p.lds, s, ev, a);
 }
 
-// More than 8 k-ranges (a long K into a narrow N: the down projection): two ranges per workgroup, NT n-tiles
-// each, and a reduction. All ranges in one workgroup would give 160 workgroups at the 4B shape, each
-// reading every row's activations: 15.2 us at 5 rows and 31.5 at 40, against 10.2 + 4.5 and 14.0 + 5.1. Fewer rows gain
-// nothing from it either: verification of 2 rows (36 layers) 2.141 ms as it is, 2.173 in one launch; a draft
-// step 235 and 237 us.
 template <typename T, int NT, int TT, int D>
-static void launch_rows_part(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  const int n_tiles = a.N >> 4;
+static void launch_rows_part(const LinArgs& a, const RowsPlan& p, hipStream_t s, const LaunchEvents* ev) {
   const LaunchEvents e0{ev ? ev->start : nullptr, nullptr}, e1{nullptr, ev ? ev->stop : nullptr};
-  launch(k_linear_rows<T, EPI_RESID, NT, TT, D, 128, true>, dim3((n_tiles + NT - 1) / NT, (a.KS + 1) / 2), dim3(128), 0, s,
+  launch(k_linear_rows<T, EPI_RESID, NT, TT, D, ROWS_PART_THREADS, true>, dim3(p.gx, p.gy), dim3(p.threads), 0, s,
          ev ? &e0 : nullptr, a);
-  launch(k_rows_reduce<T>, dim3((unsigned)((n_tiles * a.M * 4 + 255) / 256)), dim3(256), 0, s, ev ? &e1 : nullptr, a);
-}
-
-// n-tiles per workgroup: the fewest rounds of one workgroup per CU x (n-tiles + half a tile's time to
-// start), among those whose partial sums fit LDS (5 only up to 48 rows: its sums and operands fill the
-// registers). Measured at 5 rows, us for NT = 1 / 2 / 3 / 5: gate/up of the 4B shape (1216 n-tiles) 19.9 /
-// 20.9 / 20.0 / 17.9, QKV (384) 10.3 / 9.0 / 10.7 / 13.2, O (160) 8.2 / 10.4 / 12.4 / 16.6; at 8 rows gate/up of
-// the 28-layer shape (768) 16.9 / 15.6 / 11.9 / 13.5.
-static int rows_nt(int n_tiles, int KS, int M) {
-  const int cands[] = {5, 3, 2, 1};
-  int best = 1;
-  long long best_cost = -1;
-  for (int nt : cands) {
-    if (rows_lds(nt, KS, M) > ROWS_LDS || (nt == 5 && M > 48)) continue;
-    const long long cost = (((n_tiles + nt - 1) / nt + 255) / 256) * (2 * nt + 1);
-    if (best_cost < 0 || cost < best_cost) best = nt, best_cost = cost;
-  }
-  return best;
+  launch(k_rows_reduce<T>, dim3((unsigned)(((a.N >> 4) * a.M * 4 + 255) / 256)), dim3(256), 0, s, ev ? &e1 : nullptr, a);
 }
 
 template <typename T, int EPI, int TT>
-static void launch_rows_tt(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  const int n_tiles = a.N >> 4;
+static void launch_rows_tt(const LinArgs& a, const RowsPlan& p, hipStream_t s, const LaunchEvents* ev) {
   if constexpr (EPI == EPI_RESID) {
-    if (a.KS > 8) {
-      // 5 n-tiles where that still makes about two waves per CU, else 2 (28-layer down, 128 x 12 ranges, 31
-      // rows: 11.0 us with 2, 11.7 with 3; 4B down, 160 x 16, 40 rows: 22.4 / 17.0 / 14.0 with 2 / 3 / 5)
-      if constexpr (sizeof(T) == 4) launch_rows_part<T, 2, TT, 2>(a, s, ev);
-      else if ((n_tiles + 4) / 5 * a.KS >= 480) launch_rows_part<T, 5, TT, TT == 1 ? 8 : TT == 4 ? 5 : 6>(a, s, ev);
-      else launch_rows_part<T, 2, TT, TT == 1 ? 10 : 6>(a, s, ev);
+    if (p.part) {
+      if constexpr (sizeof(T) == 4) launch_rows_part<T, 2, TT, 2>(a, p, s, ev);
+      else if (p.NT == 5) launch_rows_part<T, 5, TT, TT == 1 ? 8 : TT == 4 ? 5 : 6>(a, p, s, ev);
+      else launch_rows_part<T, 2, TT, TT == 1 ? 10 : 6>(a, p, s, ev);
       return;
     }
   }
   if constexpr (EPI == EPI_HEAD) {
-    launch_rows<T, EPI, ROWS_HEAD_NT, TT, sizeof(T) == 4 ? 2 : rows_depth(ROWS_HEAD_NT, TT)>(a, s, ev);
-  } else if constexpr (sizeof(T) == 4) {   // fp32 operands take twice the registers
-    launch_rows<T, EPI, 1, TT, 2>(a, s, ev);
+    launch_rows<T, EPI, ROWS_HEAD_NT, TT, sizeof(T) == 4 ? 2 : rows_depth(ROWS_HEAD_NT, TT)>(a, p, s, ev);
+  } else if constexpr (sizeof(T) == 4) {
+    launch_rows<T, EPI, 1, TT, 2>(a, p, s, ev);
   } else {
     const bool by8 = (a.K >> 5) % (8 * a.KS) == 0;   // ranges of whole 8-tile blocks: 8 in flight, no remainder
-    switch (rows_nt(n_tiles, a.KS, a.M)) {
+    switch (p.NT) {
       case 5:
-        if constexpr (TT <= 3) launch_rows<T, EPI, 5, TT, rows_depth(5, TT)>(a, s, ev);
+        if constexpr (TT <= 3) launch_rows<T, EPI, 5, TT, rows_depth(5, TT)>(a, p, s, ev);
         break;
-      case 3: launch_rows<T, EPI, 3, TT, rows_depth(3, TT)>(a, s, ev); break;
+      case 3: launch_rows<T, EPI, 3, TT, rows_depth(3, TT)>(a, p, s, ev); break;
       case 2:
-        if (TT == 1 && by8) launch_rows<T, EPI, 2, TT, TT == 1 ? 8 : rows_depth(2, TT)>(a, s, ev);
-        else launch_rows<T, EPI, 2, TT, rows_depth(2, TT)>(a, s, ev);
+        if (TT == 1 && by8) launch_rows<T, EPI, 2, TT, TT == 1 ? 8 : rows_depth(2, TT)>(a, p, s, ev);
+        else launch_rows<T, EPI, 2, TT, rows_depth(2, TT)>(a, p, s, ev);
         break;
       default:
-        if (TT <= 2 && by8) launch_rows<T, EPI, 1, TT, TT <= 2 ? 8 : rows_depth(1, TT)>(a, s, ev);
-        else launch_rows<T, EPI, 1, TT, rows_depth(1, TT)>(a, s, ev);
+        if (TT <= 2 && by8) launch_rows<T, EPI, 1, TT, TT <= 2 ? 8 : rows_depth(1, TT)>(a, p, s, ev);
+        else launch_rows<T, EPI, 1, TT, rows_depth(1, TT)>(a, p, s, ev);
     }
   }
 }
 
 template <typename T, int EPI>
-static void launch_rows_epi(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
+static void launch_rows_epi(LinArgs a, hipStream_t s, const LaunchEvents* ev) {
+  const RowsPlan p = rows_plan(a.N, a.K, a.M, EPI, sizeof(T));
+  a.KS = p.KS;
   switch ((a.M + 15) / 16) {
-    case 1: launch_rows_tt<T, EPI, 1>(a, s, ev); break;
-    case 2: launch_rows_tt<T, EPI, 2>(a, s, ev); break;
-    case 3: launch_rows_tt<T, EPI, 3>(a, s, ev); break;
-    default: launch_rows_tt<T, EPI, 4>(a, s, ev); break;
+    case 1: launch_rows_tt<T, EPI, 1>(a, p, s, ev); break;
+    case 2: launch_rows_tt<T, EPI, 2>(a, p, s, ev); break;
+    case 3: launch_rows_tt<T, EPI, 3>(a, p, s, ev); break;
+    default: launch_rows_tt<T, EPI, 4>(a, p, s, ev); break;
   }
 }
 
 template <typename T>
-void launch_linear_rows(const LinArgs& a0, int epilogue, hipStream_t s, const LaunchEvents* ev) {
-  LinArgs a = a0;
-  a.KS = rows_ks(a.N >> 4, a.K >> 5, epilogue);
+void launch_linear_rows(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev) {
   switch (epilogue) {
     case EPI_QKV: launch_rows_epi<T, EPI_QKV>(a, s, ev); break;
     case EPI_SWIGLU: launch_rows_epi<T, EPI_SWIGLU>(a, s, ev); break;
@@ -419,8 +381,8 @@ static bool allow_rows() {
   auto allow = [](const void* f) {
     return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ROWS_LDS) == hipSuccess;
   };
-  bool ok = allow(reinterpret_cast<const void*>(&k_linear_rows<T, EPI, 3, TT, rows_depth(3, TT), 512, false>));
-  if constexpr (TT <= 3) ok &= allow(reinterpret_cast<const void*>(&k_linear_rows<T, EPI, 5, TT, rows_depth(5, TT), 512, false>));
+  bool ok = allow(reinterpret_cast<const void*>(&k_linear_rows<T, EPI, 3, TT, rows_depth(3, TT), ROWS_THREADS, false>));
+  if constexpr (TT <= 3) ok &= allow(reinterpret_cast<const void*>(&k_linear_rows<T, EPI, 5, TT, rows_depth(5, TT), ROWS_THREADS, false>));
   return ok;
 }
 

@@ -1,0 +1,56 @@
+"""The launch rules of the linear kernels (csrc/dispatch.h) over every shape the library accepts, on the host: each
+rule is compiled into a small program that walks the sizes and prints the first launch that breaks a bound of its
+kernel."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2609_36590_amd", "csrc")
+
+HEAD = r"""
+#include "dispatch.h"
+#include <cstdio>
+#include <cstdlib>
+using namespace seedk;
+#define CHECK(c, ...) do { if (!(c)) { printf("%s: ", #c); printf(__VA_ARGS__); printf("\n"); exit(1); } } while (0)
+static const int ROWS[] = {1, 2, 5, 15, 16, 17, 31, 32, 33, 40, 47, 48, 49, 63, 64};
+"""
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text(HEAD + body)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    return r.stdout
+
+
+def test_decode_projections_fit_their_kernels(tmp_path):
+    """Threads within the launch bounds, partial sums within LDS, every n-tile and k-range covered, and k-ranges that
+    depend on the weight shape alone: hidden and ffn sizes of any multiple of 32 up to 32768 as K, N from one n-tile
+    to a wide ffn, with the rows of every decode pass."""
+    _run(tmp_path, r"""
+int main() {
+  const int wide[] = {384, 511, 512, 768, 1216, 1280, 1281, 2047, 3584, 4096};
+  for (int kt = 1; kt <= 1024; ++kt)
+    for (int i = 1; i <= 300 + 10; ++i) {
+      const int nt = i <= 300 ? i : wide[i - 301];
+      for (int epi : {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_HEAD})
+        for (int es : {2, 4})
+          for (int M : ROWS) {
+            const RowsPlan p = rows_plan(nt * 16, kt * 32, M, epi, es);
+            CHECK(p.threads <= (p.part ? ROWS_PART_THREADS : ROWS_THREADS),
+                  "N %d K %d rows %d epilogue %d: %d threads", nt * 16, kt * 32, M, epi, p.threads);
+            CHECK(p.lds <= ROWS_LDS, "N %d K %d rows %d epilogue %d: %zu bytes", nt * 16, kt * 32, M, epi, p.lds);
+            CHECK(p.KS >= 1 && p.KS <= std::min(kt, ROWS_KS_MAX), "N %d K %d epilogue %d: %d k-ranges", nt * 16, kt * 32, epi, p.KS);
+            CHECK(p.KS == rows_plan(nt * 16, kt * 32, 1, epi, es).KS, "N %d K %d rows %d: k-ranges", nt * 16, kt * 32, M);
+            CHECK(!p.part || epi == EPI_RESID, "N %d K %d epilogue %d", nt * 16, kt * 32, epi);
+            CHECK(p.gx * p.NT >= nt && (p.gx - 1) * p.NT < nt, "N %d: %d workgroups of %d", nt * 16, p.gx, p.NT);
+            CHECK(p.part ? p.gy * 2 >= p.KS && p.gy * 2 <= p.KS + 1 : p.gy == 1 && p.threads == 64 * p.KS,
+                  "K %d: %d k-ranges in %d x %d threads", kt * 32, p.KS, p.gy, p.threads);
+            CHECK(p.NT == 1 || p.NT == 2 || p.NT == 3 || (p.NT == 5 && (p.part || M <= 48)), "%d n-tiles, %d rows", p.NT, M);
+          }
+    }
+}
+""")

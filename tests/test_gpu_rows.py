@@ -21,6 +21,8 @@ SHAPES = {
     "long-k": dict(hidden=96, n_heads=3, n_kv_heads=1, head_dim=64, ffn=4640, vocab=592),
     # QKV: 272 n-tiles of 9 k-tiles, O: 128 k-tiles; a head of 2049 n-tiles
     "heads": dict(hidden=288, n_heads=32, n_kv_heads=1, head_dim=128, ffn=8192, vocab=32784),
+    # QKV (20 n-tiles) and gate/up (12) of 145 k-tiles: long K into a narrow N outside the residual projections
+    "narrow-long-k": dict(hidden=4640, n_heads=3, n_kv_heads=1, head_dim=64, ffn=96, vocab=64),
 }
 ROWS = ((1, 0), (1, 4), (1, 15), (17, 0), (8, 3), (11, 2), (12, 3), (7, 6), (16, 3))   # sequences, drafts
 
