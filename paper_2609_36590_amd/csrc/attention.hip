@@ -36,6 +36,7 @@
 #include "device_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace seedk {
 
@@ -578,7 +579,7 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a, PassSegs 
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o_c[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  auto consume = [&](int s, int slot) __attribute__((always_inline)) {
+  auto consume = [&](int s, int slot, auto tail) __attribute__((always_inline)) {
     const bool od = SPEC && s >= ns_deep;
     const int p0 = od ? (own0 + (s - ns_deep) * PB) * 16 : s * PB * 16;   // the stage's first position
     const int lim_min = SPEC && !od ? lo_min : hi_min, lim_max = SPEC && !od ? lo_max : hi_max;
@@ -675,12 +676,26 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a, PassSegs 
         }
       l_c[qt] += sum;
     }
+    // tail: blocks no query of the wave sees may hold anything (not written yet, or of a later token that
+    // overflowed); a probability of 0 times a value that is not finite is not 0, so those values are cleared
+    const int nvis = __builtin_amdgcn_readfirstlane((lim_max - p0 + 15) >> 4);
+    unsigned keep[PB];
+#pragma unroll
+    for (int u = 0; u < PB; ++u) keep[u] = u < nvis ? ~0u : 0u;
     vread(vf[0], 0);
 #pragma unroll
     for (int g = 0; g < NVG; ++g) {
       if (g + 1 < NVG) vread(vf[(g + 1) & 1], g + 1);
       __builtin_amdgcn_sched_barrier(0);
       const int pr = g >> 1, dt0 = (g & 1) * VG;
+      if constexpr (decltype(tail)::value) {
+#pragma unroll
+        for (int i = 0; i < VG; ++i) {
+          u32x4 v = __builtin_bit_cast(u32x4, vf[g & 1][i]);
+          v[0] &= keep[2 * pr], v[1] &= keep[2 * pr], v[2] &= keep[2 * pr + 1], v[3] &= keep[2 * pr + 1];
+          vf[g & 1][i] = __builtin_bit_cast(bf16x8, v);
+        }
+      }
 #pragma unroll
       for (int i = 0; i < VG; ++i)
 #pragma unroll
@@ -695,6 +710,9 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a, PassSegs 
     }
   };
 
+  // stages that the first row sees whole, and so every wave all their blocks; the rest take a loop of their own
+  // (a branch beside the products spilled 38 registers and took 10% of a 16k-token prefill)
+  const int s_tail = (SPEC ? a.row_pos[r0] / a.s_block * a.s_block : a.row_pos[r0] + 1) / (PB * 16);
   if (s1 > s0) {
     idload(s0);
     gload(s0);
@@ -702,12 +720,22 @@ __global__ void __launch_bounds__(256, 2) k_attention_pass(AttnArgs a, PassSegs 
     gload(s0 + 1);
     __syncthreads();
     // slot s & 1 holds stage s; the other one was read before the last barrier
-    for (int s = s0; s < s1; ++s) {
+    const int sm = min(s1, s_tail);
+    int s = s0;
+    for (; s < sm; ++s) {
       const int slot = (s - s0) & 1;
       lstore(slot ^ 1);
       gload(s + 2);
       __builtin_amdgcn_sched_barrier(0);
-      consume(s, slot);
+      consume(s, slot, std::false_type{});
+      __syncthreads();
+    }
+    for (; s < s1; ++s) {
+      const int slot = (s - s0) & 1;
+      lstore(slot ^ 1);
+      gload(s + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(s, slot, std::true_type{});
       __syncthreads();
     }
   }

@@ -56,3 +56,34 @@ def test_second_pass_splits_positions(dtype):
     # passes of 4096 and 103 rows; blocks of 30 cross row 4096
     cfg = BASE.replace(name="pass-split", n_layers=2, n_dec_layers=1, n_heads=4, n_kv_heads=1, head_dim=64, dtype=dtype)
     _check(cfg, (4200,), 30)
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("heads,kv,n,at", [(4, 1, 200, 120), (32, 16, 2090, 1085)], ids=["64-vectors", "128-vectors"])
+def test_rows_before_a_token_that_overflows(heads, kv, n, at, dtype):
+    """A token whose embedding is not finite spoils its own row and what attends to it, and no earlier block of 16
+    positions, although those rows share its 64-position stage (and, with 2 heads per KV head, its row-block of 64):
+    their keys, values and logits are what the prompt has with any other token there. (fp32 row-blocks stream whole
+    tiles up to their own last row: 32 rows with 2 heads per KV head.)"""
+    cfg = BASE.replace(name="pass-overflow", n_heads=heads, n_kv_heads=kv, head_dim=64, dtype=dtype)
+    w = synth.make_weights(cfg, seed=11)
+    w["embed"][5] = np.float32("nan") if dtype == synth.F32 else 0x7FC0
+    g = np.random.default_rng(3)
+    x = g.integers(6, cfg.vocab, n).astype(np.int32)
+    bad = x.copy()
+    bad[at] = 5
+    clean = at // 32 * 32 if dtype == synth.F32 and heads == 32 else at // 16 * 16
+    dec = decoder(cfg, w, max_batch=1, max_ctx=n + 8, max_draft=2)
+    try:
+        got = []
+        for t in (x, bad):
+            say(f"[gpu] a token that overflows, {n} tokens, {dtype}")
+            lg, _, _ = dec.spec_forward(t, 16)
+            got.append([np.delete(lg[:clean], 5, axis=1)] + [dec.read_kv(0, i, 0, clean) for i in range(cfg.n_layers)])
+        assert np.all(np.isfinite(got[0][0]))
+        np.testing.assert_array_equal(got[0][0], got[1][0])
+        for i in range(1, cfg.n_layers + 1):
+            np.testing.assert_array_equal(got[0][i][0], got[1][i][0])
+            np.testing.assert_array_equal(got[0][i][1], got[1][i][1])
+    finally:
+        dec.close()
