@@ -8,11 +8,15 @@ namespace seedk {
 
 enum Epilogue { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
 
+// LDS of a CU, all of which one workgroup may take (seed_create refuses a device that grants less)
+constexpr size_t LDS_MAX = 160 * 1024;
+constexpr int ACT_TILE = 2048;      // bytes of a packed activation tile (layout in kernels.h)
+
 constexpr int ROWS_HEAD_NT = 2;     // n-tiles per argmax partial of a small vocabulary's head (rows.hip)
 constexpr int ROWS_KS_MAX = 16;     // k-ranges of a decode pass's projection
 constexpr int ROWS_THREADS = 512;   // largest workgroup of k_linear_rows (its launch bounds),
 constexpr int ROWS_PART_THREADS = 128;   // of the form whose k-ranges go to several workgroups
-constexpr size_t ROWS_LDS = 150 * 1024;   // partial sums of one workgroup
+constexpr size_t ROWS_LDS = 150 * 1024;   // partial sums of one workgroup (its row scales take 256 bytes more)
 
 inline size_t rows_lds(int NT, int KS, int M) { return (size_t)NT * KS * M * 16 * sizeof(float); }
 
@@ -73,6 +77,42 @@ inline RowsPlan rows_plan(int N, int K, int M, int epilogue, int esize) {
   p.threads = p.part ? ROWS_PART_THREADS : 64 * p.KS;
   p.lds = p.part ? 0 : rows_lds(p.NT, p.KS, M);
   return p;
+}
+
+// ---- LM head of a decode pass ----
+constexpr int HEAD_NT = 8;   // n-tiles per argmax partial of the head's own kernels (waves of a workgroup)
+constexpr int HEAD_CK = 8;   // k-tiles per chunk that k_head_chunked stages
+
+// Small vocabularies split K over waves like the other projections: at 1024 tokens the head's kernels would have 8
+// workgroups, each wave a chain over all of K (5 rows 19 us, 40 rows 55). The line is on the safe side of that,
+// not where the two meet: a verification with one thin layer of hidden size 2560 takes, at 1 / 5 / 17 / 40 / 64 rows, 87 / 95 /
+// 114 / 152 / 187 us with 32000 tokens (row kernel) and 84 / 92 / 96 / 118 / 139 with 32768 (head's kernels).
+inline bool head_by_rows(int N) { return N < 32768; }
+// n-tiles per argmax partial
+inline int head_group(int N) { return head_by_rows(N) ? ROWS_HEAD_NT : HEAD_NT; }
+
+// k_head_lds stages all rows (M <= 16): 32 bytes per row and 8 features, one zero slot, the sums and row scales
+inline size_t head_lds_bytes(int M, int K) {
+  return (size_t)(K >> 5) * 4 * M * 32 + 32 + (size_t)(HEAD_NT * M + 1) * 16 * sizeof(float);
+}
+
+struct HeadPlan {
+  bool chunked;   // k_head_chunked, NT n-tiles per wave; else k_head_lds
+  int NT, grid;
+  size_t lds;
+};
+
+inline HeadPlan head_plan(int N, int K, int M, int esize) {
+  const int n_tiles = N >> 4;
+  if (M <= 16 && head_lds_bytes(M, K) <= LDS_MAX)
+    return {false, 1, (n_tiles + HEAD_NT - 1) / HEAD_NT, head_lds_bytes(M, K)};
+  // 5 n-tiles per wave (the largest whose sums and operands fit the registers of two waves per SIMD) from the
+  // vocabulary on that makes half a round of workgroups of them, one per CU. At 151936 tokens, one round, 31 rows of the
+  // 28-layer shape take 120 us against 146 with 16 waves of one n-tile. At the line itself one n-tile is no
+  // slower: a verification with one thin layer of hidden size 2560 at 17 / 31 / 40 / 64 rows takes 143 / 153 / 190 / 225 us with
+  // 81904 tokens (1 n-tile) and 162 / 176 / 195 / 229 with 81920 (5).
+  const int nt = esize == 2 && n_tiles >= 128 * 5 * HEAD_NT ? 5 : 1, per = nt * HEAD_NT;
+  return {true, nt, (n_tiles + per - 1) / per, 2 * (size_t)((M + 15) / 16) * HEAD_CK * ACT_TILE};
 }
 
 }  // namespace seedk

@@ -61,7 +61,7 @@ __device__ __forceinline__ typename ET<T>::B lds_slot(const char* p) {
   return ET<T>::join(reinterpret_cast<const uint4*>(p)[0], reinterpret_cast<const uint4*>(p)[1]);
 }
 
-__host__ __device__ inline size_t lds_x_bytes(int M, int nkt) { return (size_t)nkt * 4 * M * 32 + 32; }
+__device__ inline size_t lds_x_bytes(int M, int nkt) { return (size_t)nkt * 4 * M * 32 + 32; }
 
 // ---------------------------------------------------------------------------------------------
 // M <= 16 rows (one MFMA tile): the workgroup (8 waves, one n-tile each) issues its first weight
@@ -185,8 +185,6 @@ __global__ void __launch_bounds__(64 * HEAD_NT) k_head_lds(LinArgs a) {
 // 28-layer shape (622 MB) 146 -> 120 us (5.2 TB/s) against 16 waves of one n-tile each, 594 workgroups in 2.3
 // rounds; 8 k-tiles of weights in flight instead of 4 changed nothing (125 us).
 // ---------------------------------------------------------------------------------------------
-constexpr int HEAD_CK = 8;   // k-tiles per staged chunk
-
 template <typename T, int TT, int NT, int D>
 __global__ void __launch_bounds__(64 * HEAD_NT) k_head_chunked(LinArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -346,45 +344,31 @@ __global__ void __launch_bounds__(256) k_argmax_finalize(const float* val, const
 }
 
 // ---------------------------------------------------------------------------------------------
-// Launchers.
+// Launchers (head_plan in dispatch.h).
 // ---------------------------------------------------------------------------------------------
-static size_t g_lds_limit = 65536;   // dynamic LDS one workgroup may use (set by configure_kernels)
-
-static size_t head_lds_bytes(int M, int K) { return lds_x_bytes(M, K >> 5) + (size_t)(HEAD_NT * M + 1) * 16 * sizeof(float); }
-// n-tiles per argmax partial
-int head_group(int N) { return head_by_rows(N) ? ROWS_HEAD_NT : HEAD_NT; }
-
-template <typename T, int TT, int NT>
-static void launch_head_chunked(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  const int n_tiles = a.N >> 4, per = NT * HEAD_NT;
-  launch(k_head_chunked<T, TT, NT, 4>, dim3((n_tiles + per - 1) / per), dim3(64 * HEAD_NT), 2 * (size_t)TT * HEAD_CK * ACT_TILE,
-         s, ev, a);
-}
-
-// n-tiles per wave: 5 where a round of one workgroup per CU takes the whole vocabulary, or nearly (it is the
-// largest whose sums and operands fit the registers of two waves per SIMD), else 1
 template <typename T, int TT>
-static void launch_head_tt(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
+static void launch_head_chunked(const LinArgs& a, const HeadPlan& p, hipStream_t s, const LaunchEvents* ev) {
   if constexpr (sizeof(T) == 2) {
-    if ((a.N >> 4) >= 128 * 5 * HEAD_NT) {
-      launch_head_chunked<T, TT, 5>(a, s, ev);
+    if (p.NT == 5) {
+      launch(k_head_chunked<T, TT, 5, 4>, dim3(p.grid), dim3(64 * HEAD_NT), p.lds, s, ev, a);
       return;
     }
   }
-  launch_head_chunked<T, TT, 1>(a, s, ev);
+  launch(k_head_chunked<T, TT, 1, 4>, dim3(p.grid), dim3(64 * HEAD_NT), p.lds, s, ev, a);
 }
 
 template <typename T>
 static void launch_head(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
-  if (a.M <= 16 && head_lds_bytes(a.M, a.K) <= g_lds_limit) {
-    launch(k_head_lds<T>, dim3(((a.N >> 4) + HEAD_NT - 1) / HEAD_NT), dim3(64 * HEAD_NT), head_lds_bytes(a.M, a.K), s, ev, a);
+  const HeadPlan p = head_plan(a.N, a.K, a.M, sizeof(T));
+  if (!p.chunked) {
+    launch(k_head_lds<T>, dim3(p.grid), dim3(64 * HEAD_NT), p.lds, s, ev, a);
     return;
   }
   switch ((a.M + 15) / 16) {
-    case 1: launch_head_tt<T, 1>(a, s, ev); break;
-    case 2: launch_head_tt<T, 2>(a, s, ev); break;
-    case 3: launch_head_tt<T, 3>(a, s, ev); break;
-    default: launch_head_tt<T, 4>(a, s, ev); break;
+    case 1: launch_head_chunked<T, 1>(a, p, s, ev); break;
+    case 2: launch_head_chunked<T, 2>(a, p, s, ev); break;
+    case 3: launch_head_chunked<T, 3>(a, p, s, ev); break;
+    default: launch_head_chunked<T, 4>(a, p, s, ev); break;
   }
 }
 
@@ -401,30 +385,12 @@ void launch_argmax_finalize(const float* val, const int* idx, int stride, int n_
                      host_stride);
 }
 
-// Dynamic LDS available to one workgroup: the device's per-block limit, raised to the opt-in limit
-// when every kernel accepted it (failed opt-ins are cleared and ignored).
-template <typename T>
-static bool allow_big_lds(int bytes) {
-  const void* fns[] = {reinterpret_cast<const void*>(&k_head_lds<T>), reinterpret_cast<const void*>(&k_head_chunked<T, 3, 1, 4>),
-                       reinterpret_cast<const void*>(&k_head_chunked<T, 4, 1, 4>),
-                       reinterpret_cast<const void*>(&k_head_chunked<T, 3, sizeof(T) == 2 ? 5 : 1, 4>),
-                       reinterpret_cast<const void*>(&k_head_chunked<T, 4, sizeof(T) == 2 ? 5 : 1, 4>)};
-  bool ok = true;
-  for (const void* f : fns) ok &= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
-  return ok && rows_allow_lds<T>();
-}
-
-hipError_t configure_kernels(int bf16) {
-  int dev = 0, base = 0, optin = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
-  if (hipDeviceGetAttribute(&base, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && base > 0)
-    g_lds_limit = (size_t)base;
-  if (hipDeviceGetAttribute(&optin, hipDeviceAttributeSharedMemPerBlockOptin, dev) == hipSuccess &&
-      (size_t)optin > g_lds_limit) {
-    if (bf16 ? allow_big_lds<uint16_t>(optin) : allow_big_lds<float>(optin)) g_lds_limit = (size_t)optin;
-  }
-  (void)hipGetLastError();
-  return hipSuccess;
+hipError_t check_device() {
+  int dev = 0, lds = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+  if (e != hipSuccess) return e;
+  return (size_t)lds >= LDS_MAX ? hipSuccess : hipErrorInvalidDevice;
 }
 
 template void launch_linear<uint16_t>(const LinArgs&, int, hipStream_t, const LaunchEvents*);

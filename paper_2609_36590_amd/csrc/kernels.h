@@ -32,7 +32,6 @@ namespace seedk {
 // keep a row's slots in one 128-byte line (one row reads whole lines: 4 draft steps 998 us, 1033 in
 // operand order); passes of more rows keep them in operand order, so that a plane is one wave's 1 KB
 // load without gaps (8 x 5 rows through 4 layers: 655 us, 695 as lines).
-constexpr int ACT_TILE = 2048;
 __host__ __device__ inline bool act_frag(int M) { return M > 16; }
 __host__ __device__ inline int act_plane(bool frag) { return frag ? 1024 : 64; }
 __host__ __device__ inline int act_slot(bool frag, int row16, int kg) {
@@ -190,12 +189,6 @@ struct DevState {
   int stamp_cap;
 };
 
-// n-tiles per argmax partial of the LM head's own kernels (waves of a workgroup); ROWS_HEAD_NT of small vocabularies
-constexpr int HEAD_NT = 8;
-// Small vocabularies split K over waves like the other projections: at 1024 tokens the head's kernels
-// would have 8 workgroups, each wave a chain over all of K (5 rows 19 us, 40 rows 55).
-__host__ __device__ inline bool head_by_rows(int N) { return N < 32768; }
-int head_group(int N);   // n-tiles per argmax partial
 constexpr int PF_SPLIT_MAX = 3;     // position splits of the one-launch pass attention,
 constexpr int PF_SPLIT_ROWS = 1024;  // of passes of at most this many rows
 constexpr int WIDE_SPLIT_MAX = 4;   // k-ranges of a split wide pass (its partials: WIDE_SPLIT_MAX x rows x N floats)
@@ -214,8 +207,6 @@ template <typename T>
 void launch_linear_rows(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev);
 template <typename T>
 void launch_linear_wide(const LinArgs& a, int epilogue, hipStream_t s, const LaunchEvents* ev);
-template <typename T>
-bool rows_allow_lds();
 // Attention partials per group of span positions (the final output when the rows see one group).
 template <typename T>
 void launch_attention(const AttnArgs& a, hipStream_t s, const LaunchEvents* ev = nullptr);
@@ -290,6 +281,6 @@ void launch_pack(const void* src, void* dst, const int* dst_row, int rows, int K
 void launch_to_f32(const void* src, int src_is_bf16, float* dst, long long n, hipStream_t s);
 void launch_fill_u32(void* dst, unsigned value, long long n_words, hipStream_t s);
 
-// allow the linear kernels to use more than 64 KB of LDS (once per process and dtype)
-hipError_t configure_kernels(int bf16);
+// whether the current device grants a workgroup the LDS that the launch rules count on
+hipError_t check_device();
 }  // namespace seedk

@@ -375,28 +375,6 @@ void launch_linear_rows(const LinArgs& a, int epilogue, hipStream_t s, const Lau
   }
 }
 
-// Partial sums beyond 64 KB: 5 or 3 n-tiles of 17 rows or more (2 n-tiles x 8 ranges x 64 rows are 64 KB).
-template <typename T, int EPI, int TT>
-static bool allow_rows() {
-  auto allow = [](const void* f) {
-    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ROWS_LDS) == hipSuccess;
-  };
-  bool ok = allow(reinterpret_cast<const void*>(&k_linear_rows<T, EPI, 3, TT, rows_depth(3, TT), ROWS_THREADS, false>));
-  if constexpr (TT <= 3) ok &= allow(reinterpret_cast<const void*>(&k_linear_rows<T, EPI, 5, TT, rows_depth(5, TT), ROWS_THREADS, false>));
-  return ok;
-}
-
-template <typename T>
-bool rows_allow_lds() {
-  if constexpr (sizeof(T) == 4) return true;   // one n-tile
-  else
-    return allow_rows<T, EPI_QKV, 2>() && allow_rows<T, EPI_QKV, 3>() && allow_rows<T, EPI_QKV, 4>() &&
-           allow_rows<T, EPI_SWIGLU, 2>() && allow_rows<T, EPI_SWIGLU, 3>() && allow_rows<T, EPI_SWIGLU, 4>() &&
-           allow_rows<T, EPI_RESID, 2>() && allow_rows<T, EPI_RESID, 3>() && allow_rows<T, EPI_RESID, 4>();
-}
-
-template bool rows_allow_lds<uint16_t>();
-template bool rows_allow_lds<float>();
 template void launch_linear_rows<uint16_t>(const LinArgs&, int, hipStream_t, const LaunchEvents*);
 template void launch_linear_rows<float>(const LinArgs&, int, hipStream_t, const LaunchEvents*);
 

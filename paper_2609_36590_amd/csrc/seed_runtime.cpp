@@ -1202,7 +1202,7 @@ seed_status seed_create(const seed_config* cfg, void* hip_stream, void* weight_a
   if (!weight_arena || !kv_pool || !workspace) return fail(SEED_ERR_ARG, "buffers must not be NULL");
   if (((uintptr_t)weight_arena | (uintptr_t)kv_pool | (uintptr_t)workspace) & 255)
     return fail(SEED_ERR_ARG, "buffers must be 256-byte aligned");
-  HIPCHK(configure_kernels(cfg->dtype == SEED_BF16));
+  HIPCHK(check_device());
   seed_ctx* c = new seed_ctx();
   c->p = make_plan(*cfg);
   c->s = reinterpret_cast<hipStream_t>(hip_stream);

@@ -54,3 +54,24 @@ int main() {
     }
 }
 """)
+
+
+def test_heads_fit_their_kernels(tmp_path):
+    """LDS of the LM head's kernels, for hidden sizes of any multiple of 32 up to 32768 and every row count: the rows
+    staged whole only while they fit, chunks within the CU's LDS beside the row scales, the sums within the chunks."""
+    _run(tmp_path, r"""
+int main() {
+  const int tiles[] = {1, 63, 64, 2000, 2047, 2048, 2049, 5119, 5120, 5121, 9496, 16384, 16385};
+  for (int kt = 1; kt <= 1024; ++kt)
+    for (int nt : tiles)
+      for (int es : {2, 4})
+        for (int M = 1; M <= 64; ++M) {
+          const HeadPlan p = head_plan(nt * 16, kt * 32, M, es);
+          CHECK(p.lds + (p.chunked ? 256 : 0) <= LDS_MAX, "N %d K %d rows %d: %zu bytes", nt * 16, kt * 32, M, p.lds);
+          CHECK(p.chunked || M <= 16, "N %d K %d rows %d", nt * 16, kt * 32, M);
+          CHECK(!p.chunked || (size_t)HEAD_NT * M * 64 <= p.lds, "rows %d: %zu bytes for the sums", M, p.lds);
+          CHECK(p.grid * p.NT * HEAD_NT >= nt && (p.grid - 1) * p.NT * HEAD_NT < nt, "N %d: %d workgroups", nt * 16, p.grid);
+        }
+  static_assert(ROWS_LDS + 256 <= LDS_MAX, "the row kernel's sums and row scales");
+}
+""")
