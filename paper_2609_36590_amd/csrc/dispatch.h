@@ -115,4 +115,10 @@ inline HeadPlan head_plan(int N, int K, int M, int esize) {
   return {true, nt, (n_tiles + per - 1) / per, 2 * (size_t)((M + 15) / 16) * HEAD_CK * ACT_TILE};
 }
 
+// ---- residual projections of a wide pass ----
+// Their k-ranges: 2 for N <= 4096, whose workgroups do not fill the chip otherwise (1024 rows x 2560: 128 of 20
+// n-tiles); a function of the weight shape only, so that a row's output does not depend on the pass's row count.
+constexpr int WIDE_SPLIT_MAX = 2;   // (partials: WIDE_SPLIT_MAX x rows x N floats)
+inline int wide_split(int n_tiles, int KT) { return std::max(1, std::min(n_tiles <= 256 ? WIDE_SPLIT_MAX : 1, KT / 4)); }
+
 }  // namespace seedk

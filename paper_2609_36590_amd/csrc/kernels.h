@@ -191,7 +191,6 @@ struct DevState {
 
 constexpr int PF_SPLIT_MAX = 3;     // position splits of the one-launch pass attention,
 constexpr int PF_SPLIT_ROWS = 1024;  // of passes of at most this many rows
-constexpr int WIDE_SPLIT_MAX = 4;   // k-ranges of a split wide pass (its partials: WIDE_SPLIT_MAX x rows x N floats)
 
 // Optional timing events stamped by the launches themselves (hipExtLaunchKernel): `start` at the
 // start of the first kernel of the operation, `stop` at the end of its last kernel.

@@ -314,10 +314,6 @@ __global__ void __launch_bounds__(256) k_wide_resid(LinArgs a) {
 // ---------------------------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------------------------
-// k-ranges of a residual projection: a function of the weight shape only, so that a row's output
-// does not depend on the pass's row count.
-static int wide_split(int n_tiles, int KT) { return std::max(1, std::min(n_tiles <= 256 ? 2 : 1, KT / 4)); }
-
 template <typename T, int EPI, int NI>
 static void launch_wide_tile(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
   const int n_tiles = a.N >> 4, m_tiles = (a.M + 15) >> 4;

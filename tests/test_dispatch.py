@@ -56,6 +56,22 @@ int main() {
 """)
 
 
+def test_split_wide_passes_use_all_their_partials(tmp_path):
+    """k-ranges that leave none empty, and no more partials in the workspace than some shape uses."""
+    _run(tmp_path, r"""
+int main() {
+  int most = 0;
+  for (int kt = 1; kt <= 2048; ++kt)
+    for (int nt = 2; nt <= 2048; ++nt) {
+      const int s = wide_split(nt, kt);
+      CHECK(s >= 1 && s <= kt && s <= WIDE_SPLIT_MAX, "N %d K %d: %d", nt * 16, kt * 32, s);
+      most = std::max(most, s);
+    }
+  CHECK(most == WIDE_SPLIT_MAX, "partials for %d k-ranges, %d used", WIDE_SPLIT_MAX, most);
+}
+""")
+
+
 def test_heads_fit_their_kernels(tmp_path):
     """LDS of the LM head's kernels, for hidden sizes of any multiple of 32 up to 32768 and every row count: the rows
     staged whole only while they fit, chunks within the CU's LDS beside the row scales, the sums within the chunks."""
