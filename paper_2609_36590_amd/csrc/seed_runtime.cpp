@@ -743,8 +743,9 @@ seed_status do_prefill(seed_ctx* c, const std::vector<int>& tokens_packed) {
   const Plan& p = c->p;
   const int B = c->B;
   // committed tokens + state: the decode state's arrays from the committed lengths to the tokens are one
-  // region of the workspace, written with one copy (rounds and counters among them start at zero)
-  std::vector<char> state(p.o_trace - p.o_t, 0);
+  // region of the workspace, written with one copy (rounds and counters among them start at zero), up to the
+  // tokens of the sequences the call has: the rest are never read
+  std::vector<char> state(p.o_tokens - p.o_t + (size_t)B * p.tstride * 4, 0);
   auto at = [&](size_t off) { return reinterpret_cast<int*>(state.data() + (off - p.o_t)); };
   size_t o = 0;
   for (int b = 0; b < B; ++b) {
@@ -755,9 +756,7 @@ seed_status do_prefill(seed_ctx* c, const std::vector<int>& tokens_packed) {
     at(p.o_active)[b] = 1;
     at(p.o_drafts)[(size_t)b * p.dstride] = tokens_packed[o - 1];
   }
-  // tokens of sequences the call does not have are never read
-  const size_t bytes = p.o_tokens - p.o_t + (size_t)B * p.tstride * 4;
-  HIPCHK(hipMemcpyAsync(c->WS + p.o_t, state.data(), bytes, hipMemcpyHostToDevice, c->s));
+  HIPCHK(hipMemcpyAsync(c->WS + p.o_t, state.data(), state.size(), hipMemcpyHostToDevice, c->s));
   launch_fill_u32(c->ws<int>(p.o_stamp), 0, (long long)p.log_cap * 6, c->s);
   HIPCHK(hipGetLastError());
   // run the full model over X[0..t-2]; X[t-1] stays pending (its cache entry would be dropped

@@ -360,3 +360,33 @@ def test_missing_weights_are_reported():
         host.close()
     finally:
         dec.close()
+
+
+def test_prefill_cost_does_not_grow_with_the_batch_capacity():
+    """One prompt of a decoder with room for 64 sequences of 262144 positions: the call prepares the tokens of the
+    sequences it has (1 MB), not of all it could have (64 MB, 12 ms of host time). Prefill takes 0.5 ms here (0.13
+    with room for one sequence; the list of free cache blocks is the difference)."""
+    import time
+
+    import torch
+
+    cfg = synth.C1_TINY.replace(name="one-of-many", n_layers=1, n_dec_layers=1, hidden=32, n_heads=1, n_kv_heads=1,
+                                head_dim=64, ffn=32, vocab=16, dtype=synth.BF16)
+    w = synth.make_weights(cfg, seed=1)
+    best = {}
+    for batch in (1, 64):
+        dec = decoder(cfg, w, max_batch=batch, max_ctx=1 << 18, max_draft=0)
+        try:
+            times = []
+            for _ in range(12):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                dec.prefill([np.arange(8, dtype=np.int32)])
+                torch.cuda.synchronize()
+                times.append(time.perf_counter() - t0)
+            best[batch] = min(times)
+        finally:
+            dec.close()
+            del dec
+    say(f"[gpu] prefill of one prompt: {1e3 * best[1]:.2f} ms, with room for 64: {1e3 * best[64]:.2f} ms")
+    assert best[64] < best[1] + 4e-3
