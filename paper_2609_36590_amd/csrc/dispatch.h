@@ -108,17 +108,39 @@ inline HeadPlan head_plan(int N, int K, int M, int esize) {
     return {false, 1, (n_tiles + HEAD_NT - 1) / HEAD_NT, head_lds_bytes(M, K)};
   // 5 n-tiles per wave (the largest whose sums and operands fit the registers of two waves per SIMD) from the
   // vocabulary on that makes half a round of workgroups of them, one per CU. At 151936 tokens, one round, 31 rows of the
-  // 28-layer shape take 120 us against 146 with 16 waves of one n-tile. At the line itself one n-tile is no
-  // slower: a verification with one thin layer of hidden size 2560 at 17 / 31 / 40 / 64 rows takes 143 / 153 / 190 / 225 us with
+  // 28-layer shape take 120 us against 146 with 16 waves of one n-tile. At the line itself one n-tile is
+  // still the faster: a verification with one thin layer of hidden size 2560 at 17 / 31 / 40 / 64 rows takes 143 / 153 / 190 / 225 us with
   // 81904 tokens (1 n-tile) and 162 / 176 / 195 / 229 with 81920 (5).
   const int nt = esize == 2 && n_tiles >= 128 * 5 * HEAD_NT ? 5 : 1, per = nt * HEAD_NT;
   return {true, nt, (n_tiles + per - 1) / per, 2 * (size_t)((M + 15) / 16) * HEAD_CK * ACT_TILE};
 }
 
-// ---- residual projections of a wide pass ----
-// Their k-ranges: 2 for N <= 4096, whose workgroups do not fill the chip otherwise (1024 rows x 2560: 128 of 20
-// n-tiles); a function of the weight shape only, so that a row's output does not depend on the pass's row count.
+// ---- wide passes ----
+constexpr int WIDE_MJ = 4;   // token tiles per workgroup (64 rows)
+
+// K-ranges of the residual projections: 2 for N <= 4096, whose workgroups do not fill the chip otherwise (1024
+// rows x 2560: 128 of 20 n-tiles); a function of the weight shape only, so that a row's output does not depend
+// on the pass's row count.
 constexpr int WIDE_SPLIT_MAX = 2;   // (partials: WIDE_SPLIT_MAX x rows x N floats)
 inline int wide_split(int n_tiles, int KT) { return std::max(1, std::min(n_tiles <= 256 ? WIDE_SPLIT_MAX : 1, KT / 4)); }
+
+// n-tiles per wave: the candidate with the lowest rounds of one workgroup per CU x (n-tiles + a fixed
+// part for the token tiles' staging, which every n-tile of the wave shares), a quarter more when there
+// is one round only (a lone workgroup on a CU has none to overlap its barriers). Measured, us for NI =
+// 3 / 4 / 5 / 6: gate/up (1216 n-tiles) of 1024 rows 189 / 170 / 166 / 183, of 4096 rows NI = 4 / 5 / 6
+// 716 / 678 / 669; QKV (384) of 1024 rows 65 / 78 / 88 / 65; O and down (160 in 2 k-ranges, mean) 77 / 91
+// / 63 / 70. 8 token tiles per workgroup instead of 4 (one wave per SIMD) were slower at every width
+// (prefill of 4 layers 2.92 against 2.26 ms).
+inline int wide_ni(int n_tiles, int M, int S) {
+  const int MT = (((M + 15) >> 4) + WIDE_MJ - 1) / WIDE_MJ;
+  int best = 0;
+  long long best_cost = -1;
+  for (int ni = 6; ni >= 1; --ni) {
+    const long long wgs = (long long)((n_tiles + 4 * ni - 1) / (4 * ni)) * MT * S;
+    const long long rounds = (wgs + 255) / 256, cost = rounds * (10 * ni + 12) * (rounds == 1 ? 5 : 4);
+    if (best_cost < 0 || cost < best_cost) best = ni, best_cost = cost;
+  }
+  return best;
+}
 
 }  // namespace seedk

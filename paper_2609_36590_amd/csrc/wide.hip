@@ -31,7 +31,6 @@ namespace seedk {
 // XCD's 64 resident workgroups share activations too (4096 rows: gate/up 763 us with all 4096 rows of
 // an n-group in a row, 734 in blocks of 1024, 739 of 512, 763 of 2048).
 // ---------------------------------------------------------------------------------------------
-constexpr int WIDE_MJ = 4;    // token tiles per workgroup (64 rows)
 constexpr int WIDE_MTB = 16;  // workgroups (1024 rows) of one n-group in a row
 
 template <typename T, int EPI, int NI>
@@ -312,7 +311,7 @@ __global__ void __launch_bounds__(256) k_wide_resid(LinArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Launchers.
+// Launchers (wide_split and wide_ni in dispatch.h).
 // ---------------------------------------------------------------------------------------------
 template <typename T, int EPI, int NI>
 static void launch_wide_tile(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
@@ -323,27 +322,12 @@ static void launch_wide_tile(const LinArgs& a, hipStream_t s, const LaunchEvents
          s, ev, a);
 }
 
-// n-tiles per wave: the candidate with the lowest rounds of one workgroup per CU x (n-tiles + a fixed
-// part for the token tiles' staging, which every n-tile of the wave shares), a quarter more when there
-// is one round only (a lone workgroup on a CU has none to overlap its barriers). Measured, us for NI =
-// 3 / 4 / 5 / 6: gate/up (1216 n-tiles) of 1024 rows 189 / 170 / 166 / 183, of 4096 rows NI = 4 / 5 / 6
-// 716 / 678 / 669; QKV (384) of 1024 rows 65 / 78 / 88 / 65; O and down (160 in 2 k-ranges, mean) 77 / 91
-// / 63 / 70. 8 token tiles per workgroup instead of 4 (one wave per SIMD) were slower at every width
-// (prefill of 4 layers 2.92 against 2.26 ms).
 template <typename T, int EPI>
 static void launch_wide_epi(const LinArgs& a, hipStream_t s, const LaunchEvents* ev) {
   if constexpr (sizeof(T) == 4) {   // fp32 operands take twice the registers
     launch_wide_tile<T, EPI, 2>(a, s, ev);
   } else {
-    const int n_tiles = a.N >> 4, MT = (((a.M + 15) >> 4) + WIDE_MJ - 1) / WIDE_MJ, S = EPI == EPI_RESID ? a.KS : 1;
-    int best = 0;
-    long long best_cost = -1;
-    for (int ni = 6; ni >= 1; --ni) {
-      const long long wgs = (long long)((n_tiles + 4 * ni - 1) / (4 * ni)) * MT * S;
-      const long long rounds = (wgs + 255) / 256, cost = rounds * (10 * ni + 12) * (rounds == 1 ? 5 : 4);
-      if (best_cost < 0 || cost < best_cost) best = ni, best_cost = cost;
-    }
-    switch (best) {
+    switch (wide_ni(a.N >> 4, a.M, EPI == EPI_RESID ? a.KS : 1)) {
       case 6: launch_wide_tile<T, EPI, 6>(a, s, ev); break;
       case 5: launch_wide_tile<T, EPI, 5>(a, s, ev); break;
       case 4: launch_wide_tile<T, EPI, 4>(a, s, ev); break;

@@ -72,6 +72,31 @@ int main() {
 """)
 
 
+def test_wide_shapes_cover_every_width(tmp_path):
+    """The GPU test's wide shapes pick every number of n-tiles per wave (1 is the only one for its small shapes) in
+    gate/up, the head and the residual projections, each with a wave partly filled or left empty."""
+    from test_gpu_wide import MANY_TILES
+    rows = ", ".join("{%s}" % ", ".join(map(str, s)) for s in MANY_TILES)
+    _run(tmp_path, "static const int S[][6] = {" + rows + "};" + r"""
+static unsigned seen[3];
+static void add(int e, int nt, int M, int S) {
+  const int ni = wide_ni(nt, M, S), last = nt % (4 * ni);
+  if (last % ni || (last && last <= 3 * ni)) seen[e] |= 1u << ni;
+}
+int main() {
+  for (auto& s : S) {
+    const int nt = s[0] / 16, M = s[5];
+    CHECK(M > 1024, "%d rows", M);
+    add(0, 2 * s[3] / 16, M, 1);
+    add(1, s[4] / 16, M, 1);
+    add(2, nt, M, wide_split(nt, s[1] * 2));
+    add(2, nt, M, wide_split(nt, s[3] / 32));
+  }
+  for (int e = 0; e < 3; ++e) CHECK((seen[e] | 2u) == 126u, "projection %d: widths %x", e, seen[e]);
+}
+""")
+
+
 def test_heads_fit_their_kernels(tmp_path):
     """LDS of the LM head's kernels, for hidden sizes of any multiple of 32 up to 32768 and every row count: the rows
     staged whole only while they fit, chunks within the CU's LDS beside the row scales, the sums within the chunks."""
