@@ -32,7 +32,9 @@
 // exact identity of every merge, and the tree's shape depends only on absolute group indices, so
 // a query's result depends only on the positions it attends to, not on how many rows share the
 // pass: verify rows and plain greedy decoding give bit-identical outputs, and so do a sequence
-// decoded alone and inside a batch.
+// decoded alone and inside a batch by one decoder, or by two with the same positions per group
+// (attention_span in dispatch.h: up to 1024 positions of capacity always 64, beyond that the batch
+// capacity may decide).
 #include "device_common.h"
 
 #include <algorithm>
@@ -992,17 +994,6 @@ static void launch_attention_hd(const AttnArgs& a, hipStream_t s, const LaunchEv
     if (q2) launch_attention_qt<T, HD, 2, ATT_CAUSAL>(a, s, ev);
     else launch_attention_qt<T, HD, 1, ATT_CAUSAL>(a, s, ev);
   }
-}
-
-// One sequence: 64 positions per group up to 4096 (at its ~1.2k-position context, 1024-token
-// prompt, 128-position groups leave half the 160 workgroups of a launch out: verification
-// attention 7.9 -> 9.6 us per layer). Several sequences fill the chip sooner: 64 while max_batch (8 at
-// most) x positions stay within 8192, and up to 2048, then 128 (8 ragged sequences of up to 2048 positions:
-// verification attention 18.4 -> 16.2 us per layer and its merge 9.2 -> 7.2 us against 64; at ~2300 positions
-// 19.7 -> 17.4, 256 gave 19.3). 256 beyond 8192 positions (16k contexts).
-int attention_span(int max_ctx, int max_batch) {
-  const int small = max_batch == 1 ? 4096 : std::min(2048, 8192 / std::min(max_batch, 8));
-  return max_ctx <= small ? 64 : (max_ctx <= 8192 ? 128 : 256);
 }
 
 template <typename T>

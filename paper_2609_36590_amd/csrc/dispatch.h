@@ -143,4 +143,18 @@ inline int wide_ni(int n_tiles, int M, int S) {
   return best;
 }
 
+// ---- attention of decode passes ----
+// Positions per attention group for a context capacity and batch capacity (fixed per decoder, so
+// that a query's merge tree depends only on absolute positions).
+// One sequence: 64 positions per group up to 4096 (at its ~1.2k-position context, 1024-token
+// prompt, 128-position groups leave half the 160 workgroups of a launch out: verification
+// attention 7.9 -> 9.6 us per layer). Several sequences fill the chip sooner: 64 while max_batch (8 at
+// most) x positions stay within 8192, and up to 2048, then 128 (8 ragged sequences of up to 2048 positions:
+// verification attention 18.4 -> 16.2 us per layer and its merge 9.2 -> 7.2 us against 64; at ~2300 positions
+// 19.7 -> 17.4, 256 gave 19.3). 256 beyond 8192 positions (16k contexts).
+inline int attention_span(int max_ctx, int max_batch) {
+  const int small = max_batch == 1 ? 4096 : std::min(2048, 8192 / std::min(max_batch, 8));
+  return max_ctx <= small ? 64 : (max_ctx <= 8192 ? 128 : 256);
+}
+
 }  // namespace seedk

@@ -116,3 +116,20 @@ int main() {
   static_assert(ROWS_LDS + 256 <= LDS_MAX, "the row kernel's sums and row scales");
 }
 """)
+
+
+def test_attention_groups(tmp_path):
+    """Positions per group for every pair of capacities: one sequence 64 up to 4096, 128 up to 8192, then 256; several
+    sequences the same from 4097 positions on and 64 up to 1024, in between 64 up to 2048 while the batch capacity is
+    at most 4, else up to 8192 / min(batch, 8). Decoders with the same figure give a sequence the same bits."""
+    _run(tmp_path, r"""
+int main() {
+  for (int b = 1; b <= 64; ++b)
+    for (int n = 2; n <= 20000; ++n) {
+      const int s = attention_span(n, b), one = n <= 4096 ? 64 : n <= 8192 ? 128 : 256;
+      const int small = b == 1 ? 4096 : b <= 4 ? 2048 : 8192 / std::min(b, 8);
+      CHECK(s == (n <= small ? 64 : std::max(one, 128)), "capacity %d, batch %d: %d", n, b, s);
+      CHECK((n > 1024 && n <= 4096) || s == one, "capacity %d, batch %d: %d", n, b, s);
+    }
+}
+""")
