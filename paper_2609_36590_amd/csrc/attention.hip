@@ -446,7 +446,9 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 // online softmax; the output is written directly. The decode kernel above spreads positions over groups
 // of workgroups and merges partials, which suits a few rows over a long cache. Here the matrix cores
 // (128 MFMAs of 16 cycles per wave and stage at QT = 2) and the softmax's vector instructions (about
-// 1500 cycles) bound it; two waves share a SIMD and overlap them, and both are cut to what is needed:
+// 1500 cycles) bound a stage; two waves share a SIMD and overlap them, and both are cut to what is
+// needed. (A pass of 1024 rows from position 0 is one round of workgroups of 1 to 16 stages: the matrix
+// cores are 16% busy there, MfmaUtil; long caches come to 1.1 PFLOP/s of MFMA work, below.)
 //  * a stage's keys and values are fetched once per workgroup, a stage ahead in registers, and staged
 //    in LDS in MFMA operand order (two slots, one barrier per stage): reads and key writes are
 //    linear, and at QT = 2 the waves read 64 bytes of LDS per CU and MFMA cycle (128 at QT = 1);

@@ -71,7 +71,11 @@ inline RowsPlan rows_plan(int N, int K, int M, int epilogue, int esize) {
   else if (epilogue == EPI_HEAD)
     p.NT = ROWS_HEAD_NT;
   else
-    p.NT = esize == 4 ? 1 : rows_nt(n_tiles, p.KS, M);   // fp32 operands take twice the registers
+    // fp32 operands take twice the registers: 1 n-tile, 2 k-tiles in flight (launch_rows_tt), not tuned further.
+    // Against the kernels that staged rows in LDS, verification of two 4B layers in fp32, whole calls at 1 / 5 / 16 / 17 /
+    // 40 / 64 rows: 358 / 366 / 410 / 493 / 682 / 930 -> 245 / 276 / 341 / 353 / 465 / 572 us (about 55 of it outside the
+    // kernels); four steps of two 28-layer shapes' layers for 8 sequences 955 -> 716.
+    p.NT = esize == 4 ? 1 : rows_nt(n_tiles, p.KS, M);
   p.gx = (n_tiles + p.NT - 1) / p.NT;
   p.gy = p.part ? (p.KS + 1) / 2 : 1;
   p.threads = p.part ? ROWS_PART_THREADS : 64 * p.KS;

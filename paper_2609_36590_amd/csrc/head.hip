@@ -94,8 +94,8 @@ __global__ void __launch_bounds__(64 * HEAD_NT) k_head_lds(LinArgs a) {
   float* s_rs = Y + (size_t)HEAD_NT * M * 16;
   {
     // two batches of 2 slots per thread per round trip: both batches' loads are issued before
-    // either is written, so a workgroup whose rows take several batches (O at 5 rows, the LM head
-    // at more than 3) pays half the round trips. Loads are branch-free (slots past the end reload
+    // either is written, so a workgroup whose rows take several batches (more than 3 rows of 2560)
+    // pays half the round trips. Loads are branch-free (slots past the end reload
     // the last one and are not written) and none is issued after a wait: a load under a branch
     // makes the compiler wait for every load in flight before each write, and a surplus load
     // issued after the first wait would add a round trip to the one-batch case.

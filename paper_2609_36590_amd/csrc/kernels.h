@@ -73,7 +73,9 @@ struct LinArgs {
   float* amax_val;        // per-workgroup argmax partials [M][amax_stride]
   int* amax_idx;
   int amax_stride;
-  float* part;            // passes of more than 64 rows: k-range partials [KS][M][N]
+  // k-range partials [KS][M][N] of the residual projections: of wide passes, and of decode passes of any row
+  // count where there are more than 8 k-ranges
+  float* part;
 };
 
 // Arguments of the split-KV paged attention kernel and its combine kernel.

@@ -185,7 +185,8 @@ Plan make_plan(const seed_config& c) {
   const size_t split_rows = (size_t)PF_SPLIT_MAX * std::min(p.max_rows, PF_SPLIT_ROWS);
   p.o_pf_o = take(split_rows * p.QD * 4);   // split pass attention partials
   p.o_pf_ml = take(split_rows * p.NQ * 2 * 4);
-  // k-range partials of the residual projections (N = H): wide passes, and decode passes of 17..64 rows
+  // k-range partials of the residual projections (N = H): wide passes, and decode passes (1..64 rows) of
+  // projections with more than 8 k-ranges
   p.o_wide_part = take(std::max((size_t)seedk::WIDE_SPLIT_MAX * p.max_rows, (size_t)seedk::ROWS_KS_MAX * MAX_ROWS) * p.H * 4);
   p.o_topk = take((size_t)TOPK_PARTS * (2 * TOPK_MAX + 2) * 4);
   p.o_tdraft = take((size_t)TREE_MAX_STEPS * (TOPK_MAX + 2) * 4 + 16);

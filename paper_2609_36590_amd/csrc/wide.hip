@@ -17,12 +17,15 @@ namespace seedk {
 //  * activations are used by all 4 waves: each fragment is fetched once per workgroup (two k-tiles
 //    in flight in registers), written to one of two LDS slots, and read back one k-tile ahead into
 //    the second of two register sets, so that the MFMAs of a k-tile wait for nothing issued in it.
-// One barrier per k-tile. The matrix cores bound it: 16 cycles per MFMA against, per CU, 64 bytes of
-// LDS per cycle at NI = 5 (of 128) and about 45 of vector memory. Measured (MI355X, 1024 rows, 4B
-// shapes): gate/up 269 -> 166 us (1.23 PFLOP/s of MFMA work, counting both planes), QKV 122 -> 65,
-// O and down 106 -> 63 (mean), the LM head with logits 2110 -> 1306 us, against a kernel that
-// converted fp32 rows to operand pairs in every workgroup; a library bf16 GEMM of the gate/up shape
-// runs at 1.04 PFLOP/s on the same card. Every output is one MFMA chain over its k-range, hi before lo in every
+// One barrier per k-tile. By count the matrix cores are the nearest limit: 16 cycles per MFMA against,
+// per CU, 64 bytes of LDS per cycle at NI = 5 (of 128) and about 45 of vector memory (of 64). They are
+// busy 55% of the time in gate/up, 40% in QKV, 44% in O and down, 58% in the LM head (MfmaUtil, 1024
+// rows): the rest goes to a barrier per 40 MFMAs of a wave, the vector-memory path close behind, and
+// the last round of workgroups. Measured (MI355X, 1024 rows, 4B shapes, passes in a row; the first
+// pass after a pause takes 5-10% longer): gate/up 269 -> 167 us (1.23 PFLOP/s of MFMA work, counting
+// both planes), QKV 122 -> 65, O and down 106 -> 63 (mean), the LM head with logits 2110 -> 1245 us,
+// against a kernel that converted fp32 rows to operand pairs in every workgroup; a library bf16 GEMM
+// of the gate/up shape runs at 1.04 PFLOP/s on the same card. Every output is one MFMA chain over its k-range, hi before lo in every
 // k-tile; these passes write the prompt's cache and the objective's logits, which no decode pass has
 // to reproduce bit for bit.
 // Workgroup order: the token tiles of one n-group are consecutive workgroups of one XCD (workgroup
