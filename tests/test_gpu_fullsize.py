@@ -283,8 +283,8 @@ def test_spec_forward_28l_matches_oracle():
 def test_tree_round_matches_oracle_at_full_size(weights_4b):
     """Dynamic drafting and tree verification on the 4B model after the 1024-token prefill: the
     first step's drafter logits and p0 against the oracle's, the drafted tree where no decision is
-    near a boundary; then a 31-node tree (depth 3, fan-out 10: the split-K and wide-head launch
-    shapes) verified by the GPU, every node's logits within 2e-2 of the oracle's tree verification,
+    near a boundary; then a 31-node tree (depth 3, fan-out 10: the row kernels of two token tiles and
+    the chunked head) verified by the GPU, every node's logits within 2e-2 of the oracle's tree verification,
     path and bonus where the visited nodes' top-2 gaps leave no doubt; finally tree decoding commits
     the GPU's plain greedy tokens."""
     from oracle import tree as ot

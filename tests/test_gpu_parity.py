@@ -20,9 +20,8 @@ CASES = {
     "tiny-f32-damped": (synth.C1_TINY, 0.1, 1e-4),
     "tiny-bf16": (synth.C1_TINY.replace(name="tiny-4L-h256-bf16", dtype=synth.BF16), 1.0, 2e-2),
     "tiny-bf16-damped": (synth.C1_TINY.replace(name="tiny-4L-h256-bf16", dtype=synth.BF16), 0.1, 2e-2),
-    # a wide FFN and 32 query heads: the verification rows' down projection (5 x 8192 and 7 x 8192
-    # activations) is past what the narrow kernel stages whole and runs split-K, while the draft
-    # and plain greedy rows (1 x 8192) stay in the narrow kernel: the bit-exact test compares the two
+    # a wide FFN and 32 query heads: a down projection of 16 k-ranges, which go to several workgroups and are
+    # added by a second kernel, at 1, 5 and 7 rows
     "wide-f32": (WIDE, 1.0, 1e-4),
     "wide-bf16": (WIDE.replace(name="wide-4L-h256-f8192-bf16", dtype=synth.BF16), 1.0, 2e-2),
 }

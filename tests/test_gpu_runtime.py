@@ -228,9 +228,9 @@ WIDE = synth.C1_TINY.replace(name="wide-4L-h256-f8192", ffn=8192, n_heads=32, n_
 
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16], ids=["fp32", "bf16"])
 def test_wide_batch_equals_each_sequence_alone(dtype):
-    """A wide FFN (8192): the batch's verification passes (4 x 5 = 20 rows) run gate/up in the
-    chunked kernel and the other projections split-K, each sequence alone (5 rows) and plain
-    greedy decoding (1 row) the narrow kernels; every sequence's tokens must be identical."""
+    """A wide FFN (8192): the batch's verification passes (4 x 5 = 20 rows) take two token tiles and activations
+    in operand order, each sequence alone (5 rows) and plain greedy decoding (1 row) one tile and
+    activations by rows; every sequence's tokens must be identical."""
     cfg = WIDE.replace(dtype=dtype)
     w = synth.make_weights(cfg, seed=8)
     prompts = _prompts(cfg, [30, 19, 41, 26], seed=15)

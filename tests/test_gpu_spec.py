@@ -2,9 +2,10 @@
 against the oracle's block-by-block loop.
 
 Tiny models (fp32: logits within 1e-4; bf16 weights and caches: 2e-2), block sizes from 1 to
-larger than the sequence; a 100-token sequence runs as one wide pass of 99 rows with a ragged last
-token tile, and an 1100-token one makes blocks straddle the 1024-row passes of the GPU path (rows
-of one block computed in two passes read each other's keys/values from the pass's own cache). Per-row negative log-likelihoods within the logit tolerance (+ rounding of the
+larger than the sequence; 100- and 1100-token sequences run as one wide pass with a ragged last token
+tile, and 4130 tokens make blocks straddle the 4096-row passes of the GPU path (rows of one block computed
+in two passes read each other's keys/values from the pass's own cache; the second pass, 33 rows, takes the
+kernels of narrow passes). Per-row negative log-likelihoods within the logit tolerance (+ rounding of the
 log-sum-exp), L_spec within n times that. The decoder-only split (n_dec = l) must reproduce the
 full model's causal logits for every block size.
 """
@@ -54,9 +55,14 @@ def test_one_ragged_wide_pass():
     _run(synth.C1_TINY, 100, [5, 16, 30], 1e-4, seed=3)
 
 
-def test_blocks_straddle_passes():
-    # 1099 rows: passes of 1024 and 75; blocks of 5 and 30 cross row 1024, blocks of 16 end on it
+def test_one_long_wide_pass():
     _run(synth.C1_TINY, 1100, [5, 16, 30], 1e-4, seed=4)
+
+
+@pytest.mark.parametrize("cfg,tol", [(synth.C1_TINY, 1e-4), (TINY_BF16, 2e-2)], ids=["f32", "bf16"])
+def test_blocks_straddle_passes(cfg, tol):
+    # 4129 rows: passes of 4096 and 33; blocks of 30 cross row 4096, blocks of 16 end on it
+    _run(cfg, 4130, [16, 30], tol, seed=4)
 
 
 def test_two_tokens():

@@ -21,7 +21,7 @@ from paper_2609_36590_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 TINY_BF16 = synth.C1_TINY.replace(name="tiny-4L-h256-bf16", dtype=synth.BF16)
-# a wide FFN and 32 query heads: a depth-1 tree of 11 nodes runs the O and down projections split-K
+# a wide FFN and 32 query heads: the down projection's 16 k-ranges go to several workgroups
 WIDE = synth.C1_TINY.replace(name="wide-4L-h256-f8192", ffn=8192, n_heads=32, n_kv_heads=8, head_dim=128)
 
 

@@ -2,9 +2,10 @@
 oracle: row counts one around a token tile, a workgroup's 64 rows and the narrow passes' 64-row limit;
 one, two and odd numbers of k-tiles (one k-tile cannot split K); and, with more rows and features, every
 number of n-tiles per wave that the launch rule picks, in feature counts that leave a wave or a workgroup partly
-empty (test_dispatch.py checks that these shapes pick them all), with a ragged second block of 1024 rows. With n_dec = l the drafting objective's pass with one block over the sequence is the
-full causal model, so its logits go through every projection and the LM head of both wide passes (the
-prefill and the objective's own). Tolerances are those of the logits everywhere: 1e-4 fp32, 2e-2 bf16.
+empty (test_dispatch.py checks that these shapes pick them all), with a ragged second block of 1024 rows.
+With n_dec = l the drafting objective's pass with one block over the sequence is the full causal model, so
+its logits go through every projection and the LM head of both wide passes (the prefill and the objective's
+own). Tolerances are those of the logits everywhere: 1e-4 fp32, 2e-2 bf16.
 """
 import numpy as np
 import pytest
